@@ -120,7 +120,7 @@ enum {
                               /* structure factors on FP16 matrix cores with      */
                               /* split operands (2) or FP32 matrix cores (1)      */
   CPM_INFO_RS_PLANE = 27      /* 1: the real-space part of b runs the planar      */
-                              /* kernel (atoms on z planes, one image within r_c) */
+                              /* kernel (atoms on z planes, Lz >= 2 r_c)          */
 };
 
 /* Method knobs; they map onto the paper's `fix electrode` keywords and the

@@ -1682,7 +1682,8 @@ void launch_gather_charges(hipStream_t st, int g, int m, int mpad64, const int* 
 // and mpad64 / 64 apart; output rows part[(s * rchunks + chunk) * n + i]).
 // Chunk c takes the 64-charge blocks c, c + rchunks, c + 2 rchunks, ... (so
 // every chunk spans the whole z range of the ordered charges and the
-// workgroups share the work evenly).  Threads map to electrode
+// workgroups share the work evenly); with sub > 1 each block is divided further
+// between sub workgroups (few charges: small systems, single configurations).  Threads map to electrode
 // atoms through amap, which puts the atoms of one z plane, in compact
 // in-plane tiles, into whole waves (-1 pads).  Every wave walks the chunk 64
 // charges at a time on its own: a block whose z range misses the wave's z
@@ -1700,7 +1701,7 @@ void launch_gather_charges(hipStream_t st, int g, int m, int mpad64, const int* 
 constexpr int RS_WAVES = 8;
 
 __global__ void __launch_bounds__(64 * RS_WAVES) k_real_space_b(
-    int g, int n, int m, int mpad64, const int* __restrict__ amap, int nmap,
+    int g, int n, int m, int mpad64, int sub, const int* __restrict__ amap, int nmap,
     const double* __restrict__ ex, const double* __restrict__ ey, const double* __restrict__ ez,
     const double4* __restrict__ cq, const double2* __restrict__ zr, double Lx, double Ly,
     double Lz, double rc, const double* __restrict__ ptab, double* __restrict__ part) {
@@ -1710,7 +1711,9 @@ __global__ void __launch_bounds__(64 * RS_WAVES) k_real_space_b(
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int slot = blockIdx.x * blockDim.x + threadIdx.x;
   const int atom = slot < nmap ? amap[slot] : -1;
-  const int chunk = blockIdx.y, rchunks = gridDim.y;
+  const int chunk = blockIdx.y / sub, rchunks = gridDim.y / sub;
+  const int row = blockIdx.y, rows = gridDim.y;        // row of the partials
+  const bool mine = lane / (64 / sub) == (int)blockIdx.y % sub;   // this workgroup's part of a block
   const int nb64 = mpad64 / 64, nbt = (m + 63) / 64;   // blocks in a row, blocks holding charges
   const double invLx = 1.0 / Lx, invLy = 1.0 / Ly, invLz = 1.0 / Lz, rc2 = rc * rc;
   const double h = rc / RS_NT, inv_h = RS_NT / rc;
@@ -1785,7 +1788,7 @@ __global__ void __launch_bounds__(64 * RS_WAVES) k_real_space_b(
     h2 = hit(step + 3);
     f2 = fetch(step + 3, h2);
     if (hcur) {
-      const bool valid = (chunk + rchunks * blk) * 64 + lane < m;
+      const bool valid = mine && (chunk + rchunks * blk) * 64 + lane < m;
       bool keep = valid && (keep_all_z || (z - Lz * floor((z - wlo) * invLz)) < whi);
       if (!keep_all_x) {
         double d = xw0 - (xlo - rc);
@@ -1860,17 +1863,17 @@ __global__ void __launch_bounds__(64 * RS_WAVES) k_real_space_b(
       wave_lds_sync();
     }
     if (blk == nblk - 1) {
-      if (atom >= 0) part[((size_t)snap * rchunks + chunk) * n + atom] = acc;
+      if (atom >= 0) part[((size_t)snap * rows + row) * n + atom] = acc;
       acc = 0.0;
     }
   }
   if (nblk == 0 && atom >= 0)
-    for (int snap = s0; snap < g; snap += sstep) part[((size_t)snap * rchunks + chunk) * n + atom] = 0.0;
+    for (int snap = s0; snap < g; snap += sstep) part[((size_t)snap * rows + row) * n + atom] = 0.0;
 }
 
 // ---------------------------------------------------------------------------
-// Real-space pair sum for electrodes on z planes when one periodic image at
-// most lies within rc (every cell length >= 2 rc).
+// Real-space pair sum for electrodes on z planes when one periodic image in z
+// at most lies within rc (Lz >= 2 rc).
 //
 // g(r) = (erfc(alpha r) - erfc(eta r)) / r as a polynomial in s = r^2 on each
 // of RP_N intervals of [0, rc] (uniform in r): degree RP_DEG in
@@ -1941,18 +1944,19 @@ void pair_poly_table(double alpha, double eta, double rc, std::vector<double>& t
 // x and y).  The charges of a chunk arrive 64 at a time (z-sorted blocks; a
 // block whose z range misses [z_p - rc, z_p + rc] is skipped unread).  A
 // charge within rc of the plane in z is taken relative to the tile centre,
-// in each image (x, y shifted by at most one cell length) that can come
-// within rc of the tile's bounding box, and appended to the wave's ring of
-// 128 entries:
+// in each image that can come within rc of the tile's bounding box (x, y
+// shifted by at most one cell length; MULTI, for cells shorter than 2 rc: every
+// x and y image in reach; the general kernel tries all of them for every atom,
+// 150 us against 19 us for one configuration of 288 atoms and 100 charges), and
+// appended to the wave's ring of 128 entries:
 //   FP32  (-2 dx, -2 dy) and W = dx^2 + dy^2 - (rc^2 - dz^2) - margin, so that
 //         an atom at (ax, ay) from the centre is within rc when
 //         ax (-2 dx) + ay (-2 dy) + W < -(ax^2 + ay^2)  (screen, margin
 //         above its rounding error);
 //   FP64  (dx, dy, dz^2, q) for the exact test and g.
 // Every 64 entries each lane screens them into a 64-bit mask and evaluates
-// the marked ones in FP64 (s < rc^2 exactly).  Two images of one charge are
-// 2 rc or more apart, so an atom meets at most one of them within rc.  The
-// summation order of an atom is fixed by the data (deterministic).
+// the marked ones in FP64 (s < rc^2 exactly).  The summation order of an atom
+// is fixed by the data (deterministic).
 constexpr int RP_RING = 128;
 struct RpWave {
   float2 c[RP_RING];
@@ -1960,8 +1964,9 @@ struct RpWave {
   double4 d[RP_RING];
 };
 
+template <bool MULTI>
 __global__ void __launch_bounds__(64 * RS_WAVES, 4) k_real_space_plane(
-    int g, int n, int m, int mpad64, const int* __restrict__ amap, int nmap,
+    int g, int n, int m, int mpad64, int sub, const int* __restrict__ amap, int nmap,
     const double* __restrict__ ex, const double* __restrict__ ey, const double* __restrict__ ez,
     const double4* __restrict__ cq, const double2* __restrict__ zr, double Lx, double Ly,
     double Lz, double rc, const double* __restrict__ ptab, double* __restrict__ part) {
@@ -1970,7 +1975,8 @@ __global__ void __launch_bounds__(64 * RS_WAVES, 4) k_real_space_plane(
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int slot = blockIdx.x * blockDim.x + threadIdx.x;
   const int atom = slot < nmap ? amap[slot] : -1;
-  const int chunk = blockIdx.y, rchunks = gridDim.y;
+  const int chunk = blockIdx.y / sub, rchunks = gridDim.y / sub;
+  const bool mine = lane / (64 / sub) == (int)blockIdx.y % sub;   // this workgroup's part of a block
   const int nb64 = mpad64 / 64, nbt = (m + 63) / 64;
   for (int t = threadIdx.x; t < RP_N * RP_REC / 2; t += blockDim.x)
     reinterpret_cast<double2*>(s_tab)[t] = reinterpret_cast<const double2*>(ptab)[t];
@@ -2086,32 +2092,21 @@ __global__ void __launch_bounds__(64 * RS_WAVES, 4) k_real_space_plane(
         fA = fB;
         bB = pop();
         fB = fetch(snap, bB);
-        const bool valid = (chunk + rchunks * blk) * 64 + lane < m;
+        const bool valid = mine && (chunk + rchunks * blk) * 64 + lane < m;
         double dz = cur.z - zp;
         dz -= Lz * rint(dz * invLz);
         const double rho2 = rc2 - dz * dz;
         double dx = cur.x - cx, dy = cur.y - cy;
         dx -= Lx * rint(dx * invLx);
         dy -= Ly * rint(dy * invLy);
-        const double dx2 = dx - copysign(Lx, dx), dy2 = dy - copysign(Ly, dy);
         // images whose distance from the tile's box can be below sqrt(rho2)
         auto near = [&](double px, double py) {
           const double ux = fmax(fabs(px) - hx, 0.0), uy = fmax(fabs(py) - hy, 0.0);
           return ux * ux + uy * uy < rho2 + marg;
         };
-        int cand = 0;
-        if (valid && fabs(dz) < rc) {
-          cand = (near(dx, dy) ? 1 : 0) | (near(dx2, dy) ? 2 : 0) | (near(dx, dy2) ? 4 : 0) |
-                 (near(dx2, dy2) ? 8 : 0);
-        }
-        while (true) {
-          const bool has = cand != 0;
-          const unsigned long long bal = __ballot(has);
-          if (!bal) break;
+        // append the lanes' images (has), then screen and sum full batches
+        auto append = [&](bool has, unsigned long long bal, double px, double py) {
           if (has) {
-            const int which = __builtin_ctz(cand);
-            cand &= cand - 1;
-            const double px = (which & 1) ? dx2 : dx, py = (which & 2) ? dy2 : dy;
             const int pos = (tail + __popcll(bal & ((1ull << lane) - 1ull))) & (RP_RING - 1);
             W.c[pos] = make_float2((float)(-2.0 * px), (float)(-2.0 * py));
             W.w[pos] = (float)(px * px + py * py - rho2 - marg);
@@ -2123,30 +2118,71 @@ __global__ void __launch_bounds__(64 * RS_WAVES, 4) k_real_space_plane(
             process(head & (RP_RING - 1), 64);
             head += 64;
           }
+        };
+        if constexpr (MULTI) {
+          // every (ia, ib) with |dx + ia Lx| <= reach + hx and the like
+          int ia = 0, ib = 0, blo = 0, bhi = -1, ahi = -1;
+          if (valid && fabs(dz) < rc) {
+            const double reach = rc + 1e-3;
+            ia = (int)ceil((-(reach + hx) - dx) * invLx);
+            ahi = (int)floor(((reach + hx) - dx) * invLx);
+            blo = (int)ceil((-(reach + hy) - dy) * invLy);
+            bhi = (int)floor(((reach + hy) - dy) * invLy);
+            ib = blo;
+          }
+          bool more = ia <= ahi && blo <= bhi;
+          while (__ballot(more)) {
+            const double px = dx + ia * Lx, py = dy + ib * Ly;
+            const bool has = more && near(px, py);
+            const unsigned long long bal = __ballot(has);
+            if (more && ++ib > bhi) {
+              ib = blo;
+              more = ++ia <= ahi;
+            }
+            if (bal) append(has, bal, px, py);
+          }
+        } else {
+          const double dx2 = dx - copysign(Lx, dx), dy2 = dy - copysign(Ly, dy);
+          int cand = 0;
+          if (valid && fabs(dz) < rc) {
+            cand = (near(dx, dy) ? 1 : 0) | (near(dx2, dy) ? 2 : 0) | (near(dx, dy2) ? 4 : 0) |
+                   (near(dx2, dy2) ? 8 : 0);
+          }
+          while (true) {
+            const bool has = cand != 0;
+            const unsigned long long bal = __ballot(has);
+            if (!bal) break;
+            const int which = has ? __builtin_ctz(cand) : 0;
+            cand &= cand - 1;
+            append(has, bal, (which & 1) ? dx2 : dx, (which & 2) ? dy2 : dy);
+          }
         }
       }
     }
     if (tail > head) process(head & (RP_RING - 1), tail - head);
     head = tail = 0;
-    if (atom >= 0) part[((size_t)snap * rchunks + chunk) * n + atom] = acc;
+    if (atom >= 0) part[((size_t)snap * gridDim.y + blockIdx.y) * n + atom] = acc;
     acc = 0.0;
   }
 }
 
-void launch_b_real_space(hipStream_t st, int g, int n, int m, int mpad64, int rchunks,
+void launch_b_real_space(hipStream_t st, int g, int n, int m, int mpad64, int rchunks, int sub,
                          const Buffers& b, int nmap, const double4* cq, const double2* zr,
                          double Lx, double Ly, double Lz, double rc, double* part, int wg_target,
                          const double* plane_tab) {
+  // rchunks rows of partials (sub of them per block of charges);
   // configurations spread over the third grid dimension, about wg_target
   // workgroups in all (a workgroup loops over the configurations beyond)
   const int ablk = (nmap + 64 * RS_WAVES - 1) / (64 * RS_WAVES);
   const int gz = std::max(1, std::min(g, (wg_target + ablk * rchunks - 1) / (ablk * rchunks)));
   dim3 grid(ablk, rchunks, gz), block(64 * RS_WAVES);
   if (plane_tab)
-    hipLaunchKernelGGL(k_real_space_plane, grid, block, 0, st, g, n, m, mpad64, b.amap, nmap,
+    hipLaunchKernelGGL((Lx >= 2.0 * rc && Ly >= 2.0 * rc ? k_real_space_plane<false>
+                                                         : k_real_space_plane<true>),
+                       grid, block, 0, st, g, n, m, mpad64, sub, b.amap, nmap,
                        b.ex, b.ey, b.ez, cq, zr, Lx, Ly, Lz, rc, plane_tab, part);
   else
-    hipLaunchKernelGGL(k_real_space_b, grid, block, 0, st, g, n, m, mpad64, b.amap, nmap,
+    hipLaunchKernelGGL(k_real_space_b, grid, block, 0, st, g, n, m, mpad64, sub, b.amap, nmap,
                        b.ex, b.ey, b.ez, cq, zr, Lx, Ly, Lz, rc, b.rtab, part);
 }
 

@@ -254,20 +254,27 @@ int rs_target(const cpm_ctx* c) {
 
 // real-space charge chunks for a launch group of g configurations on the
 // grouped path: the chunks and the configurations (the grid's third
-// dimension) fill about rs_wg_target workgroups together, >= 64 charges per
-// chunk
-int rchunks_for(const cpm_ctx* c, int g) {
+// dimension) fill about rs_wg_target workgroups together, blocks of 64 charges.
+// Where even a chunk per block leaves CUs idle (small systems, single
+// configurations) a block is divided into up to 16 parts (rs_sub): at 288
+// atoms and 100 charges one workgroup walked all of them in 150 us.
+int rblocks_for(const cpm_ctx* c, int g) {
   const int atom_blocks = (c->nmap + real_space_block_atoms() - 1) / real_space_block_atoms();
   const int t = rs_target(c);
-  return std::max(1, std::min(std::max(1, c->m / 64), (t + atom_blocks * g - 1) / (atom_blocks * g)));
+  return std::max(1, std::min((c->m + 63) / 64, (t + atom_blocks * g - 1) / (atom_blocks * g)));
 }
+int rs_sub(const cpm_ctx* c, int g) {
+  const int atom_blocks = (c->nmap + real_space_block_atoms() - 1) / real_space_block_atoms();
+  int sub = 1;
+  while (sub < 16 && atom_blocks * g * rblocks_for(c, g) * sub < 256) sub *= 2;
+  return sub;
+}
+int rchunks_for(const cpm_ctx* c, int g) { return rblocks_for(c, g) * rs_sub(c, g); }
 
 // the planar real-space kernel: atoms on z planes (whole waves per plane in
-// the atom map) and at most one periodic image within rc
+// the atom map) and at most one periodic image in z within rc
 bool rs_plane(const cpm_ctx* c) {
-  const double two_rc = 2.0 * c->p.rcut;
-  return c->rs_plane_ok && c->nlayers > 0 && c->p.Lx >= two_rc && c->p.Ly >= two_rc &&
-         c->Lz >= two_rc;
+  return c->rs_plane_ok && c->nlayers > 0 && c->Lz >= 2.0 * c->p.rcut;
 }
 
 cpm_status ensure_vat(cpm_ctx* c) {
@@ -1794,7 +1801,7 @@ cpm_status pv_enqueue(cpm_ctx* c, int batch, const double* d_xyz, void* d_b, int
     }
     { Timed t(c, "real_space_b", rst);
       launch_gather_charges(rst, g, m, mpad64, perm, xyz, b.elq, p.Lx, p.Ly, b.cq, b.zr);
-      launch_b_real_space(rst, g, n, m, mpad64, rch, b, c->nmap, b.cq, b.zr, p.Lx, p.Ly, c->Lz,
+      launch_b_real_space(rst, g, n, m, mpad64, rch, fast ? rs_sub(c, g) : 1, b, c->nmap, b.cq, b.zr, p.Lx, p.Ly, c->Lz,
                           p.rcut, b.phir_part, fast ? rs_target(c) : 512,
                           rs_plane(c) ? b.ptab : nullptr); }
     if (conc) HIP_TRY(c, hipEventRecord(c->rs_ev_out, rst));

@@ -534,7 +534,7 @@ void launch_group_indicator(hipStream_t st, int n, int npad, int rows, const int
 void launch_factor_response(hipStream_t st, int n, int npad, int n_e, const double* Y, int ldy,
                             double* u, double* s, double* sg);
 void launch_pair_table(hipStream_t st, double alpha, double eta, double rc, double* tab);
-void launch_b_real_space(hipStream_t st, int g, int n, int m, int mpad64, int rchunks,
+void launch_b_real_space(hipStream_t st, int g, int n, int m, int mpad64, int rchunks, int sub,
                          const Buffers& b, int nmap, const double4* cq, const double2* zr,
                          double Lx, double Ly, double Lz, double rc, double* part, int wg_target,
                          const double* plane_tab);
