@@ -277,6 +277,96 @@ bool rs_plane(const cpm_ctx* c) {
   return c->rs_plane_ok && c->nlayers > 0 && c->Lz >= 2.0 * c->p.rcut;
 }
 
+// Planar k space from z-sorted charges (zbasis.hip) for b in FP64 or FP32:
+// planes and matrix cores as for the grouped path, bins and tables within
+// their bounds.  The explicit structure factors remain for the rest, and for
+// b in FP32 when CPM_SF_F16=0 asks for the FP32 structure-factor kernel.
+int zb_type(const cpm_ctx* c, int b_is_f32) { return b_is_f32 && c->sf32_ok ? 1 : 0; }
+bool zb_usable(const cpm_ctx* c, int b_is_f32) {
+  const int ty = zb_type(c, b_is_f32);
+  const ZbTable& t = c->zt[ty];
+  return c->zb_ok && c->sf_mfma && c->use_sf_mfma && c->nlayers > 0 && !(ty && !c->sf16_ok) &&
+         t.nbins > 0 && t.nbins <= ZB_MAXSORT &&
+         (double)t.nbins * c->zb.ncu * c->nlayers * zb_terms(ty) * sizeof(double) <= ZB_MAXTABLE;
+}
+
+// items and parts of the binned sums for g configurations.  A workgroup fills
+// a CU, so the parts are chosen for whole rounds of 256: rounds x (charges of a
+// part + its fixed cost, about ZB_FIXED charges' time) plus the parts to add.
+// Few configurations take the narrow items (half the work per workgroup).
+const ZbItems& zb_items(const cpm_ctx* c, int g) {
+  return (double)c->zb.wide.nwg * g * ((c->m + 127) / 128) < 512.0 ? c->zb.narrow : c->zb.wide;
+}
+int zb_parts(const cpm_ctx* c, int g) {
+  const double wgs = (double)zb_items(c, g).nwg * g;
+  int best = 1;
+  double cost = 1e300;
+  for (int p = 1; p <= std::min(256, (c->m + 31) / 32); ++p) {
+    const double t = std::ceil(p * wgs / 256.0) * ((double)c->m / p + ZB_FIXED) + p;
+    if (t < cost) {
+      cost = t;
+      best = p;
+    }
+    if (p * wgs > 4096.0) break;
+  }
+  return best;
+}
+
+// workgroup items: for every 16 n_y the n_x that have them, in ranges of 16
+// (two per wave) or 8 (one per wave; only these when narrow).  The n_x that
+// reach only the first 8 n_y go into items of their own where that costs fewer
+// products (an item also costs about 4 products' time to form its tiles).
+void zb_make_items(const ZbPlan& z, bool narrow, ZbItems& out) {
+  const int n_all = (int)z.cu_of.size();
+  auto split = [&](int a, int e, int ny0, int nc, std::vector<ZbItem>& h) {
+    int cost = 0;
+    while (a < e) {
+      const int nu = !narrow && e - a > 8 ? 2 : 1, len = std::min(8 * nu, e - a);
+      h.push_back(ZbItem{a, len, ny0, nu + 2 * (nc - 1)});
+      cost += 8 * nu * nc + 4;
+      a += len;
+    }
+    return cost;
+  };
+  for (int ny0 = 0;; ny0 += 16) {
+    int n1 = 0, n2 = 0;                    // n_x with more than ny0, ny0 + 8 values of n_y
+    while (n1 < n_all && z.cu_of[n1].y > ny0) ++n1;
+    while (n2 < n1 && z.cu_of[n2].y > ny0 + 8) ++n2;
+    if (n1 == 0) break;
+    std::vector<ZbItem> one, two;
+    const int c1 = split(0, n1, ny0, n2 ? 2 : 1, one);
+    const int c2 = split(0, n2, ny0, 2, two) + split(n2, n1, ny0, 1, two);
+    const std::vector<ZbItem>& best = c2 < c1 ? two : one;
+    out.h.insert(out.h.end(), best.begin(), best.end());
+  }
+  out.nwg = (int)out.h.size();
+  // largest first: products per wave NU NC, shape = NU + 2 (NC - 1)
+  auto products = [](const ZbItem& i) { return ((i.shape - 1) % 2 + 1) * ((i.shape + 1) / 2); };
+  std::stable_sort(out.h.begin(), out.h.end(),
+                   [&](const ZbItem& a, const ZbItem& b) { return products(a) > products(b); });
+}
+
+// Form the response table of precision ty if the planes have moved since (its
+// memory is allocated with the step buffers, so a call in the other precision
+// leaves a captured step's buffers alone).
+cpm_status ensure_zb_table(cpm_ctx* c, int ty) {
+  ZbTable& t = c->zt[ty];
+  if (t.ready || !t.H || !c->b.layer_fz) return CPM_OK;
+  const ZbPlan& z = c->zb;
+  launch_zb_response(c->stream, z.ncu, z.nzt, t.nbins, c->nlayers, zb_terms(ty), z.d_w,
+                     c->b.layer_fz, t.H);
+  TRY(launched(c, "z-bin response"));
+  t.ready = t.used = true;
+  return CPM_OK;
+}
+
+// before a captured step is replayed: the tables in use for the current planes
+cpm_status refresh_zb_tables(cpm_ctx* c) {
+  for (int ty = 0; ty < 2; ++ty)
+    if (c->zt[ty].used) TRY(ensure_zb_table(c, ty));
+  return CPM_OK;
+}
+
 cpm_status ensure_vat(cpm_ctx* c) {
   return dalloc(c, &c->b.vat, (size_t)c->npad);
 }
@@ -560,7 +650,17 @@ cpm_status ensure_step_buffers(cpm_ctx* c) {
   c->rchunks = std::max(1, std::min(512 / atom_blocks, std::max(1, c->m / 32)));
   TRY(dalloc_cap(c, &b.sf_part, (size_t)2 * c->nk * c->mchunks));
   const bool fast = c->sf_mfma && c->nlayers > 0;
-  if (c->sf_mfma) {
+  // explicit structure factors: unless both kinds of b take the binned sums
+  const bool explicit_sf = !(zb_usable(c, 0) && zb_usable(c, 1));
+  const size_t mpad64 = (size_t)std::max(64, (c->m + 63) / 64 * 64);
+  if (fast && !explicit_sf) {
+    // configurations per launch group, within ~1 GB: sorted charges,
+    // real-space partials, parts of T
+    const double per = 40.0 * mpad64 + 16.0 * c->n + 16.0 * 32.0 * c->zb.nunits * c->nlayers;
+    c->pv_group = std::max(1, std::min(std::min(CG_MAXG, c->pv_group_cap),
+                                       (int)(1024.0 * 1024 * 1024 / per)));
+  }
+  if (c->sf_mfma && explicit_sf) {
     c->mpad = std::max(64, (c->m + 63) / 64 * 64);
     // table rows per configuration in double2 units: the FP64 / FP32 layout
     // or the split-FP16 one (float2 rows and the z operand), the larger
@@ -596,7 +696,20 @@ cpm_status ensure_step_buffers(cpm_ctx* c) {
   c->dip_blocks = std::max(1, (c->m + 255) / 256);
   TRY(dalloc_cap(c, &b.dip, (size_t)c->pv_group * c->dip_blocks * 3));
   TRY(dalloc_cap(c, &b.rtab, (size_t)3 * (RS_NT + 1)));
-  const size_t mpad64 = (size_t)std::max(64, (c->m + 63) / 64 * 64);
+  if (zb_usable(c, 0) || zb_usable(c, 1)) {
+    size_t parts = 0;
+    for (int g = 1; g <= c->pv_group; ++g) parts = std::max(parts, (size_t)g * zb_parts(c, g));
+    TRY(dalloc_cap(c, &b.zpart, parts * c->zb.nunits * c->nlayers * 32));
+    TRY(dalloc_cap(c, &b.zcounts, (size_t)c->pv_group * zb_sort_blocks(c->m) * ZB_MAXSORT));
+    TRY(dalloc_cap(c, &b.zbinoff, (size_t)c->pv_group * (ZB_MAXSORT + 1)));
+    TRY(dalloc_cap(c, &b.dtot, (size_t)c->pv_group * 3));
+    for (int f = 0; f < 2; ++f)
+      if (zb_usable(c, f)) {
+        ZbTable& t = c->zt[zb_type(c, f)];
+        if (!t.H) t.ready = false;
+        TRY(dalloc(c, &t.H, (size_t)t.nbins * c->zb.ncu * c->nlayers * zb_terms(zb_type(c, f))));
+      }
+  }
   TRY(dalloc_cap(c, &b.zperm, mpad64));
   TRY(dalloc_cap(c, &b.cq, (size_t)c->pv_group * mpad64));
   TRY(dalloc_cap(c, &b.zr, (size_t)c->pv_group * (mpad64 / 64)));
@@ -709,6 +822,16 @@ cpm_status ensure_uploaded(cpm_ctx* c) {
       HIP_TRY(c, hipMemcpy(b.sf16_items, c->h_sf16_items.data(),
                            c->h_sf16_items.size() * sizeof(int4), hipMemcpyHostToDevice));
     }
+    if (c->sf_mfma) {
+      ZbPlan& z = c->zb;
+      auto up2 = [&](auto** dst, const auto& v) -> cpm_status {
+        TRY(dalloc(c, dst, v.size()));
+        HIP_TRY(c, hipMemcpy(*dst, v.data(), v.size() * sizeof(v[0]), hipMemcpyHostToDevice));
+        return CPM_OK;
+      };
+      TRY(up2(&z.d_units, z.units)); TRY(up2(&z.d_cu_of, z.cu_of)); TRY(up2(&z.d_cols, z.cols));
+      TRY(up2(&z.d_w, z.w)); TRY(up2(&z.wide.d_items, z.wide.h)); TRY(up2(&z.narrow.d_items, z.narrow.h));
+    }
     TRY(dalloc(c, &b.chunk_col, c->h_chunk_col.size()));
     TRY(dalloc(c, &b.flag, 4));
     TRY(dalloc(c, &b.scal, 8));
@@ -796,6 +919,7 @@ cpm_status cpm_create(const cpm_params* params, void* hip_stream, cpm_ctx** out)
     const int v = std::atoi(ev);
     c->sf16_nt = v >= 4 ? 4 : v >= 2 ? 2 : 1;
   }
+  if (const char* ev = std::getenv("CPM_SF_ZBIN")) c->zb_ok = std::atoi(ev) != 0;
   if (const char* ev = std::getenv("CPM_RS_PLANE")) c->rs_plane_ok = std::atoi(ev) != 0;
   c->kc = (p.kcut > 0.0) ? p.kcut : 2.0 * p.alpha * std::sqrt(std::log(1.0 / p.kspace_eps));
   c->ke = (p.coulomb_k > 0.0) ? p.coulomb_k : KE_DEFAULT;
@@ -902,6 +1026,47 @@ cpm_status cpm_create(const cpm_params* params, void* hip_stream, cpm_ctx** out)
     for (int k = 0; k < c->ncolsort; ++k)
       c->sfm_maxcnt = std::max(c->sfm_maxcnt, c->h_sc_nidx[k + 1] - c->h_sc_nidx[k]);
     (void)emax;
+  }
+  {
+    // binned planar sums: column pairs, units of 8 n_y, weights of cos(n kz1 z)
+    ZbPlan& z = c->zb;
+    z.nzt = c->nzm + 1;
+    std::vector<int> nyc(c->nxm + 1, 0);
+    for (int k = 0; k < c->ncolsort; ++k)
+      nyc[c->h_sc_nx[k]] = std::max(nyc[c->h_sc_nx[k]], std::abs(c->h_sc_ny[k]) + 1);
+    for (int nx = 0; nx <= c->nxm; ++nx) {
+      z.cu_of.push_back(make_int4(z.ncu, nyc[nx], (int)z.units.size(), 0));
+      z.ncu += nyc[nx];
+      for (int cb = 0; cb < (nyc[nx] + 7) / 8; ++cb) z.units.push_back(make_int2(nx, cb));
+    }
+    z.nunits = (int)z.units.size();
+    z.cols.assign(z.ncu, make_int2(-1, -1));
+    z.w.assign((size_t)z.ncu * z.nzt, 0.0);
+    for (int k = 0; k < c->ncolsort; ++k) {
+      const int nx = c->h_sc_nx[k], ny = c->h_sc_ny[k], cu = z.cu_of[nx].x + std::abs(ny);
+      if (ny < 0) {
+        z.cols[cu].y = k;
+        continue;
+      }
+      z.cols[cu].x = k;
+      // n and -n together; the column (0, 0) holds only n > 0
+      const int lo = c->h_sc_lo[k], hi = lo + c->h_sc_len[k] - 1;
+      for (int n = std::max(0, lo); n <= hi; ++n)
+        z.w[(size_t)n * z.ncu + cu] = (n > 0 && lo < 0 ? 2.0 : 1.0) * c->h_w2[c->h_sc_koff[k] + n - lo];
+    }
+    zb_make_items(z, false, z.wide);
+    zb_make_items(z, true, z.narrow);
+    // bins: the Chebyshev remainder below the rounding of the sums
+    for (int ty = 0; ty < 2; ++ty) {
+      ZbTable& t = c->zt[ty];
+      const double hw = zb_half_width(p.alpha, c->kc, zb_terms(ty), ty ? 1e-8 : 5e-17);
+      const double nb = std::ceil(c->Lz / (2.0 * hw));
+      t.nbins = nb <= ZB_MAXSORT ? std::max(1, (int)nb) : ZB_MAXSORT + 1;
+      // sort bins of about half an angstrom: the blocks of 64 sorted charges
+      // that a plane's real-space window can skip
+      t.sub = std::max(1, std::min(ZB_MAXSORT / t.nbins, (int)std::lround(2.0 * c->Lz / t.nbins)));
+      t.nsort = t.nbins * t.sub;
+    }
   }
   *out = c;
   return CPM_OK;
@@ -1194,6 +1359,7 @@ cpm_status build_impl(cpm_ctx* c, int n, const double* d_xyz, const int* d_eid, 
   // k-set (chunks, launch groups): sized again on first use, keeping
   // allocations that are large enough
   c->step_ready = false;
+  c->zt[0].ready = c->zt[1].ready = false;   // the planes may have moved
   // the CG work arrays and the preconditioner follow the atom map and the
   // operator (slots, chunks, work parts): a rebuild allocates them afresh
   dfree(c, b0.cg_ident); dfree(c, b0.cgv); dfree(c, b0.cgred); dfree(c, b0.cgscal);
@@ -1745,6 +1911,7 @@ cpm_status pv_prepare(cpm_ctx* c, int batch, const double* d_xyz, void* d_b, int
   if (b_is_f32 != 0 && b_is_f32 != 1) return fail(c, CPM_EINVAL, "b_is_f32 must be 0 or 1");
   TRY(ensure_uploaded(c));
   TRY(ensure_step_buffers(c));
+  if (zb_usable(c, b_is_f32)) TRY(ensure_zb_table(c, zb_type(c, b_is_f32)));
   if (c->rs_conc_ok) TRY(ensure_rs_stream(c));
   return CPM_OK;
 }
@@ -1764,6 +1931,8 @@ cpm_status pv_enqueue(cpm_ctx* c, int batch, const double* d_xyz, void* d_b, int
   // b stored in FP32 (the reduced-precision solve path): structure factors on
   // FP32 matrix cores, FP32 phase tables (switch: CPM_SF_FP32=0)
   const int sf32 = (b_is_f32 && c->sf32_ok) ? (c->sf16_ok ? 2 : 1) : 0;
+  const bool zb = fast && zb_usable(c, b_is_f32);
+  const int zty = zb_type(c, b_is_f32);
   const int G = fast ? c->pv_group : 1;
   const int mpad64 = std::max(64, (m + 63) / 64 * 64);
   // the charges ordered by z (from the first configuration of a large
@@ -1772,7 +1941,7 @@ cpm_status pv_enqueue(cpm_ctx* c, int batch, const double* d_xyz, void* d_b, int
   // reuse the last order: the block z ranges come from the actual positions,
   // so an order that has aged only costs skipped blocks, never a pair
   const int* perm = nullptr;
-  if (m > 0 && (batch >= c->rs_sort_min || !c->zperm_ok)) {
+  if (m > 0 && !zb && (batch >= c->rs_sort_min || !c->zperm_ok)) {
     Timed t(c, "zsort");
     launch_zsort(st, m, d_xyz, c->Lz, zsort_bins(c->Lz), b.zperm);
     c->zperm_ok = true;
@@ -1786,7 +1955,7 @@ cpm_status pv_enqueue(cpm_ctx* c, int batch, const double* d_xyz, void* d_b, int
       launch_fill_zero(st, (size_t)g * n * esz / sizeof(float), static_cast<float*>(out));
       continue;
     }
-    const int nch = mfma ? sf_chunks_for(c, g, sf32 == 2) : 0;
+    const int nch = mfma && !zb ? sf_chunks_for(c, g, sf32 == 2) : 0;
     const int rch = fast ? rchunks_for(c, g) : c->rchunks;
     // grouped path: the real-space pass runs on its own stream beside the
     // structure factors (VALU/LDS-bound beside MFMA-bound work); it starts
@@ -1794,13 +1963,19 @@ cpm_status pv_enqueue(cpm_ctx* c, int batch, const double* d_xyz, void* d_b, int
     // which read its partials) and the final sum of this group waits for it
     const bool conc = fast && c->rs_stream && !c->capturing;
     hipStream_t rst = st;
+    if (zb) {
+      // every configuration's charges sorted by z, and the dipole partials
+      Timed t(c, "sf_tables");
+      launch_zb_sort(st, g, m, mpad64, c->zt[zty], p.Lx, p.Ly, c->Lz, xyz, b.elq, b.zcounts, b.cq,
+                     b.zr, b.zbinoff, b.dip);
+    }
     if (conc) {
       HIP_TRY(c, hipEventRecord(c->rs_ev_in, st));
       HIP_TRY(c, hipStreamWaitEvent(c->rs_stream, c->rs_ev_in, 0));
       rst = c->rs_stream;
     }
     { Timed t(c, "real_space_b", rst);
-      launch_gather_charges(rst, g, m, mpad64, perm, xyz, b.elq, p.Lx, p.Ly, b.cq, b.zr);
+      if (!zb) launch_gather_charges(rst, g, m, mpad64, perm, xyz, b.elq, p.Lx, p.Ly, b.cq, b.zr);
       launch_b_real_space(rst, g, n, m, mpad64, rch, fast ? rs_sub(c, g) : 1, b, c->nmap, b.cq, b.zr, p.Lx, p.Ly, c->Lz,
                           p.rcut, b.phir_part, fast ? rs_target(c) : 512,
                           rs_plane(c) ? b.ptab : nullptr); }
@@ -1809,7 +1984,15 @@ cpm_status pv_enqueue(cpm_ctx* c, int batch, const double* d_xyz, void* d_b, int
       Timed t(c, "dipole");
       launch_b_elyt_dipole(st, g, m, xyz, b.elq, b.dip);
     }
-    if (mfma) {
+    if (zb) {
+      const int np = zb_parts(c, g);
+      { Timed t(c, "structure_factor");
+        launch_zb_sums(st, g, zty != 0, c->zb, c->zt[zty], zb_items(c, g), m, mpad64, np,
+                       c->nlayers, b.cq, b.zbinoff, p.Lx, p.Ly, c->Lz, b.zpart); }
+      { Timed t(c, "sf_reduce");
+        launch_zb_reduce(st, g, c->zb, c->nlayers, np, b.zpart, 2 * c->ncp, b.bT,
+                         zb_sort_blocks(m), b.dip, b.dtot); }
+    } else if (mfma) {
       // the table kernel also writes the dipole partials
       { Timed t(c, "sf_tables");
         launch_b_sf_tables(st, g, m, c->mpad, c->nxm, c->nym, c->sfm_nbz, xyz, b.elq, p.Lx, p.Ly,
@@ -1827,11 +2010,13 @@ cpm_status pv_enqueue(cpm_ctx* c, int batch, const double* d_xyz, void* d_b, int
         launch_b_sf_reduce(st, c->nk, c->mchunks, b.sf_part, b.w2, b.sfw); }
     }
     if (fast) {
-      { Timed t(c, "sf_reduce");
+      if (!zb) {
+        Timed t(c, "sf_reduce");
         launch_b_sf_layer_reduce(st, g, c->ncolsort, nch, c->sfm_pchunk, c->nlayers,
                                  c->sfm_npadc / 2, c->sfm_maxcnt, b.tile_nb, b.tile_off, b.sc_lo,
                                  b.sc_len, b.sc_koff, b.sc_nidx, b.sfm_part, b.w2, b.pz,
-                                 2 * c->ncp, b.bT); }
+                                 2 * c->ncp, b.bT);
+      }
       { Timed t(c, "projection");
         // one configuration: vector units (a matrix-core tile would fill 64 lanes for one)
         if (g == 1)
@@ -1842,7 +2027,8 @@ cpm_status pv_enqueue(cpm_ctx* c, int batch, const double* d_xyz, void* d_b, int
       if (conc) HIP_TRY(c, hipStreamWaitEvent(st, c->rs_ev_out, 0));
       { Timed t(c, "combine");
         launch_b_final(st, g, n, c->nmap, c->b_nparts, b.slot_of, b.bPhi, b.phir_part,
-                       rch, b, b.dip, c->dip_blocks, c->cdip, c->ke, out, b_is_f32); }
+                       rch, b, zb ? b.dtot : b.dip, zb ? 1 : c->dip_blocks, c->cdip, c->ke, out,
+                       b_is_f32); }
       TRY(launched(c, "potential_vector"));
       continue;
     }
@@ -2178,6 +2364,7 @@ cpm_status cpm_replay_step(cpm_ctx* c) {
   if (c->alloc_gen != c->graph_gen || !c->have_inv || !c->have_v ||
       (c->store & c->graph_store) != c->graph_store || (c->graph_ccm && !c->have_q))
     return fail(c, CPM_ESTATE, "context buffers changed since cpm_capture_step; capture again");
+  TRY(refresh_zb_tables(c));
   HIP_TRY(c, hipGraphLaunch(c->graph_exec, c->stream));
   return CPM_OK;
 }
@@ -2434,6 +2621,7 @@ cpm_status cpm_replay_grouped(cpm_ctx* const* ctxs, int n_ctx) {
     if (c->alloc_gen != c0->ggroup[i].second || !c->have_inv || c->factor_only || !c->have_v ||
         !(c->store & CPM_STORE_BF16X2))
       return fail(c0, CPM_ESTATE, "context %d changed since cpm_capture_grouped; capture again", i);
+    TRY(refresh_zb_tables(c));
   }
   HIP_TRY(c0, hipGraphLaunch(c0->ggraph_exec, c0->stream));
   return CPM_OK;
@@ -2936,7 +3124,8 @@ cpm_status cpm_get_info(const cpm_ctx* c, int key, double* out) {
     case CPM_INFO_PC_MODE: *out = c->pc_mode; return CPM_OK;
     case CPM_INFO_PC_COARSE: *out = (double)c->pc_tiles * c->pc_kuse; return CPM_OK;
     case CPM_INFO_SF_FP32:
-      *out = (c->sf_mfma && c->use_sf_mfma && c->sf32_ok) ? (c->sf16_ok ? 2.0 : 1.0) : 0.0;
+      *out = (c->sf_mfma && c->use_sf_mfma && c->sf32_ok)
+                 ? (c->sf16_ok && !zb_usable(c, 1) ? 2.0 : 1.0) : 0.0;
       return CPM_OK;
     case CPM_INFO_RS_PLANE: *out = rs_plane(c) ? 1.0 : 0.0; return CPM_OK;
     default: return CPM_EINVAL;
@@ -2981,6 +3170,9 @@ void cpm_destroy(cpm_ctx* c) {
   dfree(b.res); dfree(b.bpad); dfree(b.qpad); dfree(b.scal); dfree(b.means); dfree(b.rtab); dfree(b.ptab);
   dfree(b.xhi); dfree(b.xlo);
   dfree(b.zperm); dfree(b.cq); dfree(b.zr);
+  dfree(b.zcounts); dfree(b.zbinoff); dfree(b.zpart); dfree(b.dtot);
+  dfree(c->zb.d_units); dfree(c->zb.d_cu_of); dfree(c->zb.d_cols); dfree(c->zb.d_w);
+  dfree(c->zb.wide.d_items); dfree(c->zb.narrow.d_items); dfree(c->zt[0].H); dfree(c->zt[1].H);
   dfree(b.kpart); dfree(b.ccmU); dfree(b.ccmC); dfree(b.sg); dfree(b.zeta); dfree(b.szeta);
   dfree(b.Qpair); dfree(b.ell_col); dfree(b.ell_val); dfree(b.plane_off); dfree(b.dextra);
   dfree(b.bsr_col); dfree(b.bsr_val); dfree(b.cg_items); dfree(b.asmG); dfree(b.asmF);

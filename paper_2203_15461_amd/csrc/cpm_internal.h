@@ -53,6 +53,38 @@ constexpr int CG_MAXG = 64;        // vectors per conjugate-gradient group (slot
 constexpr int CG_RED = 13;         // block partial fields
 constexpr int CG_NSCAL = 4;        // per-vector scalar rows reported to the host
 
+constexpr int ZB_NX = 16;          // most n_x values of a workgroup item (zbasis.hip)
+inline int zb_terms(int f32) { return f32 ? 8 : 16; }      // Chebyshev terms per z bin
+constexpr int ZB_MAXSORT = 512;    // most sort bins (and z bins) of a configuration
+constexpr double ZB_FIXED = 200.0;  // fixed cost of a workgroup's part, in charges
+constexpr double ZB_MAXTABLE = 2.0 * 1024 * 1024 * 1024;   // largest response table (bytes)
+
+// a workgroup item of the binned k-space sums: n_x = nxa .. nxa + nxn - 1 (NU
+// per wave) and the 8 NC values of n_y from ny0 on; shape = NU + 2 (NC - 1)
+struct ZbItem { int nxa, nxn, ny0, shape; };
+struct ZbItems {
+  int nwg = 0;                     // items
+  std::vector<ZbItem> h;
+  ZbItem* d_items = nullptr;
+};
+// the fixed part: column pairs c = (n_x, n_y >= 0), units of 8 n_y
+struct ZbPlan {
+  int ncu = 0, nunits = 0, nzt = 0;
+  std::vector<int2> units, cols;         // {n_x, n_y / 8}; {column of +n_y, -n_y}
+  std::vector<int4> cu_of;               // per n_x: {first c, n_y count, first unit, 0}
+  std::vector<double> w;                 // w(c, n), nzt x ncu
+  ZbItems wide, narrow;                  // many / few configurations
+  int2* d_units = nullptr; int4* d_cu_of = nullptr; int2* d_cols = nullptr;
+  double* d_w = nullptr;
+};
+// z bins and response of one precision
+struct ZbTable {
+  int nbins = 0, nsort = 0, sub = 1;
+  double* H = nullptr;             // nbins x ncu x nlayers x terms
+  bool ready = false;              // formed for the current planes
+  bool used = false;               // formed at least once
+};
+
 struct Buffers {
   // electrode geometry (internal order = caller order), SoA, x and y wrapped
   double* ex = nullptr;  double* ey = nullptr;  double* ez = nullptr;
@@ -108,6 +140,10 @@ struct Buffers {
   double* ptab = nullptr;          // planar pair polynomials (RP_N x RP_REC), set once
   double* fwork = nullptr;         // factor-only inverse: two 64 x npad right-hand-side blocks
   int* zperm = nullptr;            // order of the charges for the real-space pass (m)
+  int* zcounts = nullptr;          // sort-bin counts of every charge block (zbasis.hip)
+  int* zbinoff = nullptr;          // first sorted charge of each z bin, per configuration
+  double* zpart = nullptr;         // parts of T(c, L) (zbasis.hip)
+  double* dtot = nullptr;          // electrolyte dipole per configuration
   double4* cq = nullptr;           // gathered charges (x, y wrapped, z, q), pv_group x mpad64
   double2* zr = nullptr;           // z range of each 64-charge block, pv_group x mpad64 / 64
   double* qt = nullptr;            // q-tilde (batch x npad)
@@ -327,6 +363,9 @@ struct cpm_ctx {
   int sf16_nt = 2;                 // ... M tiles per work item (1, 2 or 4)
   bool rs_plane_ok = true;         // planar real-space kernel (pair polynomials in r^2)
   bool factor_only = false;        // cpm_invert kept the Cholesky factor, not S
+  bool zb_ok = true;               // planar k space from z-sorted charges (CPM_SF_ZBIN=0: structure factors)
+  cpm::ZbPlan zb;
+  cpm::ZbTable zt[2];              // z bins for FP64 and FP32 sums
   int ncolsort = 0, sfm_tiles = 0, sfm_npadc = 0, sfm_ntot = 0;
   int sfm_nbz = 2, sfm_nitems = 0, sf16_nitems = 0, mpad = 0, sft_rows = 0, sft_blocks = 1;
   int sfm_pchunk = 0;              // doubles per (configuration, chunk) of sfm_part
@@ -506,6 +545,21 @@ void launch_b_sf_layer_reduce(hipStream_t st, int g, int ncolsort, int nchunks, 
                               const double* w2, const double2* pz, int M2, double* Tcat);
 void launch_plane_phases(hipStream_t st, int nlayers, int nzt, const double* layer_fz,
                          double2* pz);
+// planar k space from z-sorted charges (zbasis.hip)
+double zb_half_width(double alpha, double kc, int P, double tol);
+int zb_sort_blocks(int m);
+void launch_zb_sort(hipStream_t st, int g, int m, int mpad64, const ZbTable& t, double Lx,
+                    double Ly, double Lz, const double* xyz, const double* q, int* counts,
+                    double4* cq, double2* zr, int* binoff, double* dip);
+void launch_zb_response(hipStream_t st, int ncu, int nzt, int nbins, int nlayers, int P,
+                        const double* w, const double* layer_fz, double* H);
+void launch_zb_sums(hipStream_t st, int g, bool f32, const ZbPlan& z, const ZbTable& t,
+                    const ZbItems& I, int m, int mpad64, int nparts, int nlayers,
+                    const double4* cq, const int* binoff, double Lx, double Ly, double Lz,
+                    double* part);
+void launch_zb_reduce(hipStream_t st, int g, const ZbPlan& z, int nlayers, int nparts,
+                      const double* part, int M2, double* Tcat, int dblk, const double* dip,
+                      double* dtot);
 // planar electrodes: b from the projection parts (k_cg_tiles over the slot
 // tiles), the real-space partials and the dipole term
 void launch_b_final(hipStream_t st, int g, int n, int nslot, int nparts, const int* slot_of,
