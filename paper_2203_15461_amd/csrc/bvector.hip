@@ -1463,7 +1463,6 @@ int layer_project_chunks(int ncols) { return (ncols + LP_COLS - 1) / LP_COLS; }
 // Real-space pair sum: one thread per electrode atom, electrolyte tiles in LDS.
 // part[chunk * n + i] = sum_j q_j sum_t [erfc(alpha r) - erfc(eta r)] / r.
 // ---------------------------------------------------------------------------
-constexpr int RS_TILE = 256;
 
 // Electrode-point pair function g(r) = (erfc(alpha r) - erfc(eta r)) / r
 // (the Gaussian-smeared electrode charge seen from a point charge, minus

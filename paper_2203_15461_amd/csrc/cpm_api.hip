@@ -768,17 +768,26 @@ cpm_status ensure_kpart(cpm_ctx* c, size_t len) {
   return CPM_OK;
 }
 
+// work for the partial tiles of split FP64 products: without it (no memory) they
+// run unsplit
+void ensure_gemm_work(cpm_ctx* c, GemmWork& w, size_t len) {
+  if (len <= w.len) return;
+  dfree(c, w.p);
+  w.len = dalloc(c, &w.p, len) == CPM_OK ? len : 0;
+}
+
 // work buffers of one solve: the context's own (grown on demand), or carved
 // out of the fixed scratch array of cpm_solve_charges_noalloc
 struct SolveWork {
   double* qt; double* res; double* bpad; double* qpad; double* means; double* kpart;
   uint16_t* xhi; uint16_t* xlo;
   const cpm_ctx::GemmCfg* bf16 = nullptr;      // forced split-BF16 configuration
+  GemmWork gw = {};
 };
 
 SolveWork ctx_work(cpm_ctx* c) {
   Buffers& b = c->b;
-  return SolveWork{b.qt, b.res, b.bpad, b.qpad, b.means, b.kpart, b.xhi, b.xlo, nullptr};
+  return SolveWork{b.qt, b.res, b.bpad, b.qpad, b.means, b.kpart, b.xhi, b.xlo, nullptr, b.gws};
 }
 
 // one split-BF16 product C (+)= X S~ over `rows` rows of this context; X is
@@ -2089,6 +2098,8 @@ cpm_status sc_prepare(cpm_ctx* c, int batch, const void* d_b, int b_is_f32, unsi
   const bool gemm = (batch >= GEMM_MIN_BATCH && prec == 0) || prec == 2 || c->factor_only;
   const int rows = gemm ? ((batch + TILE - 1) / TILE) * TILE : batch;
   TRY(ensure_solve_buffers(c, rows));
+  if (gemm && !c->factor_only && prec == 0)
+    ensure_gemm_work(c, c->b.gws, gemm_f64_work(rows, c->npad, c->npad));
   if (prec == 2) {
     const cpm_ctx::GemmCfg cfg = bf16_cfg(c, rows);
     if (cfg.ks > 1) TRY(ensure_kpart(c, (size_t)cfg.ks * rows * c->npad));
@@ -2139,7 +2150,7 @@ cpm_status sc_enqueue(cpm_ctx* c, int batch, const void* d_b, int b_is_f32, unsi
         launch_pad_rows(st, n, npad, batch, rows, d_b, b_is_f32, nullptr, w.bpad); }
       Timed t(c, "gemm_f64");
       launch_gemm_f64(st, false, false, rows, npad, npad, 1.0, w.bpad, npad, b.Ainv, npad, 0.0, w.qt,
-                      npad, 0, 0);
+                      npad, 0, 0, nullptr, w.gw);
     }
     { Timed t(c, "finalize");
       launch_ccm_finalize(st, n, batch, w.qt, npad, b.ccmU, b.ccmC, b.ccmC + c->n_e * c->n_e, b.eid,
@@ -2152,7 +2163,7 @@ cpm_status sc_enqueue(cpm_ctx* c, int batch, const void* d_b, int b_is_f32, unsi
     if (prec == 0) {
       Timed t(c, "gemm_f64");
       launch_gemm_f64(st, false, false, rows, npad, npad, 1.0, x, npad, b.S, npad,
-                      accumulate ? 1.0 : 0.0, y, npad, 0, 0);
+                      accumulate ? 1.0 : 0.0, y, npad, 0, 0, nullptr, w.gw);
     } else {
       Timed t(c, "gemm_bf16x3");
       enqueue_bf16(c, x, y, rows, accumulate, w.bf16 ? *w.bf16 : bf16_cfg(c, rows), w);
@@ -2208,7 +2219,8 @@ cpm_status sc_enqueue(cpm_ctx* c, int batch, const void* d_b, int b_is_f32, unsi
                     nullptr); }
   { Timed t(c, "make_rhs");
     launch_make_rhs(st, n, npad, batch, d_b, b_is_f32, b.vat, w.res); }
-  // R = C - Qp A (FP64 MFMA), centred, then Q = Qp + R S~
+  // R = C - Qp A (FP64 MFMA, not split: a last-bit change of R moves its BF16 pairs
+  // and so q), centred, then Q = Qp + R S~
   { Timed t(c, "gemm_f64");
     launch_gemm_f64(st, false, false, rows, npad, npad, -1.0, w.qt, npad, b.A, npad, 1.0, w.res,
                     npad, 0, 0); }
@@ -3173,7 +3185,7 @@ void cpm_destroy(cpm_ctx* c) {
   dfree(b.zcounts); dfree(b.zbinoff); dfree(b.zpart); dfree(b.dtot);
   dfree(c->zb.d_units); dfree(c->zb.d_cu_of); dfree(c->zb.d_cols); dfree(c->zb.d_w);
   dfree(c->zb.wide.d_items); dfree(c->zb.narrow.d_items); dfree(c->zt[0].H); dfree(c->zt[1].H);
-  dfree(b.kpart); dfree(b.ccmU); dfree(b.ccmC); dfree(b.sg); dfree(b.zeta); dfree(b.szeta);
+  dfree(b.kpart); dfree(b.gws.p); dfree(b.ccmU); dfree(b.ccmC); dfree(b.sg); dfree(b.zeta); dfree(b.szeta);
   dfree(b.Qpair); dfree(b.ell_col); dfree(b.ell_val); dfree(b.plane_off); dfree(b.dextra);
   dfree(b.bsr_col); dfree(b.bsr_val); dfree(b.cg_items); dfree(b.asmG); dfree(b.asmF);
   dfree(b.Ecat); dfree(b.cg_ident); dfree(b.cgv); dfree(b.cgred);

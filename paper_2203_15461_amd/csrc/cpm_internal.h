@@ -85,6 +85,12 @@ struct ZbTable {
   bool used = false;               // formed at least once
 };
 
+// partial tiles of split FP64 products (see launch_gemm_f64)
+struct GemmWork {
+  double* p = nullptr;
+  size_t len = 0;
+};
+
 struct Buffers {
   // electrode geometry (internal order = caller order), SoA, x and y wrapped
   double* ex = nullptr;  double* ey = nullptr;  double* ez = nullptr;
@@ -154,6 +160,7 @@ struct Buffers {
   uint16_t* xlo = nullptr;         //   (bpad_rows x npad each)
   double* means = nullptr;         // per-vector uniform part removed before S products
   double* kpart = nullptr;         // split-K partial slices of the batched split-BF16 GEMM
+  GemmWork gws;                    // partial tiles of the FP64 solves
   double* ccmU = nullptr;          // constrained charges: U = A^-1 G (n x n_e)
   double* ccmC = nullptr;          // C~^-1 (n_e x n_e) followed by the targets Q (n_e)
   double* sg = nullptr;            // S G: response of the charges to each electrode's
@@ -444,7 +451,11 @@ void launch_mirror_lower(hipStream_t st, int npad, double* A);
 // tri: 0 all tiles, 1 lower tiles only.  kmode: 0 K range [0,K), 1 [max(m0,n0), K).
 void launch_gemm_f64(hipStream_t st, bool transA, bool transB, int M, int N, int K,
                      double alpha, const double* A, int lda, const double* B, int ldb,
-                     double beta, double* C, int ldc, int tri, int kmode, const int* rowmap = nullptr);
+                     double beta, double* C, int ldc, int tri, int kmode, const int* rowmap = nullptr,
+                     GemmWork work = {});
+// doubles of work that splits an M x N x K product (0: it is better unsplit); with
+// less it runs unsplit.  Only untransposed, full products are split.
+size_t gemm_f64_work(int M, int N, int K);
 void launch_potrf_diag(hipStream_t st, double* Lblk, int ld, double* Dinv, int* flag, int k0);
 void launch_set_identity(hipStream_t st, int npad, double* X);
 void launch_row_sums(hipStream_t st, int n, int npad, const double* M, double* out);

@@ -18,116 +18,297 @@
 namespace cpm {
 
 typedef double v4d __attribute__((ext_vector_type(4)));
+typedef double d2v __attribute__((ext_vector_type(2)));
 
 // ---------------------------------------------------------------------------
-// GEMM: C = beta C + alpha op(A) op(B), 64x64 tile per 256-thread workgroup,
-// each wave a 32x32 quadrant of 2x2 MFMA blocks, K staged through LDS in
-// slabs of 16 with the next slab prefetched into registers.
+// GEMM: C = beta C + alpha op(A) op(B), T x T tile per workgroup of 4 T threads, K
+// in slabs of 16 through two alternating LDS buffers, one barrier per slab, the
+// next slab's global loads (of the next tile at a tile's end) in flight.  M and N
+// are multiples of 64, K of 16.  The FP64 matrix rate bounds large products: a
+// register-only loop reaches 50-57 TFLOP/s with one wave per SIMD and 66-67 with
+// two or more.
+//
+// T = 64, a workgroup (four waves of 32 x 32) per tile: 80 registers and 36 KiB of
+// LDS, so that four workgroups share a CU.  Tiles in row-major order, only those
+// on and below the diagonal for tri.  K runs in one chain in ascending order, as it
+// always has: the same bits, which the split-BF16 copies and refinement residuals
+// need.  One LDS buffer and two barriers per slab reached less (before -> now, in
+// TFLOP/s, random operands): K = 512, N = 8192 NN 49 -> 60, its lower triangle NT
+// 40 -> 53, N = 2432 31 -> 43; X^T X of a lower-triangular X, n = 8192 41 -> 58,
+// n = 2944 30 -> 37; N = K = 2944, M = 1024 45 -> 56.  Rank-64 updates are bound by
+// the traffic of C and stay: 12224 x 448 x 64 24 us.  128 x 128 tiles, two
+// workgroups per CU, gave the same or less for want of tiles (K = 512 lower
+// triangle n = 4096 39 against 49), 5 % more only in the largest X^T X.
+//
+// SPLIT, T = 128 (eight waves of 64 x 32): too few tiles for the chip, so all tiles'
+// slabs, in tile order, are cut into GT_RUNS equal runs, one workgroup per CU.  A
+// run writes the tiles that it begins; the head of a run that continues a tile goes
+// to the work array (128 KiB per run) and k_gemm_f64_join adds it, so that every
+// sum has one fixed order.  The kernel has to stay within 128 registers (212
+// when 32 store addresses were hoisted: 343 us instead of 291 for M = 1024 below).
+// C must not overlap A or B.  Before -> T = 64 -> split, N = K = 2944: M = 64 169 ->
+// 140 -> 64 us, M = 256 171 -> 142 -> 102, M = 512 280 -> 220 -> 177.
 // ---------------------------------------------------------------------------
-template <bool TA, bool TB>
-__global__ void __launch_bounds__(256) k_gemm_f64(int M, int N, int K, double alpha,
-                                                  const double* __restrict__ A, int lda,
-                                                  const double* __restrict__ B, int ldb,
-                                                  double beta, double* C, int ldc, int tri,
-                                                  int kmode, const int* __restrict__ rowmap) {
-  const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
-  if (tri && n0 > m0) return;
-  const int kbeg = kmode ? (m0 > n0 ? m0 : n0) : 0;
-  __shared__ double As[16][64 + 4];
-  __shared__ double Bs[16][64 + 4];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
-  v4d acc[2][2];
-  for (int a = 0; a < 2; ++a)
-    for (int b = 0; b < 2; ++b) acc[a][b] = (v4d){0.0, 0.0, 0.0, 0.0};
+// LDS pitch (16 rows of a read on distinct banks); doubles of a split tile; runs
+constexpr int GT_P = 18, GT_PART = 128 * 128, GT_LRUNS = 8, GT_RUNS = 1 << GT_LRUNS;
 
-  double ra[4], rb[4];
-  auto load = [&](int k0) {
-    if (!TA) {
-      const int r = tid >> 2, c = (tid & 3) * 4;
-      const double* src = A + (size_t)(m0 + r) * lda + k0 + c;
-      for (int t = 0; t < 4; ++t) ra[t] = src[t];
-    } else {
-      const int r = tid >> 4, c = (tid & 15) * 4;
-      const double* src = A + (size_t)(k0 + r) * lda + m0 + c;
-      for (int t = 0; t < 4; ++t) ra[t] = src[t];
-    }
-    if (!TB) {
-      const int r = tid >> 4, c = (tid & 15) * 4;
-      const double* src = B + (size_t)(k0 + r) * ldb + n0 + c;
-      for (int t = 0; t < 4; ++t) rb[t] = src[t];
-    } else {
-      const int r = tid >> 2, c = (tid & 3) * 4;
-      const double* src = B + (size_t)(n0 + r) * ldb + k0 + c;
-      for (int t = 0; t < 4; ++t) rb[t] = src[t];
-    }
-  };
-  auto store = [&]() {
-    if (!TA) {
-      const int r = tid >> 2, c = (tid & 3) * 4;
-      for (int t = 0; t < 4; ++t) As[c + t][r] = ra[t];
-    } else {
-      const int r = tid >> 4, c = (tid & 15) * 4;
-      for (int t = 0; t < 4; ++t) As[r][c + t] = ra[t];
-    }
-    if (!TB) {
-      const int r = tid >> 4, c = (tid & 15) * 4;
-      for (int t = 0; t < 4; ++t) Bs[r][c + t] = rb[t];
-    } else {
-      const int r = tid >> 2, c = (tid & 3) * 4;
-      for (int t = 0; t < 4; ++t) Bs[c + t][r] = rb[t];
-    }
-  };
-
-  if (kbeg < K) load(kbeg);
-  for (int k0 = kbeg; k0 < K; k0 += 16) {
-    store();
-    __syncthreads();
-    if (k0 + 16 < K) load(k0 + 16);
-#pragma unroll
-    for (int kk = 0; kk < 16; kk += 4) {
-      const int kr = kk + (lane >> 4), cc = lane & 15;
-      const double a0 = As[kr][wm + cc], a1 = As[kr][wm + 16 + cc];
-      const double b0 = Bs[kr][wn + cc], b1 = Bs[kr][wn + 16 + cc];
-      acc[0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b0, acc[0][0], 0, 0, 0);
-      acc[0][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b1, acc[0][1], 0, 0, 0);
-      acc[1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b0, acc[1][0], 0, 0, 0);
-      acc[1][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b1, acc[1][1], 0, 0, 0);
-    }
-    __syncthreads();
+// The tiles in row-major order (tri: those on and below the diagonal), each a run
+// of K slabs (kmode: from its own first row).
+struct GtGeom {
+  int M, N, K, tri, kmode, T, tm, tn;
+  int total;                                         // slabs of all tiles (split)
+  __host__ __device__ int cols(int bm) const { return tri && bm + 1 < tn ? bm + 1 : tn; }
+  __host__ __device__ int kbeg(int bm) const { return kmode ? bm * T : 0; }
+  __host__ __device__ int slabs(int bm) const { return (K - kbeg(bm)) / 16; }
+  __host__ __device__ int tiles() const {
+    return tri ? tm * tn - tn * (tn - 1) / 2 : tm * tn;      // (tri: tm >= tn)
   }
-  for (int a = 0; a < 2; ++a)
-    for (int b = 0; b < 2; ++b)
-      for (int r = 0; r < 4; ++r) {
-        int row = m0 + wm + a * 16 + (lane >> 4) + 4 * r;
-        if (rowmap) {                                  // scattered output rows (-1: skip)
-          row = rowmap[row];
-          if (row < 0) continue;
-        }
-        const int col = n0 + wn + b * 16 + (lane & 15);
-        double* cp = C + (size_t)row * ldc + col;
-        const double v = alpha * acc[a][b][r];
-        *cp = (beta != 0.0) ? v + beta * (*cp) : v;
+  __host__ __device__ int begin(int w) const { return (int)((long)total * w >> GT_LRUNS); }
+  // the tile and slab of position `it` in the concatenation of all tiles
+  __host__ __device__ void locate(int it, int& bm, int& bn, int& s) const {
+    for (bm = 0;; ++bm) {
+      const int in_row = cols(bm) * slabs(bm);
+      if (it < in_row) break;
+      it -= in_row;
+    }
+    bn = it / slabs(bm);
+    s = it - bn * slabs(bm);
+  }
+  // tile w
+  __device__ void tile(int w, int& bm, int& bn) const {
+    const int head = tn * (tn - 1) / 2;              // tiles of the rows 0 .. tn - 2
+    if (tri && w < head) {                           // row bm holds bm + 1 tiles
+      bm = (int)((sqrtf(8.f * w + 1.f) - 1.f) * 0.5f);
+      while (bm * (bm + 1) / 2 > w) --bm;
+      while ((bm + 1) * (bm + 2) / 2 <= w) ++bm;
+      bn = w - bm * (bm + 1) / 2;
+    } else {
+      const int t = tri ? w - head : w;
+      bm = t / tn;
+      bn = t - bm * tn;
+      if (tri) bm += tn - 1;
+    }
+  }
+};
+
+template <int T>
+struct GtWave {                                      // this thread's part of a tile
+  static constexpr int BI = T / 32, BJ = 2;          // MFMA block rows and columns of a wave
+  static constexpr int WC = T / 32;                  // waves side by side
+  static __device__ int wm() { return (int)(threadIdx.x >> 6) / WC * (16 * BI); }
+  static __device__ int wn() { return (int)(threadIdx.x >> 6) % WC * 32; }
+  // output row of register r of block row i (-1: none) and column of block column j
+  static __device__ int row(int i, int r, int m0, int M, const int* rowmap) {
+    const int row = m0 + wm() + 16 * i + (int)((threadIdx.x & 63) >> 4) + 4 * r;
+    if (row >= M) return -1;
+    return rowmap ? rowmap[row] : row;               // scattered output rows (-1: skip)
+  }
+  static __device__ int col(int j, int n0) { return n0 + wn() + 16 * j + (int)(threadIdx.x & 15); }
+};
+
+template <int T, bool SPLIT, bool TA, bool TB>
+__global__ void __launch_bounds__(4 * T, 4) k_gemm_f64(GtGeom g, double alpha,
+                                                       const double* __restrict__ A, int lda,
+                                                       const double* __restrict__ B, int ldb,
+                                                       double beta, double* C, int ldc,
+                                                       const int* __restrict__ rowmap,
+                                                       double* __restrict__ part) {
+  using W = GtWave<T>;
+  __shared__ __align__(16) double sA[2][T][GT_P];
+  __shared__ __align__(16) double sB[2][T][GT_P];
+  int bm, bn, s0 = 0, it, end, w;
+  if (SPLIT) {
+    // workgroups of one XCD (every eighth) take neighbouring runs
+    w = (int)(blockIdx.x & 7) * (GT_RUNS / 8) + (int)(blockIdx.x >> 3);
+    it = g.begin(w);
+    end = g.begin(w + 1);
+    if (it >= end) return;
+    g.locate(it, bm, bn, s0);
+  } else {
+    w = blockIdx.x;
+    g.tile(w, bm, bn);
+    it = 0;
+    end = g.slabs(bm);
+  }
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wm = W::wm(), wn = W::wn(), l15 = lane & 15, lg = lane >> 4;
+  // loader: a row and 4 k (row-major operand) or a k and 4 rows (k-major one)
+  const int rr = tid >> 2, rk = (tid & 3) * 4, kk = tid & 15, kr = (tid >> 4) * 4;
+  const double *pa, *pb;
+  auto start = [&](int m, int n, int k) {
+    pa = TA ? A + (size_t)(k + kk) * lda + min(m * T + kr, g.M - 4)
+            : A + (size_t)min(m * T + rr, g.M - 1) * lda + k + rk;
+    pb = TB ? B + (size_t)min(n * T + rr, g.N - 1) * ldb + k + rk
+            : B + (size_t)(k + kk) * ldb + min(n * T + kr, g.N - 4);
+  };
+  d2v a0, a1, b0, b1;
+  auto load = [&]() {
+    const d2v *qa = reinterpret_cast<const d2v*>(pa), *qb = reinterpret_cast<const d2v*>(pb);
+    a0 = qa[0]; a1 = qa[1];
+    b0 = qb[0]; b1 = qb[1];
+  };
+  auto store = [&](int buf) {
+    if (TA) {
+      sA[buf][kr][kk] = a0.x; sA[buf][kr + 1][kk] = a0.y;
+      sA[buf][kr + 2][kk] = a1.x; sA[buf][kr + 3][kk] = a1.y;
+    } else {
+      *reinterpret_cast<d2v*>(&sA[buf][rr][rk]) = a0;
+      *reinterpret_cast<d2v*>(&sA[buf][rr][rk + 2]) = a1;
+    }
+    if (TB) {
+      *reinterpret_cast<d2v*>(&sB[buf][rr][rk]) = b0;
+      *reinterpret_cast<d2v*>(&sB[buf][rr][rk + 2]) = b1;
+    } else {
+      sB[buf][kr][kk] = b0.x; sB[buf][kr + 1][kk] = b0.y;
+      sB[buf][kr + 2][kk] = b1.x; sB[buf][kr + 3][kk] = b1.y;
+    }
+  };
+  start(bm, bn, g.kbeg(bm) + 16 * s0);
+  load();
+  store(0);
+  __syncthreads();
+  int buf = 0;
+  while (it < end) {
+    v4d acc[W::BI][W::BJ];
+    int nm = bm, nn = bn + 1, ns = end - it;         // the next tile
+    if (SPLIT) {
+      ns = min(g.slabs(bm) - s0, ns);
+      if (nn == g.cols(bm)) {
+        nn = 0;
+        ++nm;
       }
+    }
+    it += ns;
+#pragma unroll
+    for (int i = 0; i < W::BI; ++i)
+#pragma unroll
+      for (int j = 0; j < W::BJ; ++j) acc[i][j] = (v4d){0.0, 0.0, 0.0, 0.0};
+    for (int s = 0; s < ns; ++s) {
+      if (s + 1 < ns) {
+        pa += TA ? (size_t)16 * lda : 16;
+        pb += TB ? 16 : (size_t)16 * ldb;
+      } else if (SPLIT && it < end) {
+        start(nm, nn, g.kbeg(nm));
+      }
+      load();                                        // (a run's last slab loads itself again)
+#pragma unroll
+      for (int h = 0; h < 4; ++h) {
+        double a[W::BI], b[W::BJ];
+#pragma unroll
+        for (int i = 0; i < W::BI; ++i) a[i] = sA[buf][wm + 16 * i + l15][4 * h + lg];
+#pragma unroll
+        for (int j = 0; j < W::BJ; ++j) b[j] = sB[buf][wn + 16 * j + l15][4 * h + lg];
+#pragma unroll
+        for (int i = 0; i < W::BI; ++i)
+#pragma unroll
+          for (int j = 0; j < W::BJ; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], b[j], acc[i][j], 0, 0, 0);
+      }
+      store(buf ^ 1);
+      __syncthreads();
+      buf ^= 1;
+    }
+    if (!SPLIT || s0 == 0) {
+#pragma unroll
+      for (int i = 0; i < W::BI; ++i)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int row = W::row(i, r, bm * T, g.M, rowmap);
+          if (row < 0) continue;
+#pragma unroll
+          for (int j = 0; j < W::BJ; ++j) {
+            const int col = W::col(j, bn * T);
+            if (col >= g.N) continue;
+            double* cp = C + (size_t)row * ldc + col;
+            const double v = alpha * acc[i][j][r];
+            *cp = (beta != 0.0) ? v + beta * (*cp) : v;
+          }
+        }
+    } else {                                         // at most the run's first tile
+      unsigned o = w * GT_PART + tid;
+      asm("" : "+v"(o));                             // (keeps 32 addresses out of the slab loop)
+#pragma unroll
+      for (int i = 0; i < W::BI; ++i)
+#pragma unroll
+        for (int j = 0; j < W::BJ; ++j)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) part[o + ((i * 2 + j) * 4 + r) * 512] = acc[i][j][r];
+    }
+    s0 = 0;
+    bm = nm;
+    bn = nn;
+  }
+}
+
+// C += alpha (the later K parts of a tile, in order of k); blockIdx.x = the run
+// that holds the tile's second part, blockIdx.y = MFMA block row
+__global__ void __launch_bounds__(512) k_gemm_f64_join(GtGeom g, double alpha, double* C, int ldc,
+                                                       const int* __restrict__ rowmap,
+                                                       const double* __restrict__ part) {
+  using W = GtWave<128>;
+  const int w = blockIdx.x + 1, i = blockIdx.y;
+  const int it = g.begin(w);
+  if (it >= g.total) return;
+  int bm, bn, s;
+  g.locate(it, bm, bn, s);
+  if (s == 0 || g.begin(w - 1) > it - s) return;     // a tile's start, or a third part
+  const int tend = it - s + g.slabs(bm);
+  v4d acc[2] = {(v4d){0.0, 0.0, 0.0, 0.0}, (v4d){0.0, 0.0, 0.0, 0.0}};
+  for (int v = w; v < GT_RUNS && g.begin(v) < tend; ++v) {
+    if (g.begin(v) == g.begin(v + 1)) continue;
+    const double* pv = part + (size_t)v * GT_PART + threadIdx.x;
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) acc[j][r] += pv[((i * 2 + j) * 4 + r) * 512];
+  }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int row = W::row(i, r, bm * 128, g.M, rowmap);
+    if (row < 0) continue;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int col = W::col(j, bn * 128);
+      if (col < g.N) C[(size_t)row * ldc + col] += alpha * acc[j][r];
+    }
+  }
+}
+
+// Split up to two 64-tiles per CU, where unsplit workgroups have a CU to themselves
+// or share it unevenly: N = K = 2944 with M = 512 (368 tiles) 220 -> 177 us, M = 1024
+// (736 tiles) 316 -> 305, not worth twice the work array.  Short products do not
+// repay the partial tiles and the second launch: 256 x 1024 x 1024 (1024 slabs of
+// 128-tiles) 48 -> 38 us, 2048 x 576 x 576 50 -> 52, 256 x 576 x 576 29 -> 40.
+size_t gemm_f64_work(int M, int N, int K) {
+  const long tiles = (long)((M + 127) / 128) * ((N + 127) / 128);
+  const bool split = K >= 1024 && (long)(M / 64) * (N / 64) <= 512 && tiles * (K / 16) >= 1024;
+  return split ? (size_t)GT_PART * GT_RUNS : 0;
 }
 
 void launch_gemm_f64(hipStream_t st, bool transA, bool transB, int M, int N, int K, double alpha,
                      const double* A, int lda, const double* B, int ldb, double beta, double* C,
-                     int ldc, int tri, int kmode, const int* rowmap) {
+                     int ldc, int tri, int kmode, const int* rowmap, GemmWork work) {
   if (M <= 0 || N <= 0) return;
-  dim3 grid(N / 64, M / 64), block(256);
-  if (!transA && !transB)
-    hipLaunchKernelGGL((k_gemm_f64<false, false>), grid, block, 0, st, M, N, K, alpha, A, lda, B,
-                       ldb, beta, C, ldc, tri, kmode, rowmap);
-  else if (!transA && transB)
-    hipLaunchKernelGGL((k_gemm_f64<false, true>), grid, block, 0, st, M, N, K, alpha, A, lda, B,
-                       ldb, beta, C, ldc, tri, kmode, rowmap);
-  else if (transA && !transB)
-    hipLaunchKernelGGL((k_gemm_f64<true, false>), grid, block, 0, st, M, N, K, alpha, A, lda, B,
-                       ldb, beta, C, ldc, tri, kmode, rowmap);
-  else
-    hipLaunchKernelGGL((k_gemm_f64<true, true>), grid, block, 0, st, M, N, K, alpha, A, lda, B,
-                       ldb, beta, C, ldc, tri, kmode, rowmap);
+  const size_t need = gemm_f64_work(M, N, K);
+  if (need > 0 && work.len >= need && !transA && !transB && !tri && !kmode) {
+    const GtGeom g{M, N, K, 0, 0, 128, (M + 127) / 128, (N + 127) / 128,
+                   ((M + 127) / 128) * ((N + 127) / 128) * (K / 16)};
+    hipLaunchKernelGGL((k_gemm_f64<128, true, false, false>), dim3(GT_RUNS), dim3(512), 0, st, g,
+                       alpha, A, lda, B, ldb, beta, C, ldc, rowmap, work.p);
+    hipLaunchKernelGGL(k_gemm_f64_join, dim3(GT_RUNS - 1, 4), dim3(512), 0, st, g, alpha, C, ldc,
+                       rowmap, work.p);
+    return;
+  }
+  const GtGeom g{M, N, K, tri, kmode, 64, M / 64, N / 64, 0};
+#define CPM_GT(TA, TB)                                                                              \
+  hipLaunchKernelGGL((k_gemm_f64<64, false, TA, TB>), dim3(g.tiles()), dim3(256), 0, st, g, alpha, A, \
+                     lda, B, ldb, beta, C, ldc, rowmap, nullptr)
+  if (transA) {
+    if (transB) CPM_GT(true, true); else CPM_GT(true, false);
+  } else {
+    if (transB) CPM_GT(false, true); else CPM_GT(false, false);
+  }
+#undef CPM_GT
 }
 
 // ---------------------------------------------------------------------------
@@ -436,7 +617,6 @@ void launch_convert_S(hipStream_t st, int npad, const double* S, float* S32, uin
 // order.  Matrices larger than the last-level cache are read with
 // nontemporal loads (streamed past the caches, which the x vector keeps).
 // ---------------------------------------------------------------------------
-typedef double d2v __attribute__((ext_vector_type(2)));
 typedef float f4v __attribute__((ext_vector_type(4)));
 
 template <typename TM, int R, bool NT>
