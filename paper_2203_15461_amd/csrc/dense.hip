@@ -312,15 +312,23 @@ void launch_gemm_f64(hipStream_t st, bool transA, bool transB, int M, int N, int
 }
 
 // ---------------------------------------------------------------------------
-// Diagonal 64x64 block of the Cholesky factorisation, in one workgroup, in
-// four panels of 16 columns: wave 0 factors the panel's 16 x 16 diagonal
-// block right-looking in registers (cross-lane moves), one thread per row below
-// solves that row's 16 panel entries, then every thread updates trailing
-// elements.  The inverse of the factor: the four diagonal 16 x 16 blocks by
-// forward substitution (a wave each, a lane per column), then block rows 1..3
-// in turn, X_ik = -X_ii sum_{j=k}^{i-1} L_ij X_jk.  About 20 workgroup
-// barriers in all.  A pivot <= 0 (or NaN) records 1 + its global index in
-// *flag (first one wins) and continues with 1.
+// Diagonal 64x64 block of the Cholesky factorisation and the inverse of its
+// factor, in one workgroup, in four panels of 16 columns.  The chain of 64 roots and
+// reciprocals bounds it, so wave 0 factors a panel alone in registers, a lane per
+// row of the block and every row at once: a step reads the pivot and the column's
+// entries in the panel from their lanes, and its updates fill the latency of the
+// next step's root.  The columns right of the panel follow by MFMA, 16 x 16 blocks
+// over the waves.  The other waves meanwhile form the inverse, as far as panels are
+// complete: the diagonal 16 x 16 blocks by forward substitution, then block column
+// k by one wave, X_ik = -X_ii sum_{j=k}^{i-1} L_ij X_jk by MFMA.  Every element is
+// one chain of FMAs in ascending order of the summed index, which FP64 MFMA keeps.
+// A pivot <= 0 (or NaN) records 1 + its global index in *flag (first one wins) and
+// continues with 1.
+// 34.5 us in one workgroup of 16 waves with the root and a division in the chain and
+// the inverse afterwards; now 12.4: 1.0 us loads, 2.0 per panel (330 clocks per column
+// before the LDS reads of its entries were moved behind the next root, 290 after),
+// 0.3-0.6 for the columns right of it, 1.8 for what of the inverse needs the last
+// panel.
 // ---------------------------------------------------------------------------
 // lane l's value of v, in every lane (l uniform)
 __device__ inline double readlane_f64(double v, int l) {
@@ -330,142 +338,187 @@ __device__ inline double readlane_f64(double v, int l) {
   return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
 
-__global__ void __launch_bounds__(1024) k_potrf_diag(double* Lblk, int ld, double* Dinv, int* flag,
-                                                     int k0) {
-  __shared__ double a[64][65];     // working lower triangle, becomes L
-  __shared__ double X[64][65];     // L^-1
-  __shared__ double T[3][16][17];  // block-row products of the inverse
-  __shared__ double rd[64];        // 1 / L[j][j]
+// d = sqrt(x) and 1 / d, both correctly rounded, for x well inside the FP64 range
+// unless d is all ones: Goldschmidt's iteration for the root and half its reciprocal
+// together, then each one's residual by FMA (Markstein).  Eight operations in a
+// chain instead of about 30 of sqrt(x) and a division, with equal results.
+__device__ inline void root_and_reciprocal(double x, double& d, double& rd) {
+  const double y = __builtin_amdgcn_rsq(x);
+  double g = x * y, h = 0.5 * y;
+  double r = fma(-h, g, 0.5);
+  g = fma(g, r, g);
+  h = fma(h, r, h);
+  r = fma(-h, g, 0.5);
+  d = fma(fma(-g, g, x), h, g);
+  h = fma(h, r, h);
+  h += h;
+  rd = fma(fma(-d, h, 1.0), h, h);
+}
+
+// panel p0 of the block in LDS, by one wave; FAST: by root_and_reciprocal; false if
+// that is not exact for a pivot (the block is as before then, bc and rd are not)
+template <bool FAST>
+__device__ inline bool potrf_panel(double (*a)[65], double* bc, double* rd, int p0, int lane, int* flag,
+                                   int k0) {
+  double v[16], lc[16], dl = 1.0;          // lc: column j's entries in the panel
+#pragma unroll
+  for (int t = 0; t < 16; ++t) v[t] = a[lane][p0 + t];
+  double piv = readlane_f64(v[0], p0), d, rdj;
+#pragma unroll
+  for (int j = 0; j < 16; ++j) {
+    if (FAST) {
+      root_and_reciprocal(piv, d, rdj);
+    } else {
+      if (!(piv > 0.0)) {
+        if (lane == 0) atomicCAS(flag, 0, k0 + p0 + j + 1);
+        piv = 1.0;
+      }
+      d = sqrt(piv);
+      rdj = 1.0 / d;
+    }
+    // the previous column's updates past the next one: its entries come by LDS,
+    // whose latency the root covers
+#pragma unroll
+    for (int c = j + 1; c < 16; ++c)
+      if (j > 0) v[c] -= v[j - 1] * lc[c];
+    __builtin_amdgcn_sched_barrier(0);
+    v[j] *= rdj;                           // column j of L below the diagonal
+    if (j < 15) {
+      // (the next pivot's lane multiplies its own entry, ahead of the others)
+      piv = readlane_f64(v[j + 1] - v[j] * v[j], p0 + j + 1);
+      bc[lane] = v[j];
+#pragma unroll
+      for (int c = j + 2; c < 16; ++c) lc[c] = bc[p0 + c];
+      v[j + 1] -= v[j] * readlane_f64(v[j], p0 + j + 1);
+    }
+    if (lane == p0 + j) dl = d;
+    rd[p0 + j] = rdj;                      // (every lane the same)
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  if (FAST && __any(!(dl > 0x1p-200 && dl < 0x1p200) || (__double_as_longlong(dl) << 12 | 0xfff) == -1))
+    return false;
+  if (lane >= p0) {
+#pragma unroll
+    for (int t = 0; t < 16; ++t) a[lane][p0 + t] = v[t];
+    if (lane < p0 + 16) a[lane][lane] = dl;
+  }
+  return true;
+}
+
+// X = the inverse of L's diagonal block at p0 by forward substitution, a lane per
+// column (one wave); entries above the diagonal come out as zero
+__device__ inline void invert16(const double (*a)[65], const double* rd, int p0, int lane,
+                                double (*X)[17]) {
+  if (lane < 16) {
+    double s[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) s[r] = r == lane ? 1.0 : 0.0;
+#pragma unroll
+    for (int t = 0; t < 16; ++t) {
+      s[t] *= rd[p0 + t];
+#pragma unroll
+      for (int r = t + 1; r < 16; ++r) s[r] -= a[p0 + r][p0 + t] * s[t];
+    }
+#pragma unroll
+    for (int r = 0; r < 16; ++r) X[r][lane] = s[r];
+  }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+}
+
+// acc + L x: L 16 x 16 in LDS (pitch P), x and acc in MFMA registers (register h of
+// a result is the right operand of the next product's k = 4 h .. 4 h + 3)
+template <int P>
+__device__ inline v4d mul16(const double* L, v4d x, v4d acc, int lane) {
+#pragma unroll
+  for (int h = 0; h < 4; ++h)
+    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(L[(lane & 15) * P + 4 * h + (lane >> 4)], x[h], acc, 0,
+                                               0, 0);
+  return acc;
+}
+
+__global__ void __launch_bounds__(256) k_potrf_diag(double* Lblk, int ld, double* Dinv, int* flag,
+                                                    int k0) {
+  __shared__ double a[64][65];      // working lower triangle, becomes L (above: anything)
+  __shared__ double Xd[4][16][17];  // inverses of L's diagonal 16 x 16 blocks
+  __shared__ double rd[64];         // 1 / L[j][j]
+  __shared__ __align__(16) double bc[64];   // a column of L
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int l15 = lane & 15, lg = lane >> 4, k = wave - 1;
   {
-    // four entries per thread, their loads all in flight at once
-    double t[4];
+    double t[16];                   // all loads in flight at once
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int e = tid + 1024 * u, r = e >> 6, c = e & 63;
-      t[u] = (c <= r) ? Lblk[(size_t)r * ld + c] : 0.0;
-    }
+    for (int u = 0; u < 16; ++u) t[u] = Lblk[(size_t)(wave + 4 * u) * ld + lane];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int e = tid + 1024 * u, r = e >> 6, c = e & 63;
-      a[r][c] = t[u];
-      X[r][c] = 0.0;
-    }
+    for (int u = 0; u < 16; ++u) a[wave + 4 * u][lane] = t[u];
   }
   __syncthreads();
-  for (int p0 = 0; p0 < 64; p0 += 16) {
+  const v4d zero = (v4d){0.0, 0.0, 0.0, 0.0};
+  v4d t0 = zero, t1 = zero, t2 = zero, t3 = zero;      // sum_j L_ij X_jk of rows i = p - 1 ..
+  auto put = [&](int i, int kk, v4d y) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) Dinv[(16 * i + lg + 4 * r) * 64 + 16 * kk + l15] = y[r];
+  };
+  auto put_L = [&](int p) {                            // L's columns of panel p
+    for (int r = 4 * k + lg; r < 64; r += 12)
+      Lblk[(size_t)r * ld + 16 * p + l15] = 16 * p + l15 <= r ? a[r][16 * p + l15] : 0.0;
+  };
+  auto diag = [&](int p) {
+    v4d y;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) y[r] = Xd[p][lg + 4 * r][l15];
+    return y;
+  };
+#pragma unroll 1
+  for (int p = 0; p < 4; ++p) {
+    const int p0 = 16 * p;
     if (wave == 0) {
-      // lane (r, part) keeps row p0 + r, columns p0 + 4 part .. + 3, of the
-      // panel's diagonal block in registers; step j reads the pivot and the
-      // entries of column j from the lanes that own them (cross-lane moves),
-      // so no step waits on LDS
-      const int r = lane & 15, part = lane >> 4;
-      double v[4];
-#pragma unroll
-      for (int s = 0; s < 4; ++s) v[s] = a[p0 + r][p0 + 4 * part + s];
-      double rdl = 0.0;                    // 1 / L[p0 + r][p0 + r]
-#pragma unroll
-      for (int j = 0; j < 16; ++j) {
-        const int pj = j >> 2, sj = j & 3;   // owner part and slot of column j
-        double piv = readlane_f64(v[sj], j + 16 * pj);
-        if (!(piv > 0.0)) {
-          if (lane == 0) atomicCAS(flag, 0, k0 + p0 + j + 1);
-          piv = 1.0;
-        }
-        const double d = sqrt(piv), rdj = 1.0 / d;
-        const double arj = __shfl(v[sj], r + 16 * pj, 64);       // L[r][j] before scaling
-        double acj[4];
-#pragma unroll
-        for (int s = 0; s < 4; ++s) acj[s] = __shfl(v[sj], 4 * part + s + 16 * pj, 64);
-        const double lr = arj * rdj;
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-          const int c = 4 * part + s;
-          if (c > j && c <= r) v[s] -= lr * (acj[s] * rdj);
-        }
-        if (part == pj) {
-          if (r > j) v[sj] = lr;
-          else if (r == j) v[sj] = d;
-        }
-        if (r == j) rdl = rdj;
+      if (!potrf_panel<true>(a, bc, rd, p0, lane, flag, k0))
+        potrf_panel<false>(a, bc, rd, p0, lane, flag, k0);
+    } else if (p > 0) {
+      // meanwhile: block row p - 1 of the inverse, by each wave its column k, from
+      // the same inverse of the diagonal block
+      invert16(a, rd, p0 - 16, lane, Xd[p - 1]);
+      if (k <= p - 1) {
+        const v4d y = k == p - 1 ? diag(p - 1) : -mul16<17>(&Xd[p - 1][0][0], t0, zero, lane);
+        t0 = mul16<65>(&a[p0][p0 - 16], y, t1, lane);
+        if (p < 3) t1 = mul16<65>(&a[p0 + 16][p0 - 16], y, t2, lane);
+        if (p < 2) t2 = mul16<65>(&a[p0 + 32][p0 - 16], y, t3, lane);
+        put(p - 1, k, y);
+      } else {
+        put(p - 1, k, zero);
       }
-#pragma unroll
-      for (int s = 0; s < 4; ++s)
-        if (4 * part + s <= r) a[p0 + r][p0 + 4 * part + s] = v[s];
-      if (part == 0) rd[p0 + r] = rdl;
+      put_L(p - 1);
     }
     __syncthreads();
-    const int nrem = 64 - p0 - 16;
-    if (tid < nrem) {                      // row R of the panel below the diagonal block
-      const int R = p0 + 16 + tid;
-      double row[16];
+    // blocks (I, J) right of the panel, row by row of the triangle
+    const int nb = 3 - p;
+    for (int e = wave; e < nb * (nb + 1) / 2; e += 4) {
+      const int i = e < 1 ? 0 : e < 3 ? 1 : 2, j = e - i * (i + 1) / 2;
+      const int I = p0 + 16 * (i + 1), J = p0 + 16 * (j + 1);
+      v4d acc;
 #pragma unroll
-      for (int t = 0; t < 16; ++t) row[t] = a[R][p0 + t];
+      for (int r = 0; r < 4; ++r) acc[r] = a[I + lg + 4 * r][J + l15];
 #pragma unroll
-      for (int j = 0; j < 16; ++j) {
-        double s = row[j];
+      for (int h = 0; h < 4; ++h)
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(-a[I + l15][p0 + 4 * h + lg],
+                                                   a[J + l15][p0 + 4 * h + lg], acc, 0, 0, 0);
 #pragma unroll
-        for (int t = 0; t < j; ++t) s -= row[t] * a[p0 + j][p0 + t];
-        row[j] = s * rd[p0 + j];
-      }
-#pragma unroll
-      for (int t = 0; t < 16; ++t) a[R][p0 + t] = row[t];
+      for (int r = 0; r < 4; ++r) a[I + lg + 4 * r][J + l15] = acc[r];
     }
-    __syncthreads();
-    for (int e = tid; e < nrem * nrem; e += 1024) {
-      const int R = p0 + 16 + e / nrem, C = p0 + 16 + e % nrem;
-      if (C <= R) {
-        double s = a[R][C];
-#pragma unroll
-        for (int t = 0; t < 16; ++t) s -= a[R][p0 + t] * a[C][p0 + t];
-        a[R][C] = s;
-      }
-    }
-    __syncthreads();
+    if (p < 3) __syncthreads();
   }
-  // diagonal blocks of X: wave k inverts L_kk, lane c solves column c
-  if (wave < 4 && lane < 16) {
-    // entries above the diagonal of the column stay zero: x[t] = 0 for t < c
-    const int p0 = 16 * wave, c = lane;
-    double x[16];
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      double s = (r == c) ? 1.0 : 0.0;
-#pragma unroll
-      for (int t = 0; t < r; ++t) s -= a[p0 + r][p0 + t] * x[t];
-      x[r] = (r >= c) ? s * rd[p0 + r] : 0.0;
-    }
-#pragma unroll
-    for (int r = 0; r < 16; ++r) X[p0 + r][p0 + c] = x[r];
-  }
-  __syncthreads();
-  for (int i = 1; i < 4; ++i) {
-    const int k = tid >> 8, r = (tid >> 4) & 15, c = tid & 15;
-    if (k < i) {
-      double s = 0.0;
-      for (int j = k; j < i; ++j)
-#pragma unroll
-        for (int t = 0; t < 16; ++t) s += a[16 * i + r][16 * j + t] * X[16 * j + t][16 * k + c];
-      T[k][r][c] = s;
-    }
-    __syncthreads();
-    if (k < i) {
-      double s = 0.0;
-#pragma unroll
-      for (int t = 0; t < 16; ++t) s += X[16 * i + r][16 * i + t] * T[k][t][c];
-      X[16 * i + r][16 * k + c] = -s;
-    }
-    __syncthreads();
-  }
-  for (int e = tid; e < 64 * 64; e += 1024) {
-    const int r = e >> 6, c = e & 63;
-    Lblk[(size_t)r * ld + c] = (c <= r) ? a[r][c] : 0.0;
-    Dinv[e] = X[r][c];
+  if (wave > 0) put_L(3);
+  invert16(a, rd, 48, lane, Xd[3]);                    // (each wave the same values)
+  if (wave > 0) {
+    put(3, k, -mul16<17>(&Xd[3][0][0], t0, zero, lane));
+  } else {
+    put(3, 3, diag(3));
+    for (int i = 0; i < 3; ++i) put(i, 3, zero);
   }
 }
 
 void launch_potrf_diag(hipStream_t st, double* Lblk, int ld, double* Dinv, int* flag, int k0) {
-  hipLaunchKernelGGL(k_potrf_diag, dim3(1), dim3(1024), 0, st, Lblk, ld, Dinv, flag, k0);
+  hipLaunchKernelGGL(k_potrf_diag, dim3(1), dim3(256), 0, st, Lblk, ld, Dinv, flag, k0);
 }
 
 __global__ void k_set_identity(int npad, double* X) {
