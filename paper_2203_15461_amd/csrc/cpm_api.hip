@@ -1700,49 +1700,28 @@ cpm_status cpm_invert(cpm_ctx* c, unsigned store_flags) {
   // Blocked right-looking Cholesky on the lower triangle of L, two levels:
   // 64-wide panels inside blocks of OB columns (a multiple of 64), so that
   // the large trailing updates are rank-OB products (OB / 64 times fewer
-  // passes over the trailing matrix than rank-64 ones).
+  // passes over the trailing matrix than rank-64 ones).  X = L^-1 by forward
+  // substitution (in Ainv's buffer first), grouped alike, in the same launches.
   const int OB = c->chol_block;
+  const unsigned store_before = c->store;
+  const bool have_q_before = c->have_q;
+  double* X = factor ? nullptr : b.Ainv;
+  auto dinv = [&](int k0) { return b.Dinv + (size_t)(k0 / TILE) * TILE * TILE; };
+  if (X) launch_set_identity(st, npad, X);
+  { Timed t(c, "potrf_diag", st);
+    launch_potrf_diag(st, b.L, npad, b.Dinv, b.flag, 0); }
   for (int K0 = 0; K0 < npad; K0 += OB) {
     const int kend = std::min(npad, K0 + OB);
     for (int k0 = K0; k0 < kend; k0 += TILE) {
-      const int kb = k0 / TILE, rest = npad - k0 - TILE;
-      double* diag = b.L + (size_t)k0 * npad + k0;
-      { Timed t(c, "potrf_diag", st);
-        launch_potrf_diag(st, diag, npad, b.Dinv + (size_t)kb * TILE * TILE, b.flag, k0); }
-      if (rest > 0) {
-        Timed t(c, "chol_update", st);
-        double* panel = b.L + (size_t)(k0 + TILE) * npad + k0;
-        // L21 = A21 L11^-T for every row below the panel
-        launch_gemm_f64(st, false, true, rest, TILE, TILE, 1.0, panel, npad,
-                        b.Dinv + (size_t)kb * TILE * TILE, TILE, 0.0, panel, npad, 0, 0);
-        // A22 -= L21 L21^T on the block's own remaining columns (lower tiles)
-        const int pw = kend - (k0 + TILE);
-        if (pw > 0) {
-          double* trail = b.L + (size_t)(k0 + TILE) * npad + (k0 + TILE);
-          launch_gemm_f64(st, false, true, rest, pw, TILE, -1.0, panel, npad, panel, npad, 1.0,
-                          trail, npad, 1, 0);
-        }
-      }
-      TRY(launched(c, "cholesky"));
-    }
-    // the columns right of the block: A22 -= L21 L21^T with the block's OB columns
-    const int rest = npad - kend;
-    if (rest > 0) {
+      { Timed t(c, "chol_solve", st);
+        launch_chol_solve(st, npad, b.L, X, dinv(k0), k0); }
+      const int r0 = k0 + TILE;
       Timed t(c, "chol_update", st);
-      const double* P = b.L + (size_t)kend * npad + K0;
-      launch_gemm_f64(st, false, true, rest, rest, kend - K0, -1.0, P, npad, P, npad, 1.0,
-                      b.L + (size_t)kend * npad + kend, npad, 1, 0);
+      if (r0 < kend)                       // the block's own columns, and its rows of X
+        launch_chol_update(st, npad, b.L, X, dinv(r0), b.flag, k0, TILE, kend - r0, kend - r0, r0);
+      else if (r0 < npad)                  // all columns right of the block, all rows below
+        launch_chol_update(st, npad, b.L, X, dinv(r0), b.flag, K0, r0 - K0, npad - r0, npad - r0, r0);
       TRY(launched(c, "cholesky"));
-    }
-  }
-  if (!async) {
-    int flag = 0;
-    HIP_TRY(c, hipMemcpyAsync(&flag, b.flag, sizeof(int), hipMemcpyDeviceToHost, st));
-    HIP_TRY(c, hipStreamSynchronize(st));
-    if (flag != 0) {
-      c->pivot = flag - 1;
-      c->have_inv = false;
-      return fail(c, CPM_ENOTPD, "elastance matrix not positive definite at pivot %d", c->pivot);
     }
   }
   if (factor) {
@@ -1750,38 +1729,6 @@ cpm_status cpm_invert(cpm_ctx* c, unsigned store_flags) {
     TRY(factor_response(c, st));
     c->store = CPM_STORE_F64;
   } else {
-    // X = L^-1 by blocked forward substitution (X stored in Ainv's buffer
-    // first), grouped like the factorisation: row blocks of 64 inside blocks
-    // of OB rows, the rows below a block updated by one rank-OB product
-    double* X = b.Ainv;
-    launch_set_identity(st, npad, X);
-    for (int K0 = 0; K0 < npad; K0 += OB) {
-      const int kend = std::min(npad, K0 + OB);
-      for (int k0 = K0; k0 < kend; k0 += TILE) {
-        const int kb = k0 / TILE, cols = k0 + TILE, rin = kend - k0 - TILE;
-        double* Xk = X + (size_t)k0 * npad;
-        Timed t(c, "trtri", st);
-        // X_k = L_kk^-1 X_k on the columns that can be non-zero
-        launch_gemm_f64(st, false, false, TILE, cols, TILE, 1.0, b.Dinv + (size_t)kb * TILE * TILE,
-                        TILE, Xk, npad, 0.0, Xk, npad, 0, 0);
-        if (rin > 0) {
-          // the block's rows below: X_i -= L_ik X_k
-          launch_gemm_f64(st, false, false, rin, cols, TILE, -1.0,
-                          b.L + (size_t)(k0 + TILE) * npad + k0, npad, Xk, npad, 1.0,
-                          X + (size_t)(k0 + TILE) * npad, npad, 0, 0);
-        }
-        TRY(launched(c, "trtri"));
-      }
-      const int rest = npad - kend;
-      if (rest > 0) {
-        // every row below the block: X_below -= L_below,block X_block (columns < kend)
-        Timed t(c, "trtri", st);
-        launch_gemm_f64(st, false, false, rest, kend, kend - K0, -1.0,
-                        b.L + (size_t)kend * npad + K0, npad, X + (size_t)K0 * npad, npad, 1.0,
-                        X + (size_t)kend * npad, npad, 0, 0);
-        TRY(launched(c, "trtri"));
-      }
-    }
     // A^-1 = X^T X (lower tiles, k from max(row, col)), result into L's buffer,
     // then swap names so Ainv holds A^-1
     { Timed t(c, "lauum", st);
@@ -1801,8 +1748,19 @@ cpm_status cpm_invert(cpm_ctx* c, unsigned store_flags) {
     c->have_inv = true;
     return CPM_OK;
   }
-  HIP_TRY(c, hipMemcpyAsync(&c->s_sum, b.scal, sizeof(double), hipMemcpyDeviceToHost, st));
+  int flag = 0;
+  double s_sum = 0.0;
+  HIP_TRY(c, hipMemcpyAsync(&flag, b.flag, sizeof(int), hipMemcpyDeviceToHost, st));
+  HIP_TRY(c, hipMemcpyAsync(&s_sum, b.scal, sizeof(double), hipMemcpyDeviceToHost, st));
   HIP_TRY(c, hipStreamSynchronize(st));
+  if (flag != 0) {
+    c->pivot = flag - 1;
+    c->have_inv = c->factor_only = false;
+    c->store = store_before;
+    c->have_q = have_q_before;
+    return fail(c, CPM_ENOTPD, "elastance matrix not positive definite at pivot %d", c->pivot);
+  }
+  c->s_sum = s_sum;
   c->have_inv = true;
   return CPM_OK;
 }

@@ -457,6 +457,13 @@ void launch_gemm_f64(hipStream_t st, bool transA, bool transB, int M, int N, int
 // less it runs unsplit.  Only untransposed, full products are split.
 size_t gemm_f64_work(int M, int N, int K);
 void launch_potrf_diag(hipStream_t st, double* Lblk, int ld, double* Dinv, int* flag, int k0);
+// steps of A = L L^T and X = L^-1 (X null: the factor alone); Dinv: L_kk^-1 of the
+// panel at k0, and of the block after the update, which that launch factors.  update:
+// by columns c0 .. c0 + K - 1, L's next `cols` columns and X's next rowsX rows in the
+// columns below colsX (multiples of 64)
+void launch_chol_solve(hipStream_t st, int npad, double* L, double* X, const double* Dinv, int k0);
+void launch_chol_update(hipStream_t st, int npad, double* L, double* X, double* Dinv, int* flag,
+                        int c0, int K, int cols, int rowsX, int colsX);
 void launch_set_identity(hipStream_t st, int npad, double* X);
 void launch_row_sums(hipStream_t st, int n, int npad, const double* M, double* out);
 void launch_sum_vector(hipStream_t st, int n, const double* v, double* out);

@@ -52,29 +52,13 @@ typedef double d2v __attribute__((ext_vector_type(2)));
 // LDS pitch (16 rows of a read on distinct banks); doubles of a split tile; runs
 constexpr int GT_P = 18, GT_PART = 128 * 128, GT_LRUNS = 8, GT_RUNS = 1 << GT_LRUNS;
 
-// The tiles in row-major order (tri: those on and below the diagonal), each a run
-// of K slabs (kmode: from its own first row).
+// The tiles in row-major order (tri: those on and below the diagonal); kmode: a
+// tile's K begins at its own first row.
 struct GtGeom {
-  int M, N, K, tri, kmode, T, tm, tn;
+  int M, N, K, tri, kmode, tm, tn;
   int total;                                         // slabs of all tiles (split)
-  __host__ __device__ int cols(int bm) const { return tri && bm + 1 < tn ? bm + 1 : tn; }
-  __host__ __device__ int kbeg(int bm) const { return kmode ? bm * T : 0; }
-  __host__ __device__ int slabs(int bm) const { return (K - kbeg(bm)) / 16; }
-  __host__ __device__ int tiles() const {
-    return tri ? tm * tn - tn * (tn - 1) / 2 : tm * tn;      // (tri: tm >= tn)
-  }
-  __host__ __device__ int begin(int w) const { return (int)((long)total * w >> GT_LRUNS); }
-  // the tile and slab of position `it` in the concatenation of all tiles
-  __host__ __device__ void locate(int it, int& bm, int& bn, int& s) const {
-    for (bm = 0;; ++bm) {
-      const int in_row = cols(bm) * slabs(bm);
-      if (it < in_row) break;
-      it -= in_row;
-    }
-    bn = it / slabs(bm);
-    s = it - bn * slabs(bm);
-  }
-  // tile w
+  __device__ int kbeg(int bm) const { return kmode ? bm * 64 : 0; }
+  int tiles() const { return tri ? tm * tn - tn * (tn - 1) / 2 : tm * tn; }   // (tri: tm >= tn)
   __device__ void tile(int w, int& bm, int& bn) const {
     const int head = tn * (tn - 1) / 2;              // tiles of the rows 0 .. tn - 2
     if (tri && w < head) {                           // row bm holds bm + 1 tiles
@@ -89,6 +73,14 @@ struct GtGeom {
       if (tri) bm += tn - 1;
     }
   }
+  // split: the first slab of run w, and the tile and slab of a position in all slabs
+  __device__ int begin(int w) const { return (int)((long)total * w >> GT_LRUNS); }
+  __device__ void locate(int it, int& bm, int& bn, int& s) const {
+    const int t = it / (K / 16);
+    bm = t / tn;
+    bn = t - bm * tn;
+    s = it - t * (K / 16);
+  }
 };
 
 template <int T>
@@ -97,127 +89,192 @@ struct GtWave {                                      // this thread's part of a 
   static constexpr int WC = T / 32;                  // waves side by side
   static __device__ int wm() { return (int)(threadIdx.x >> 6) / WC * (16 * BI); }
   static __device__ int wn() { return (int)(threadIdx.x >> 6) % WC * 32; }
-  // output row of register r of block row i (-1: none) and column of block column j
-  static __device__ int row(int i, int r, int m0, int M, const int* rowmap) {
-    const int row = m0 + wm() + 16 * i + (int)((threadIdx.x & 63) >> 4) + 4 * r;
-    if (row >= M) return -1;
-    return rowmap ? rowmap[row] : row;               // scattered output rows (-1: skip)
-  }
-  static __device__ int col(int j, int n0) { return n0 + wn() + 16 * j + (int)(threadIdx.x & 15); }
+  // tile row of register r of block row i and tile column of block column j
+  static __device__ int row(int i, int r) { return wm() + 16 * i + (int)((threadIdx.x & 63) >> 4) + 4 * r; }
+  static __device__ int col(int j) { return wn() + 16 * j + (int)(threadIdx.x & 15); }
 };
 
-template <int T, bool SPLIT, bool TA, bool TB>
-__global__ void __launch_bounds__(4 * T, 4) k_gemm_f64(GtGeom g, double alpha,
-                                                       const double* __restrict__ A, int lda,
-                                                       const double* __restrict__ B, int ldb,
-                                                       double beta, double* C, int ldc,
-                                                       const int* __restrict__ rowmap,
-                                                       double* __restrict__ part) {
-  using W = GtWave<T>;
-  __shared__ __align__(16) double sA[2][T][GT_P];
-  __shared__ __align__(16) double sB[2][T][GT_P];
-  int bm, bn, s0 = 0, it, end, w;
-  if (SPLIT) {
-    // workgroups of one XCD (every eighth) take neighbouring runs
-    w = (int)(blockIdx.x & 7) * (GT_RUNS / 8) + (int)(blockIdx.x >> 3);
-    it = g.begin(w);
-    end = g.begin(w + 1);
-    if (it >= end) return;
-    g.locate(it, bm, bn, s0);
-  } else {
-    w = blockIdx.x;
-    g.tile(w, bm, bn);
-    it = 0;
-    end = g.slabs(bm);
+// one operand's slabs: a thread moves a row and 4 k (row-major operand) or a k and 4
+// rows (k-major one); rows past the operand's last are its last
+template <bool KMAJOR>
+struct GtLoader {
+  const double* p;
+  d2v x, y;
+  __device__ void start(const double* M, int ld, int row0, int rows, int k) {
+    const int tid = threadIdx.x;
+    p = KMAJOR ? M + (size_t)(k + (tid & 15)) * ld + min(row0 + (tid >> 4) * 4, rows - 4)
+               : M + (size_t)min(row0 + (tid >> 2), rows - 1) * ld + k + (tid & 3) * 4;
   }
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wm = W::wm(), wn = W::wn(), l15 = lane & 15, lg = lane >> 4;
-  // loader: a row and 4 k (row-major operand) or a k and 4 rows (k-major one)
-  const int rr = tid >> 2, rk = (tid & 3) * 4, kk = tid & 15, kr = (tid >> 4) * 4;
-  const double *pa, *pb;
-  auto start = [&](int m, int n, int k) {
-    pa = TA ? A + (size_t)(k + kk) * lda + min(m * T + kr, g.M - 4)
-            : A + (size_t)min(m * T + rr, g.M - 1) * lda + k + rk;
-    pb = TB ? B + (size_t)min(n * T + rr, g.N - 1) * ldb + k + rk
-            : B + (size_t)(k + kk) * ldb + min(n * T + kr, g.N - 4);
-  };
-  d2v a0, a1, b0, b1;
-  auto load = [&]() {
-    const d2v *qa = reinterpret_cast<const d2v*>(pa), *qb = reinterpret_cast<const d2v*>(pb);
-    a0 = qa[0]; a1 = qa[1];
-    b0 = qb[0]; b1 = qb[1];
-  };
-  auto store = [&](int buf) {
-    if (TA) {
-      sA[buf][kr][kk] = a0.x; sA[buf][kr + 1][kk] = a0.y;
-      sA[buf][kr + 2][kk] = a1.x; sA[buf][kr + 3][kk] = a1.y;
+  __device__ void next(int ld) { p += KMAJOR ? (size_t)16 * ld : 16; }
+  __device__ void load() {
+    const d2v* q = reinterpret_cast<const d2v*>(p);
+    x = q[0];
+    y = q[1];
+  }
+  __device__ void store(double (*s)[GT_P]) const {
+    const int tid = threadIdx.x;
+    if (KMAJOR) {
+      const int kk = tid & 15, r = (tid >> 4) * 4;
+      s[r][kk] = x.x; s[r + 1][kk] = x.y;
+      s[r + 2][kk] = y.x; s[r + 3][kk] = y.y;
     } else {
-      *reinterpret_cast<d2v*>(&sA[buf][rr][rk]) = a0;
-      *reinterpret_cast<d2v*>(&sA[buf][rr][rk + 2]) = a1;
+      double* d = &s[tid >> 2][(tid & 3) * 4];
+      *reinterpret_cast<d2v*>(d) = x;
+      *reinterpret_cast<d2v*>(d + 2) = y;
     }
-    if (TB) {
-      *reinterpret_cast<d2v*>(&sB[buf][rr][rk]) = b0;
-      *reinterpret_cast<d2v*>(&sB[buf][rr][rk + 2]) = b1;
-    } else {
-      sB[buf][kr][kk] = b0.x; sB[buf][kr + 1][kk] = b0.y;
-      sB[buf][kr + 2][kk] = b1.x; sB[buf][kr + 3][kk] = b1.y;
-    }
-  };
-  start(bm, bn, g.kbeg(bm) + 16 * s0);
-  load();
-  store(0);
+  }
+};
+
+// acc += one slab's product
+template <int T>
+__device__ inline void gt_slab(const double (*sA)[GT_P], const double (*sB)[GT_P],
+                               v4d (&acc)[GtWave<T>::BI][GtWave<T>::BJ]) {
+  using W = GtWave<T>;
+  const int l15 = threadIdx.x & 15, lg = (threadIdx.x & 63) >> 4, wm = W::wm(), wn = W::wn();
+#pragma unroll
+  for (int h = 0; h < 4; ++h) {
+    double a[W::BI], b[W::BJ];
+#pragma unroll
+    for (int i = 0; i < W::BI; ++i) a[i] = sA[wm + 16 * i + l15][4 * h + lg];
+#pragma unroll
+    for (int j = 0; j < W::BJ; ++j) b[j] = sB[wn + 16 * j + l15][4 * h + lg];
+#pragma unroll
+    for (int i = 0; i < W::BI; ++i)
+#pragma unroll
+      for (int j = 0; j < W::BJ; ++j)
+        acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], b[j], acc[i][j], 0, 0, 0);
+  }
+}
+
+constexpr int GT_LDS64 = 2 * 2 * 64 * GT_P;          // doubles of LDS of a 64-tile
+
+// one 64 x 64 tile by 256 threads: C = beta C + alpha A B over slabs of 16 k; A, B
+// and C at the tile's first row, column and k; rowmap: C's rows (-1: none)
+template <bool TA, bool TB>
+__device__ __forceinline__ void gemm_tile64(double* lds, const double* A, int lda, const double* B, int ldb,
+                                   int K, double alpha, double beta, double* C, int ldc,
+                                   const int* rowmap) {
+  using W = GtWave<64>;
+  auto sA = reinterpret_cast<double (*)[64][GT_P]>(lds);
+  auto sB = sA + 2;
+  GtLoader<TA> la;
+  GtLoader<!TB> lb;
+  la.start(A, lda, 0, 64, 0);
+  lb.start(B, ldb, 0, 64, 0);
+  la.load();
+  lb.load();
+  la.store(sA[0]);
+  lb.store(sB[0]);
   __syncthreads();
+  v4d acc[W::BI][W::BJ];
+#pragma unroll
+  for (int i = 0; i < W::BI; ++i)
+#pragma unroll
+    for (int j = 0; j < W::BJ; ++j) acc[i][j] = (v4d){0.0, 0.0, 0.0, 0.0};
   int buf = 0;
-  while (it < end) {
-    v4d acc[W::BI][W::BJ];
-    int nm = bm, nn = bn + 1, ns = end - it;         // the next tile
-    if (SPLIT) {
-      ns = min(g.slabs(bm) - s0, ns);
-      if (nn == g.cols(bm)) {
-        nn = 0;
-        ++nm;
+  for (int k = 0; k < K; k += 16) {
+    if (k + 16 < K) {                                // (the last slab loads itself again)
+      la.next(lda);
+      lb.next(ldb);
+    }
+    la.load();
+    lb.load();
+    gt_slab<64>(sA[buf], sB[buf], acc);
+    la.store(sA[buf ^ 1]);
+    lb.store(sB[buf ^ 1]);
+    __syncthreads();
+    buf ^= 1;
+  }
+#pragma unroll
+  for (int i = 0; i < W::BI; ++i)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      int row = W::row(i, r);
+      if (rowmap) {                                  // scattered output rows (-1: skip)
+        row = rowmap[row];
+        if (row < 0) continue;
+      }
+#pragma unroll
+      for (int j = 0; j < W::BJ; ++j) {
+        double* cp = C + (size_t)row * ldc + W::col(j);
+        const double v = alpha * acc[i][j][r];
+        *cp = (beta != 0.0) ? v + beta * (*cp) : v;
       }
     }
+}
+
+template <bool TA, bool TB>
+__global__ void __launch_bounds__(256, 4) k_gemm_f64(GtGeom g, double alpha,
+                                                     const double* __restrict__ A, int lda,
+                                                     const double* __restrict__ B, int ldb,
+                                                     double beta, double* C, int ldc,
+                                                     const int* __restrict__ rowmap) {
+  __shared__ __align__(16) double lds[GT_LDS64];
+  int bm, bn;
+  g.tile(blockIdx.x, bm, bn);
+  const size_t m0 = 64 * bm, n0 = 64 * bn, k0 = g.kbeg(bm);
+  gemm_tile64<TA, TB>(lds, TA ? A + k0 * lda + m0 : A + m0 * lda + k0, lda,
+                      TB ? B + n0 * ldb + k0 : B + k0 * ldb + n0, ldb, g.K - (int)k0, alpha, beta,
+                      C + (rowmap ? 0 : m0 * ldc) + n0, ldc, rowmap ? rowmap + m0 : nullptr);
+}
+
+__global__ void __launch_bounds__(512, 4) k_gemm_f64_split(GtGeom g, double alpha,
+                                                           const double* __restrict__ A, int lda,
+                                                           const double* __restrict__ B, int ldb,
+                                                           double beta, double* C, int ldc,
+                                                           double* __restrict__ part) {
+  using W = GtWave<128>;
+  __shared__ __align__(16) double sA[2][128][GT_P];
+  __shared__ __align__(16) double sB[2][128][GT_P];
+  // workgroups of one XCD (every eighth) take neighbouring runs
+  const int w = (int)(blockIdx.x & 7) * (GT_RUNS / 8) + (int)(blockIdx.x >> 3), end = g.begin(w + 1);
+  int it = g.begin(w), bm, bn, s0, buf = 0;
+  if (it >= end) return;
+  g.locate(it, bm, bn, s0);
+  GtLoader<false> la;
+  GtLoader<true> lb;
+  la.start(A, lda, bm * 128, g.M, 16 * s0);
+  lb.start(B, ldb, bn * 128, g.N, 16 * s0);
+  la.load();
+  lb.load();
+  la.store(sA[0]);
+  lb.store(sB[0]);
+  __syncthreads();
+  while (it < end) {
+    const int ns = min(g.K / 16 - s0, end - it);
+    const int nn = bn + 1 < g.tn ? bn + 1 : 0, nm = nn ? bm : bm + 1;   // the next tile
     it += ns;
+    v4d acc[W::BI][W::BJ];
 #pragma unroll
     for (int i = 0; i < W::BI; ++i)
 #pragma unroll
       for (int j = 0; j < W::BJ; ++j) acc[i][j] = (v4d){0.0, 0.0, 0.0, 0.0};
     for (int s = 0; s < ns; ++s) {
       if (s + 1 < ns) {
-        pa += TA ? (size_t)16 * lda : 16;
-        pb += TB ? 16 : (size_t)16 * ldb;
-      } else if (SPLIT && it < end) {
-        start(nm, nn, g.kbeg(nm));
+        la.next(lda);
+        lb.next(ldb);
+      } else if (it < end) {
+        la.start(A, lda, nm * 128, g.M, 0);
+        lb.start(B, ldb, nn * 128, g.N, 0);
       }
-      load();                                        // (a run's last slab loads itself again)
-#pragma unroll
-      for (int h = 0; h < 4; ++h) {
-        double a[W::BI], b[W::BJ];
-#pragma unroll
-        for (int i = 0; i < W::BI; ++i) a[i] = sA[buf][wm + 16 * i + l15][4 * h + lg];
-#pragma unroll
-        for (int j = 0; j < W::BJ; ++j) b[j] = sB[buf][wn + 16 * j + l15][4 * h + lg];
-#pragma unroll
-        for (int i = 0; i < W::BI; ++i)
-#pragma unroll
-          for (int j = 0; j < W::BJ; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], b[j], acc[i][j], 0, 0, 0);
-      }
-      store(buf ^ 1);
+      la.load();                                     // (a run's last slab loads itself again)
+      lb.load();
+      gt_slab<128>(sA[buf], sB[buf], acc);
+      la.store(sA[buf ^ 1]);
+      lb.store(sB[buf ^ 1]);
       __syncthreads();
       buf ^= 1;
     }
-    if (!SPLIT || s0 == 0) {
+    if (s0 == 0) {
 #pragma unroll
       for (int i = 0; i < W::BI; ++i)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          const int row = W::row(i, r, bm * T, g.M, rowmap);
-          if (row < 0) continue;
+          const int row = bm * 128 + W::row(i, r);
+          if (row >= g.M) continue;
 #pragma unroll
           for (int j = 0; j < W::BJ; ++j) {
-            const int col = W::col(j, bn * T);
+            const int col = bn * 128 + W::col(j);
             if (col >= g.N) continue;
             double* cp = C + (size_t)row * ldc + col;
             const double v = alpha * acc[i][j][r];
@@ -225,7 +282,7 @@ __global__ void __launch_bounds__(4 * T, 4) k_gemm_f64(GtGeom g, double alpha,
           }
         }
     } else {                                         // at most the run's first tile
-      unsigned o = w * GT_PART + tid;
+      unsigned o = w * GT_PART + threadIdx.x;
       asm("" : "+v"(o));                             // (keeps 32 addresses out of the slab loop)
 #pragma unroll
       for (int i = 0; i < W::BI; ++i)
@@ -243,7 +300,6 @@ __global__ void __launch_bounds__(4 * T, 4) k_gemm_f64(GtGeom g, double alpha,
 // C += alpha (the later K parts of a tile, in order of k); blockIdx.x = the run
 // that holds the tile's second part, blockIdx.y = MFMA block row
 __global__ void __launch_bounds__(512) k_gemm_f64_join(GtGeom g, double alpha, double* C, int ldc,
-                                                       const int* __restrict__ rowmap,
                                                        const double* __restrict__ part) {
   using W = GtWave<128>;
   const int w = blockIdx.x + 1, i = blockIdx.y;
@@ -252,7 +308,7 @@ __global__ void __launch_bounds__(512) k_gemm_f64_join(GtGeom g, double alpha, d
   int bm, bn, s;
   g.locate(it, bm, bn, s);
   if (s == 0 || g.begin(w - 1) > it - s) return;     // a tile's start, or a third part
-  const int tend = it - s + g.slabs(bm);
+  const int tend = it - s + g.K / 16;
   v4d acc[2] = {(v4d){0.0, 0.0, 0.0, 0.0}, (v4d){0.0, 0.0, 0.0, 0.0}};
   for (int v = w; v < GT_RUNS && g.begin(v) < tend; ++v) {
     if (g.begin(v) == g.begin(v + 1)) continue;
@@ -264,11 +320,11 @@ __global__ void __launch_bounds__(512) k_gemm_f64_join(GtGeom g, double alpha, d
   }
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
-    const int row = W::row(i, r, bm * 128, g.M, rowmap);
-    if (row < 0) continue;
+    const int row = bm * 128 + W::row(i, r);
+    if (row >= g.M) continue;
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
-      const int col = W::col(j, bn * 128);
+      const int col = bn * 128 + W::col(j);
       if (col < g.N) C[(size_t)row * ldc + col] += alpha * acc[j][r];
     }
   }
@@ -290,19 +346,19 @@ void launch_gemm_f64(hipStream_t st, bool transA, bool transB, int M, int N, int
                      int ldc, int tri, int kmode, const int* rowmap, GemmWork work) {
   if (M <= 0 || N <= 0) return;
   const size_t need = gemm_f64_work(M, N, K);
-  if (need > 0 && work.len >= need && !transA && !transB && !tri && !kmode) {
-    const GtGeom g{M, N, K, 0, 0, 128, (M + 127) / 128, (N + 127) / 128,
+  if (need > 0 && work.len >= need && !transA && !transB && !tri && !kmode && !rowmap) {
+    const GtGeom g{M, N, K, 0, 0, (M + 127) / 128, (N + 127) / 128,
                    ((M + 127) / 128) * ((N + 127) / 128) * (K / 16)};
-    hipLaunchKernelGGL((k_gemm_f64<128, true, false, false>), dim3(GT_RUNS), dim3(512), 0, st, g,
-                       alpha, A, lda, B, ldb, beta, C, ldc, rowmap, work.p);
+    hipLaunchKernelGGL(k_gemm_f64_split, dim3(GT_RUNS), dim3(512), 0, st, g, alpha, A, lda, B, ldb,
+                       beta, C, ldc, work.p);
     hipLaunchKernelGGL(k_gemm_f64_join, dim3(GT_RUNS - 1, 4), dim3(512), 0, st, g, alpha, C, ldc,
-                       rowmap, work.p);
+                       work.p);
     return;
   }
-  const GtGeom g{M, N, K, tri, kmode, 64, M / 64, N / 64, 0};
+  const GtGeom g{M, N, K, tri, kmode, M / 64, N / 64, 0};
 #define CPM_GT(TA, TB)                                                                              \
-  hipLaunchKernelGGL((k_gemm_f64<64, false, TA, TB>), dim3(g.tiles()), dim3(256), 0, st, g, alpha, A, \
-                     lda, B, ldb, beta, C, ldc, rowmap, nullptr)
+  hipLaunchKernelGGL((k_gemm_f64<TA, TB>), dim3(g.tiles()), dim3(256), 0, st, g, alpha, A, lda, B,  \
+                     ldb, beta, C, ldc, rowmap)
   if (transA) {
     if (transB) CPM_GT(true, true); else CPM_GT(true, false);
   } else {
@@ -325,7 +381,7 @@ void launch_gemm_f64(hipStream_t st, bool transA, bool transB, int M, int N, int
 // A pivot <= 0 (or NaN) records 1 + its global index in *flag (first one wins) and
 // continues with 1.
 // 34.5 us in one workgroup of 16 waves with the root and a division in the chain and
-// the inverse afterwards; now 12.4: 1.0 us loads, 2.0 per panel (330 clocks per column
+// the inverse afterwards; alone now 12.4: 1.0 us loads, 2.0 per panel (330 clocks per column
 // before the LDS reads of its entries were moved behind the next root, 290 after),
 // 0.3-0.6 for the columns right of it, 1.8 for what of the inverse needs the last
 // panel.
@@ -358,7 +414,7 @@ __device__ inline void root_and_reciprocal(double x, double& d, double& rd) {
 // panel p0 of the block in LDS, by one wave; FAST: by root_and_reciprocal; false if
 // that is not exact for a pivot (the block is as before then, bc and rd are not)
 template <bool FAST>
-__device__ inline bool potrf_panel(double (*a)[65], double* bc, double* rd, int p0, int lane, int* flag,
+__device__ __forceinline__ bool potrf_panel(double (*a)[65], double* bc, double* rd, int p0, int lane, int* flag,
                                    int k0) {
   double v[16], lc[16], dl = 1.0;          // lc: column j's entries in the panel
 #pragma unroll
@@ -407,8 +463,8 @@ __device__ inline bool potrf_panel(double (*a)[65], double* bc, double* rd, int 
 
 // X = the inverse of L's diagonal block at p0 by forward substitution, a lane per
 // column (one wave); entries above the diagonal come out as zero
-__device__ inline void invert16(const double (*a)[65], const double* rd, int p0, int lane,
-                                double (*X)[17]) {
+__device__ __forceinline__ void invert16(const double (*a)[65], const double* rd, int p0, int lane,
+                                double* X) {
   if (lane < 16) {
     double s[16];
 #pragma unroll
@@ -420,30 +476,32 @@ __device__ inline void invert16(const double (*a)[65], const double* rd, int p0,
       for (int r = t + 1; r < 16; ++r) s[r] -= a[p0 + r][p0 + t] * s[t];
     }
 #pragma unroll
-    for (int r = 0; r < 16; ++r) X[r][lane] = s[r];
+    for (int r = 0; r < 16; ++r) X[r * 65 + lane] = s[r];
   }
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 }
 
-// acc + L x: L 16 x 16 in LDS (pitch P), x and acc in MFMA registers (register h of
+// acc + L x: L 16 x 16 in LDS (pitch 65), x and acc in MFMA registers (register h of
 // a result is the right operand of the next product's k = 4 h .. 4 h + 3)
-template <int P>
 __device__ inline v4d mul16(const double* L, v4d x, v4d acc, int lane) {
 #pragma unroll
   for (int h = 0; h < 4; ++h)
-    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(L[(lane & 15) * P + 4 * h + (lane >> 4)], x[h], acc, 0,
+    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(L[(lane & 15) * 65 + 4 * h + (lane >> 4)], x[h], acc, 0,
                                                0, 0);
   return acc;
 }
 
-__global__ void __launch_bounds__(256) k_potrf_diag(double* Lblk, int ld, double* Dinv, int* flag,
-                                                    int k0) {
-  __shared__ double a[64][65];      // working lower triangle, becomes L (above: anything)
-  __shared__ double Xd[4][16][17];  // inverses of L's diagonal 16 x 16 blocks
-  __shared__ double rd[64];         // 1 / L[j][j]
-  __shared__ __align__(16) double bc[64];   // a column of L
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int l15 = lane & 15, lg = lane >> 4, k = wave - 1;
+// the block and its inverse by 256 threads; lds: PF_LDS doubles
+constexpr int PF_LDS = 64 * 65 + 64 + 64;
+
+__device__ __forceinline__ void potrf64(double* lds, double* Lblk, int ld, double* Dinv, int* flag, int k0) {
+  auto a = reinterpret_cast<double (*)[65]>(lds);   // working lower triangle, becomes L
+  double* bc = lds + 64 * 65;                       // a column of L (16-byte aligned)
+  double* rd = bc + 64;                             // 1 / L[j][j]
+  // the inverses of L's diagonal 16 x 16 blocks, above the block diagonal of a
+  auto Xd = [&](int p) { return p < 3 ? &a[0][16 * p + 16] : &a[16][48]; };
+  const int wave = threadIdx.x >> 6, k = wave - 1;
+  int lane = threadIdx.x & 63, l15 = lane & 15, lg = lane >> 4;
   {
     double t[16];                   // all loads in flight at once
 #pragma unroll
@@ -465,24 +523,27 @@ __global__ void __launch_bounds__(256) k_potrf_diag(double* Lblk, int ld, double
   auto diag = [&](int p) {
     v4d y;
 #pragma unroll
-    for (int r = 0; r < 4; ++r) y[r] = Xd[p][lg + 4 * r][l15];
+    for (int r = 0; r < 4; ++r) y[r] = Xd(p)[(lg + 4 * r) * 65 + l15];
     return y;
   };
 #pragma unroll 1
   for (int p = 0; p < 4; ++p) {
     const int p0 = 16 * p;
+    asm("" : "+v"(lane));           // (keeps what follows from it out of registers between panels)
+    l15 = lane & 15;
+    lg = lane >> 4;
     if (wave == 0) {
       if (!potrf_panel<true>(a, bc, rd, p0, lane, flag, k0))
         potrf_panel<false>(a, bc, rd, p0, lane, flag, k0);
     } else if (p > 0) {
       // meanwhile: block row p - 1 of the inverse, by each wave its column k, from
       // the same inverse of the diagonal block
-      invert16(a, rd, p0 - 16, lane, Xd[p - 1]);
+      invert16(a, rd, p0 - 16, lane, Xd(p - 1));
       if (k <= p - 1) {
-        const v4d y = k == p - 1 ? diag(p - 1) : -mul16<17>(&Xd[p - 1][0][0], t0, zero, lane);
-        t0 = mul16<65>(&a[p0][p0 - 16], y, t1, lane);
-        if (p < 3) t1 = mul16<65>(&a[p0 + 16][p0 - 16], y, t2, lane);
-        if (p < 2) t2 = mul16<65>(&a[p0 + 32][p0 - 16], y, t3, lane);
+        const v4d y = k == p - 1 ? diag(p - 1) : -mul16(Xd(p - 1), t0, zero, lane);
+        t0 = mul16(&a[p0][p0 - 16], y, t1, lane);
+        if (p < 3) t1 = mul16(&a[p0 + 16][p0 - 16], y, t2, lane);
+        if (p < 2) t2 = mul16(&a[p0 + 32][p0 - 16], y, t3, lane);
         put(p - 1, k, y);
       } else {
         put(p - 1, k, zero);
@@ -508,17 +569,89 @@ __global__ void __launch_bounds__(256) k_potrf_diag(double* Lblk, int ld, double
     if (p < 3) __syncthreads();
   }
   if (wave > 0) put_L(3);
-  invert16(a, rd, 48, lane, Xd[3]);                    // (each wave the same values)
+  invert16(a, rd, 48, lane, Xd(3));                    // (each wave the same values)
   if (wave > 0) {
-    put(3, k, -mul16<17>(&Xd[3][0][0], t0, zero, lane));
+    put(3, k, -mul16(Xd(3), t0, zero, lane));
   } else {
     put(3, 3, diag(3));
     for (int i = 0; i < 3; ++i) put(i, 3, zero);
   }
 }
 
+static_assert(PF_LDS <= GT_LDS64, "the block factors in the GEMM's LDS");
+
+__global__ void __launch_bounds__(256) k_potrf_diag(double* Lblk, int ld, double* Dinv, int* flag,
+                                                    int k0) {
+  __shared__ __align__(16) double lds[PF_LDS];
+  potrf64(lds, Lblk, ld, Dinv, flag, k0);
+}
+
 void launch_potrf_diag(hipStream_t st, double* Lblk, int ld, double* Dinv, int* flag, int k0) {
   hipLaunchKernelGGL(k_potrf_diag, dim3(1), dim3(256), 0, st, Lblk, ld, Dinv, flag, k0);
+}
+
+// ---------------------------------------------------------------------------
+// The steps of the factorisation A = L L^T and, in the same launches, of X = L^-1 by
+// forward substitution (X null: the factor alone).  A panel is 64 columns; r = the
+// first row below it.
+//   solve:  L_below <- L_below L_kk^-T, X_k <- L_kk^-1 X_k (columns that can be
+//           non-zero), in place, a tile per workgroup.
+//   update: L's tiles right of column c0 + K -= L L^T, rows of X below -= L X_c0.., by
+//           the K columns from c0 on; the workgroup of the first tile, the next
+//           diagonal block, then factors it while the others go on.
+// Launches follow one another through the chain of diagonal blocks, so what is merged
+// is hidden behind it: a panel at 2880 atoms took 51 us (block 12.4, solve and update
+// of L 7.5 + 12, of X 7.2 + 12.5) and takes 30 (6.2 + 24, of which the first tile and
+// its factor are the longest part).  The block factors in the GEMM's LDS and 128
+// registers, so that four workgroups still share a CU in the large updates.
+// ---------------------------------------------------------------------------
+__global__ void __launch_bounds__(256, 4) k_chol_solve(double* L, double* X, const double* Dinv,
+                                                       int ld, int k0, int nL) {
+  __shared__ __align__(16) double lds[GT_LDS64];
+  const int b = blockIdx.x;
+  if (b < nL) {
+    double* C = L + (size_t)(k0 + 64 + 64 * b) * ld + k0;
+    gemm_tile64<false, true>(lds, C, ld, Dinv, 64, 64, 1.0, 0.0, C, ld, nullptr);
+  } else {
+    double* C = X + (size_t)k0 * ld + 64 * (b - nL);
+    gemm_tile64<false, false>(lds, Dinv, 64, C, ld, 64, 1.0, 0.0, C, ld, nullptr);
+  }
+}
+
+__global__ void __launch_bounds__(256, 4) k_chol_update(GtGeom g, double* L, double* X, double* Dinv,
+                                                        int* flag, int ld, int c0, int ncX) {
+  __shared__ __align__(16) double lds[GT_LDS64];
+  const int nL = g.tm * g.tn - g.tn * (g.tn - 1) / 2, b = blockIdx.x, r0 = c0 + g.K;
+  if (b < nL) {
+    int bm, bn;
+    g.tile(b, bm, bn);
+    const size_t m = r0 + 64 * bm, n = r0 + 64 * bn;
+    gemm_tile64<false, true>(lds, L + m * ld + c0, ld, L + n * ld + c0, ld, g.K, -1.0, 1.0,
+                             L + m * ld + n, ld, nullptr);
+    if (b == 0) {
+      __syncthreads();
+      potrf64(lds, L + m * ld + n, ld, Dinv, flag, r0);
+    }
+  } else {
+    const size_t m = r0 + 64 * ((b - nL) / ncX), n = 64 * ((b - nL) % ncX);
+    gemm_tile64<false, false>(lds, L + m * ld + c0, ld, X + (size_t)c0 * ld + n, ld, g.K, -1.0, 1.0,
+                              X + m * ld + n, ld, nullptr);
+  }
+}
+
+void launch_chol_solve(hipStream_t st, int npad, double* L, double* X, const double* Dinv, int k0) {
+  const int nL = (npad - k0) / 64 - 1, nX = X ? k0 / 64 + 1 : 0;
+  if (nL + nX > 0)
+    hipLaunchKernelGGL(k_chol_solve, dim3(nL + nX), dim3(256), 0, st, L, X, Dinv, npad, k0, nL);
+}
+
+void launch_chol_update(hipStream_t st, int npad, double* L, double* X, double* Dinv, int* flag,
+                        int c0, int K, int cols, int rowsX, int colsX) {
+  const int r0 = c0 + K, tm = (npad - r0) / 64, tn = cols / 64;
+  const GtGeom g{npad - r0, cols, K, 1, 0, tm, tn, 0};
+  const int nX = X ? rowsX / 64 * (colsX / 64) : 0;
+  hipLaunchKernelGGL(k_chol_update, dim3(g.tiles() + nX), dim3(256), 0, st, g, L, X, Dinv, flag, npad,
+                     c0, colsX / 64);
 }
 
 __global__ void k_set_identity(int npad, double* X) {
