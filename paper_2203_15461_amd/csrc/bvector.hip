@@ -23,6 +23,7 @@
 #include <cstring>
 
 #include "cpm_internal.h"
+#include "rs_plane.hpp"
 
 namespace cpm {
 
@@ -1697,7 +1698,7 @@ void launch_gather_charges(hipStream_t st, int g, int m, int mpad64, const int* 
 // images.  g(r) comes from the LDS pair table, staged once per workgroup of
 // RS_WAVES waves.  The charges of the next three loaded blocks are in flight
 // while the current one is summed.
-constexpr int RS_WAVES = 8;
+constexpr int RS_WAVES = RP_WAVES;
 
 __global__ void __launch_bounds__(64 * RS_WAVES) k_real_space_b(
     int g, int n, int m, int mpad64, int sub, const int* __restrict__ amap, int nmap,
@@ -1939,247 +1940,35 @@ void pair_poly_table(double alpha, double eta, double rc, std::vector<double>& t
   }
 }
 
-// One wave per 64 atom-map slots of one z plane (slot tiles are compact in
-// x and y).  The charges of a chunk arrive 64 at a time (z-sorted blocks; a
-// block whose z range misses [z_p - rc, z_p + rc] is skipped unread).  A
-// charge within rc of the plane in z is taken relative to the tile centre,
-// in each image that can come within rc of the tile's bounding box (x, y
-// shifted by at most one cell length; MULTI, for cells shorter than 2 rc: every
-// x and y image in reach; the general kernel tries all of them for every atom,
-// 150 us against 19 us for one configuration of 288 atoms and 100 charges), and
-// appended to the wave's ring of 128 entries:
-//   FP32  (-2 dx, -2 dy) and W = dx^2 + dy^2 - (rc^2 - dz^2) - margin, so that
-//         an atom at (ax, ay) from the centre is within rc when
-//         ax (-2 dx) + ay (-2 dy) + W < -(ax^2 + ay^2)  (screen, margin
-//         above its rounding error);
-//   FP64  (dx, dy, dz^2, q) for the exact test and g.
-// Every 64 entries each lane screens them into a 64-bit mask and evaluates
-// the marked ones in FP64 (s < rc^2 exactly).  The summation order of an atom
-// is fixed by the data (deterministic).
-constexpr int RP_RING = 128;
-struct RpWave {
-  float2 c[RP_RING];
-  float w[RP_RING];
-  double4 d[RP_RING];
-};
-
 template <bool MULTI>
-__global__ void __launch_bounds__(64 * RS_WAVES, 4) k_real_space_plane(
-    int g, int n, int m, int mpad64, int sub, const int* __restrict__ amap, int nmap,
-    const double* __restrict__ ex, const double* __restrict__ ey, const double* __restrict__ ez,
-    const double4* __restrict__ cq, const double2* __restrict__ zr, double Lx, double Ly,
-    double Lz, double rc, const double* __restrict__ ptab, double* __restrict__ part) {
-  __shared__ __align__(16) double s_tab[RP_N * RP_REC];
-  __shared__ RpWave s_w[RS_WAVES];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int slot = blockIdx.x * blockDim.x + threadIdx.x;
-  const int atom = slot < nmap ? amap[slot] : -1;
-  const int chunk = blockIdx.y / sub, rchunks = gridDim.y / sub;
-  const bool mine = lane / (64 / sub) == (int)blockIdx.y % sub;   // this workgroup's part of a block
-  const int nb64 = mpad64 / 64, nbt = (m + 63) / 64;
-  for (int t = threadIdx.x; t < RP_N * RP_REC / 2; t += blockDim.x)
-    reinterpret_cast<double2*>(s_tab)[t] = reinterpret_cast<const double2*>(ptab)[t];
-  __syncthreads();
-  const unsigned long long valid_atoms = __ballot(atom >= 0);
-  if (!valid_atoms) return;                      // a wave of padding slots only
-  const double invLx = 1.0 / Lx, invLy = 1.0 / Ly, invLz = 1.0 / Lz, rc2 = rc * rc;
-  double xi = 0, yi = 0, zi = 0;
-  if (atom >= 0) { xi = ex[atom]; yi = ey[atom]; zi = ez[atom]; }
-  xi -= Lx * floor(xi * invLx);
-  yi -= Ly * floor(yi * invLy);
-  // the plane's z (every atom of the wave shares it) and the tile's box
-  const int first = __ffsll((long long)valid_atoms) - 1;
-  const double zp = __shfl(zi, first, 64);
-  double xlo = atom >= 0 ? xi : 1e300, xhi = atom >= 0 ? xi : -1e300;
-  double ylo = atom >= 0 ? yi : 1e300, yhi = atom >= 0 ? yi : -1e300;
-  for (int o = 32; o > 0; o >>= 1) {
-    xlo = fmin(xlo, __shfl_xor(xlo, o, 64));
-    xhi = fmax(xhi, __shfl_xor(xhi, o, 64));
-    ylo = fmin(ylo, __shfl_xor(ylo, o, 64));
-    yhi = fmax(yhi, __shfl_xor(yhi, o, 64));
-  }
-  const double cx = 0.5 * (xlo + xhi), cy = 0.5 * (ylo + yhi);
-  const double hx = 0.5 * (xhi - xlo), hy = 0.5 * (yhi - ylo);
-  const double ax = xi - cx, ay = yi - cy;
-  const float axf = (float)ax, ayf = (float)ay, nAf = -(float)(ax * ax + ay * ay);
-  // FP32 screen margin: its rounding error is below 50 u M^2 (u = 2^-24,
-  // M the largest coordinate magnitude, rc + the tile's half extent)
-  const double M = rc + fmax(hx, hy);
-  const double marg = 4e-6 * M * M;
-  RpWave& W = s_w[wave];
-  const float inv_hf = (float)(RP_N / rc);
-  const double hh = (rc / RP_N) * (rc / RP_N);   // s_mid of interval k: hh (k (k + 1) + 1/2)
-  const int nblk = chunk < nbt ? (nbt - chunk + rchunks - 1) / rchunks : 0;
-  const int s0 = blockIdx.z, sstep = gridDim.z;
-  const int nloc = s0 < g ? (g - s0 + sstep - 1) / sstep : 0;
-  const double wlo = zp - rc, whi = zp + rc;
-  // does block blk of configuration snap reach the plane's z window?
-  auto hit = [&](int snap, int blk) {
-    const double2 r = zr[(size_t)snap * nb64 + chunk + rchunks * blk];
-    const double a = r.x - Lz * floor((r.x - wlo) * invLz), w = r.y - r.x;
-    return a < whi + 1e-9 || a + w >= wlo + Lz - 1e-9;
-  };
-  auto fetch = [&](int snap, int blk) {
-    double4 v = make_double4(0, 0, 0, 0);
-    if (blk >= 0) {
-      const int j = (chunk + rchunks * blk) * 64 + lane;
-      if (j < m) v = cq[(size_t)snap * mpad64 + j];
-    }
-    return v;
-  };
-  // screen entries [base, base + len) of the ring and add the marked pairs
-  double acc = 0.0;
-  auto process = [&](int base, int len) {
-    if (atom >= 0) {
-      unsigned long long mk = 0ull;
-#pragma unroll 1
-      for (int q4 = 0; q4 < 64; q4 += 16) {
-        unsigned int mq = 0u;
-#pragma unroll
-        for (int t = 0; t < 16; ++t) {
-          const float2 c = W.c[base + q4 + t];
-          const float v = fmaf(axf, c.x, fmaf(ayf, c.y, W.w[base + q4 + t]));
-          mq |= (v < nAf) ? (1u << t) : 0u;
-        }
-        mk |= (unsigned long long)mq << q4;
-      }
-      if (len < 64) mk &= (1ull << len) - 1ull;
-      while (mk) {
-        const int t = __builtin_ctzll(mk);
-        mk &= mk - 1ull;
-        const double4 e = W.d[base + t];
-        const double rx = ax - e.x, ry = ay - e.y;
-        const double sv = fma(rx, rx, fma(ry, ry, e.z));
-        const float rf = __builtin_amdgcn_sqrtf((float)sv);   // picks the interval only
-        const int k = min((int)(rf * inv_hf), RP_N - 1);
-        const double* T = s_tab + k * RP_REC;
-        const double2 c01 = *reinterpret_cast<const double2*>(T);
-        const double2 c23 = *reinterpret_cast<const double2*>(T + 2);
-        const float4 c46 = *reinterpret_cast<const float4*>(T + 4);
-        const double x = sv - hh * ((double)k * (double)(k + 1) + 0.5);   // s - s_mid
-        const float xf = (float)x;
-        const float th = fmaf(fmaf(c46.z, xf, c46.y), xf, c46.x);       // a6 x^2 + a5 x + a4
-        double p = fma((double)th, x, c23.y);
-        p = fma(p, x, c23.x);
-        p = fma(p, x, c01.y);
-        p = fma(p, x, c01.x);
-        acc = fma(sv < rc2 ? e.w : 0.0, p, acc);
-      }
-    }
-    wave_lds_sync();                             // the ring's entries are reused next
-  };
-  // per configuration: the blocks that reach the window, found 64 at a time
-  // (one z-range load per lane, no load waits on another), then taken in
-  // order with the charges of the next two in flight
-  int head = 0, tail = 0;                        // ring window [head, tail), head in {0, 64}
-  for (int li = 0; li < nloc; ++li) {
-    const int snap = s0 + sstep * li;
-    for (int b0 = 0; b0 < nblk; b0 += 64) {
-      unsigned long long hm = __ballot(b0 + lane < nblk && hit(snap, b0 + lane));
-      auto pop = [&]() {
-        if (!hm) return -1;
-        const int t = __builtin_ctzll(hm);
-        hm &= hm - 1ull;
-        return b0 + t;
-      };
-      int bA = pop(), bB = pop();
-      double4 fA = fetch(snap, bA), fB = fetch(snap, bB);
-      while (bA >= 0) {
-        const int blk = bA;
-        const double4 cur = fA;
-        bA = bB;
-        fA = fB;
-        bB = pop();
-        fB = fetch(snap, bB);
-        const bool valid = mine && (chunk + rchunks * blk) * 64 + lane < m;
-        double dz = cur.z - zp;
-        dz -= Lz * rint(dz * invLz);
-        const double rho2 = rc2 - dz * dz;
-        double dx = cur.x - cx, dy = cur.y - cy;
-        dx -= Lx * rint(dx * invLx);
-        dy -= Ly * rint(dy * invLy);
-        // images whose distance from the tile's box can be below sqrt(rho2)
-        auto near = [&](double px, double py) {
-          const double ux = fmax(fabs(px) - hx, 0.0), uy = fmax(fabs(py) - hy, 0.0);
-          return ux * ux + uy * uy < rho2 + marg;
-        };
-        // append the lanes' images (has), then screen and sum full batches
-        auto append = [&](bool has, unsigned long long bal, double px, double py) {
-          if (has) {
-            const int pos = (tail + __popcll(bal & ((1ull << lane) - 1ull))) & (RP_RING - 1);
-            W.c[pos] = make_float2((float)(-2.0 * px), (float)(-2.0 * py));
-            W.w[pos] = (float)(px * px + py * py - rho2 - marg);
-            W.d[pos] = make_double4(px, py, dz * dz, cur.w);
-          }
-          tail += __popcll(bal);
-          wave_lds_sync();
-          if (tail - head >= 64) {
-            process(head & (RP_RING - 1), 64);
-            head += 64;
-          }
-        };
-        if constexpr (MULTI) {
-          // every (ia, ib) with |dx + ia Lx| <= reach + hx and the like
-          int ia = 0, ib = 0, blo = 0, bhi = -1, ahi = -1;
-          if (valid && fabs(dz) < rc) {
-            const double reach = rc + 1e-3;
-            ia = (int)ceil((-(reach + hx) - dx) * invLx);
-            ahi = (int)floor(((reach + hx) - dx) * invLx);
-            blo = (int)ceil((-(reach + hy) - dy) * invLy);
-            bhi = (int)floor(((reach + hy) - dy) * invLy);
-            ib = blo;
-          }
-          bool more = ia <= ahi && blo <= bhi;
-          while (__ballot(more)) {
-            const double px = dx + ia * Lx, py = dy + ib * Ly;
-            const bool has = more && near(px, py);
-            const unsigned long long bal = __ballot(has);
-            if (more && ++ib > bhi) {
-              ib = blo;
-              more = ++ia <= ahi;
-            }
-            if (bal) append(has, bal, px, py);
-          }
-        } else {
-          const double dx2 = dx - copysign(Lx, dx), dy2 = dy - copysign(Ly, dy);
-          int cand = 0;
-          if (valid && fabs(dz) < rc) {
-            cand = (near(dx, dy) ? 1 : 0) | (near(dx2, dy) ? 2 : 0) | (near(dx, dy2) ? 4 : 0) |
-                   (near(dx2, dy2) ? 8 : 0);
-          }
-          while (true) {
-            const bool has = cand != 0;
-            const unsigned long long bal = __ballot(has);
-            if (!bal) break;
-            const int which = has ? __builtin_ctz(cand) : 0;
-            cand &= cand - 1;
-            append(has, bal, (which & 1) ? dx2 : dx, (which & 2) ? dy2 : dy);
-          }
-        }
-      }
-    }
-    if (tail > head) process(head & (RP_RING - 1), tail - head);
-    head = tail = 0;
-    if (atom >= 0) part[((size_t)snap * gridDim.y + blockIdx.y) * n + atom] = acc;
-    acc = 0.0;
-  }
+__global__ void __launch_bounds__(64 * RP_WAVES, 4) k_real_space_plane(const RpArgs A) {
+  __shared__ __align__(16) RpLds lds;
+  rp_body<MULTI>(A, blockIdx.x, blockIdx.y, blockIdx.z, lds);
+}
+
+RpArgs rp_args(int g, int n, int m, int mpad64, int rchunks, int sub, const Buffers& b, int nmap,
+               const double4* cq, const double2* zr, double Lx, double Ly, double Lz, double rc,
+               double* part, int wg_target, const double* plane_tab) {
+  // rchunks rows of partials (sub of them per block of charges);
+  // configurations spread over the third grid dimension, about wg_target
+  // workgroups in all (a workgroup loops over the configurations beyond)
+  const int ablk = (nmap + 64 * RP_WAVES - 1) / (64 * RP_WAVES);
+  const int gz = std::max(1, std::min(g, (wg_target + ablk * rchunks - 1) / (ablk * rchunks)));
+  return RpArgs{g, n, m, mpad64, sub, nmap, ablk, rchunks, gz, b.amap, b.ex, b.ey, b.ez, cq, zr,
+                Lx, Ly, Lz, rc, plane_tab, part};
 }
 
 void launch_b_real_space(hipStream_t st, int g, int n, int m, int mpad64, int rchunks, int sub,
                          const Buffers& b, int nmap, const double4* cq, const double2* zr,
                          double Lx, double Ly, double Lz, double rc, double* part, int wg_target,
                          const double* plane_tab) {
-  // rchunks rows of partials (sub of them per block of charges);
-  // configurations spread over the third grid dimension, about wg_target
-  // workgroups in all (a workgroup loops over the configurations beyond)
-  const int ablk = (nmap + 64 * RS_WAVES - 1) / (64 * RS_WAVES);
-  const int gz = std::max(1, std::min(g, (wg_target + ablk * rchunks - 1) / (ablk * rchunks)));
-  dim3 grid(ablk, rchunks, gz), block(64 * RS_WAVES);
+  const RpArgs A = rp_args(g, n, m, mpad64, rchunks, sub, b, nmap, cq, zr, Lx, Ly, Lz, rc, part,
+                           wg_target, plane_tab);
+  const dim3 grid(A.nx, A.ny, A.nz), block(64 * RS_WAVES);
   if (plane_tab)
     hipLaunchKernelGGL((Lx >= 2.0 * rc && Ly >= 2.0 * rc ? k_real_space_plane<false>
                                                          : k_real_space_plane<true>),
-                       grid, block, 0, st, g, n, m, mpad64, sub, b.amap, nmap,
-                       b.ex, b.ey, b.ez, cq, zr, Lx, Ly, Lz, rc, plane_tab, part);
+                       grid, block, 0, st, A);
   else
     hipLaunchKernelGGL(k_real_space_b, grid, block, 0, st, g, n, m, mpad64, sub, b.amap, nmap,
                        b.ex, b.ey, b.ez, cq, zr, Lx, Ly, Lz, rc, b.rtab, part);

@@ -244,12 +244,20 @@ int sf_chunks_for(const cpm_ctx* c, int g, bool f16) {
 // workgroups of a grouped real-space launch: enough rounds that the planes'
 // uneven work evens out (2880 atoms, 64 configurations: 4.3 -> 3.9 us per
 // configuration from 512 to 2048; 20064 atoms: 0.81 -> 0.57 ms from 512 to
-// 4096), fewer for small atom maps, where every workgroup's staging of the
-// pair table costs more than it evens out
-int rs_target(const cpm_ctx* c) {
+// 4096), fewer for small atom maps and few configurations, where every
+// workgroup's staging of the pair table costs more than it evens out: about 14
+// blocks of 64 charges each while 256 or more remain (b of 1, 4 and 9
+// configurations at 2880 atoms with 128 / 256 / 512 / 2048 workgroups: 50.5 / 50.6 /
+// 56.7 / 60.7 us, 88 / 80 / 83 / 99, 152 / 120 / 117 / 140; of one at 9000 atoms
+// with 256 / 1024 / 2048 / 4096: 263 / 234 / 240 / 272)
+int rs_atom_blocks(const cpm_ctx* c) {
+  return (c->nmap + real_space_block_atoms() - 1) / real_space_block_atoms();
+}
+long rs_units(const cpm_ctx* c, int g) { return (long)rs_atom_blocks(c) * g * ((c->m + 63) / 64); }
+int rs_target(const cpm_ctx* c, int g) {
   if (c->rs_wg_target > 0) return c->rs_wg_target;
-  const int atom_blocks = (c->nmap + real_space_block_atoms() - 1) / real_space_block_atoms();
-  return atom_blocks <= 8 ? 2048 : 4096;
+  const int most = rs_atom_blocks(c) <= 8 ? 2048 : 4096;
+  return (int)std::max(256L, std::min((long)most, rs_units(c, g) / 14));
 }
 
 // real-space charge chunks for a launch group of g configurations on the
@@ -259,14 +267,14 @@ int rs_target(const cpm_ctx* c) {
 // configurations) a block is divided into up to 16 parts (rs_sub): at 288
 // atoms and 100 charges one workgroup walked all of them in 150 us.
 int rblocks_for(const cpm_ctx* c, int g) {
-  const int atom_blocks = (c->nmap + real_space_block_atoms() - 1) / real_space_block_atoms();
-  const int t = rs_target(c);
-  return std::max(1, std::min((c->m + 63) / 64, (t + atom_blocks * g - 1) / (atom_blocks * g)));
+  const int per = rs_atom_blocks(c) * g;
+  return std::max(1, std::min((c->m + 63) / 64, (rs_target(c, g) + per - 1) / per));
 }
 int rs_sub(const cpm_ctx* c, int g) {
-  const int atom_blocks = (c->nmap + real_space_block_atoms() - 1) / real_space_block_atoms();
+  const int rb = rblocks_for(c, g);
   int sub = 1;
-  while (sub < 16 && atom_blocks * g * rblocks_for(c, g) * sub < 256) sub *= 2;
+  if (rb == (c->m + 63) / 64)
+    while (sub < 16 && rs_atom_blocks(c) * g * rb * sub < 256) sub *= 2;
   return sub;
 }
 int rchunks_for(const cpm_ctx* c, int g) { return rblocks_for(c, g) * rs_sub(c, g); }
@@ -310,6 +318,16 @@ int zb_parts(const cpm_ctx* c, int g) {
     if (p * wgs > 4096.0) break;
   }
   return best;
+}
+
+// The real-space sums in the launch of the binned sums: for few configurations the
+// second stream's two event waits cost more than the pair sums lose by the sums'
+// registers and LDS (a workgroup per CU instead of two).  In us, two streams ->
+// one launch: b of 1, 2, 4 and 9 configurations at 2880 atoms 62 -> 50.5, 68 -> 66,
+// 83 -> 80, 117 -> 120; at 5000 atoms 1 and 2 (8600 blocks of 512 x 64 pairs each)
+// 156 -> 143, 254 -> 241; 9000 atoms (25 k) 234 -> 253.
+bool zb_one_launch(const cpm_ctx* c, int g) {
+  return rs_plane(c) && c->rs_conc_ok && g <= 4 && rs_units(c, g) <= 20000;
 }
 
 // workgroup items: for every 16 n_y the n_x that have them, in ranges of 16
@@ -1928,7 +1946,8 @@ cpm_status pv_enqueue(cpm_ctx* c, int batch, const double* d_xyz, void* d_b, int
     // structure factors (VALU/LDS-bound beside MFMA-bound work); it starts
     // after everything enqueued so far (the previous group's final sum,
     // which read its partials) and the final sum of this group waits for it
-    const bool conc = fast && c->rs_stream && !c->capturing;
+    const bool one = zb && !c->timing && zb_one_launch(c, g);   // (timed: a name for each)
+    const bool conc = fast && !one && c->rs_stream && !c->capturing;
     hipStream_t rst = st;
     if (zb) {
       // every configuration's charges sorted by z, and the dipole partials
@@ -1941,11 +1960,13 @@ cpm_status pv_enqueue(cpm_ctx* c, int batch, const double* d_xyz, void* d_b, int
       HIP_TRY(c, hipStreamWaitEvent(c->rs_stream, c->rs_ev_in, 0));
       rst = c->rs_stream;
     }
-    { Timed t(c, "real_space_b", rst);
+    if (!one) {
+      Timed t(c, "real_space_b", rst);
       if (!zb) launch_gather_charges(rst, g, m, mpad64, perm, xyz, b.elq, p.Lx, p.Ly, b.cq, b.zr);
       launch_b_real_space(rst, g, n, m, mpad64, rch, fast ? rs_sub(c, g) : 1, b, c->nmap, b.cq, b.zr, p.Lx, p.Ly, c->Lz,
-                          p.rcut, b.phir_part, fast ? rs_target(c) : 512,
-                          rs_plane(c) ? b.ptab : nullptr); }
+                          p.rcut, b.phir_part, fast ? rs_target(c, g) : 512,
+                          rs_plane(c) ? b.ptab : nullptr);
+    }
     if (conc) HIP_TRY(c, hipEventRecord(c->rs_ev_out, rst));
     if (!mfma) {
       Timed t(c, "dipole");
@@ -1953,9 +1974,11 @@ cpm_status pv_enqueue(cpm_ctx* c, int batch, const double* d_xyz, void* d_b, int
     }
     if (zb) {
       const int np = zb_parts(c, g);
+      const RpArgs rs = rp_args(g, n, m, mpad64, rch, rs_sub(c, g), b, c->nmap, b.cq, b.zr, p.Lx,
+                                p.Ly, c->Lz, p.rcut, b.phir_part, rs_target(c, g), b.ptab);
       { Timed t(c, "structure_factor");
         launch_zb_sums(st, g, zty != 0, c->zb, c->zt[zty], zb_items(c, g), m, mpad64, np,
-                       c->nlayers, b.cq, b.zbinoff, p.Lx, p.Ly, c->Lz, b.zpart); }
+                       c->nlayers, b.cq, b.zbinoff, p.Lx, p.Ly, c->Lz, b.zpart, one ? &rs : nullptr); }
       { Timed t(c, "sf_reduce");
         launch_zb_reduce(st, g, c->zb, c->nlayers, np, b.zpart, 2 * c->ncp, b.bT,
                          zb_sort_blocks(m), b.dip, b.dtot); }

@@ -571,10 +571,24 @@ void launch_zb_sort(hipStream_t st, int g, int m, int mpad64, const ZbTable& t, 
                     double4* cq, double2* zr, int* binoff, double* dip);
 void launch_zb_response(hipStream_t st, int ncu, int nzt, int nbins, int nlayers, int P,
                         const double* w, const double* layer_fz, double* H);
+// the planar real-space kernel's arguments (its code: rs_plane.hpp)
+struct RpArgs {
+  int g, n, m, mpad64, sub, nmap, nx, ny, nz;        // grid nx x ny x nz
+  const int* amap;
+  const double *ex, *ey, *ez;
+  const double4* cq;
+  const double2* zr;
+  double Lx, Ly, Lz, rc;
+  const double* ptab;
+  double* part;
+};
+RpArgs rp_args(int g, int n, int m, int mpad64, int rchunks, int sub, const Buffers& b, int nmap,
+               const double4* cq, const double2* zr, double Lx, double Ly, double Lz, double rc,
+               double* part, int wg_target, const double* plane_tab);
 void launch_zb_sums(hipStream_t st, int g, bool f32, const ZbPlan& z, const ZbTable& t,
                     const ZbItems& I, int m, int mpad64, int nparts, int nlayers,
                     const double4* cq, const int* binoff, double Lx, double Ly, double Lz,
-                    double* part);
+                    double* part, const RpArgs* rs = nullptr);
 void launch_zb_reduce(hipStream_t st, int g, const ZbPlan& z, int nlayers, int nparts,
                       const double* part, int M2, double* Tcat, int dblk, const double* dip,
                       double* dtot);

@@ -26,6 +26,7 @@
 #include <cmath>
 
 #include "cpm_internal.h"
+#include "rs_plane.hpp"
 
 namespace cpm {
 
@@ -338,7 +339,7 @@ __device__ inline double2 zpow(double2 z, int n) {
 __device__ inline double xor_lane(double v, int o) { return __shfl_xor(v, o, 64); }
 
 struct ZbArgs {
-  int g, m, mpad64, nparts, nbins, ncu, nlayers, ppart;
+  int g, m, mpad64, nparts, nbins, ncu, nlayers, ppart, lgroups;
   const ZbItem* items;
   const int4* cu_of;
   const double4* cq;
@@ -373,7 +374,7 @@ template <> struct Zb<float> {
 };
 
 template <typename T, int NU, int NC, int NK>
-__device__ inline void zb_item(const ZbArgs& A, const ZbItem it, int pt, int s, Zb<T>* W,
+__device__ inline void zb_item(const ZbArgs& A, const ZbItem it, int pt, int s, int lgroup, Zb<T>* W,
                                const int* bo, double* red) {
   typedef Zb<T> Z;
   typedef typename Z::acc acc_t;
@@ -390,7 +391,7 @@ __device__ inline void zb_item(const ZbArgs& A, const ZbItem it, int pt, int s, 
   const int jl = tid & (TJ - 1), grp = wave / (TJ / 64);     // charge and group when forming
   const bool up = lane & 32, mid = lane & 16;
   const int nlayers = A.nlayers, nbins = A.nbins;
-  const int L0 = blockIdx.y * NL * NK;
+  const int L0 = lgroup * NL * NK;
   const double4* cq = A.cq + (size_t)s * A.mpad64;
   const bool col00 = F32 && it.nxa == 0 && it.ny0 == 0;
   // byte offsets of this lane's H (32 bits: a bin's H stays below 2^31 bytes)
@@ -682,25 +683,50 @@ __device__ inline void zb_item(const ZbArgs& A, const ZbItem it, int pt, int s, 
   }
 }
 
-template <typename T, int NK>
-__global__ void __launch_bounds__(64 * ZB_W) k_zb_sums(const ZbArgs A) {
-  __shared__ __align__(16) Zb<T> W[2];
-  __shared__ int bo[ZB_MAXSORT];
-  __shared__ double red[sizeof(T) == 4 ? 64 * ZB_W : 1];
+template <typename T>
+struct ZbLds {
+  Zb<T> W[2];
+  int bo[ZB_MAXSORT];
+  double red[sizeof(T) == 4 ? 64 * ZB_W : 1];
+};
+
+// The sums of nsum workgroups; WITH_RS: and after them the real-space pair sums of
+// R.nx * R.ny * R.nz.  For few configurations, whose sums leave CUs idle: on a
+// second stream beside the sums the pair sums cost two event waits, and a single
+// configuration of 2880 atoms takes 75 us per step instead of 90 (replayed, where the
+// streams cannot overlap, 85 instead of 105).
+template <typename T, int NK, bool WITH_RS>
+__global__ void __launch_bounds__(64 * ZB_W) k_zb_sums(const ZbArgs A, int nsum, const RpArgs R) {
+  constexpr size_t lds = WITH_RS && sizeof(RpLds) > sizeof(ZbLds<T>) ? sizeof(RpLds) : sizeof(ZbLds<T>);
+  __shared__ __align__(16) char raw[lds];
+  if constexpr (WITH_RS) {
+    static_assert(RP_WAVES == ZB_W, "one workgroup size");
+    if ((int)blockIdx.x >= nsum) {
+      const int b = blockIdx.x - nsum, by = b / R.nx % R.ny, bz = b / (R.nx * R.ny);
+      RpLds& l = *reinterpret_cast<RpLds*>(raw);
+      if (R.Lx >= 2.0 * R.rc && R.Ly >= 2.0 * R.rc)
+        rp_body<false>(R, b % R.nx, by, bz, l);
+      else
+        rp_body<true>(R, b % R.nx, by, bz, l);
+      return;
+    }
+  }
+  ZbLds<T>& S = *reinterpret_cast<ZbLds<T>*>(raw);
   // the item varies slowest (consecutive workgroups go to different XCDs: an
   // item index that varies fastest would give each XCD one kind of item), the
   // largest items first
-  const int pt = blockIdx.x % A.nparts, rest = blockIdx.x / A.nparts;
+  const int per = nsum / A.lgroups, b0 = blockIdx.x % per, lgroup = blockIdx.x / per;
+  const int pt = b0 % A.nparts, rest = b0 / A.nparts;
   const int s = rest % A.g, wg = rest / A.g;
   const ZbItem it = A.items[wg];
   for (int b = threadIdx.x; b < A.nbins; b += 64 * ZB_W)
-    bo[b] = A.binoff[(size_t)s * (A.nbins + 1) + b];
+    S.bo[b] = A.binoff[(size_t)s * (A.nbins + 1) + b];
   __syncthreads();
   switch (it.shape) {                                        // NU + 2 (NC - 1)
-    case 1: zb_item<T, 1, 1, NK>(A, it, pt, s, W, bo, red); break;
-    case 2: zb_item<T, 2, 1, NK>(A, it, pt, s, W, bo, red); break;
-    case 3: zb_item<T, 1, 2, NK>(A, it, pt, s, W, bo, red); break;
-    default: zb_item<T, 2, 2, NK>(A, it, pt, s, W, bo, red); break;
+    case 1: zb_item<T, 1, 1, NK>(A, it, pt, s, lgroup, S.W, S.bo, S.red); break;
+    case 2: zb_item<T, 2, 1, NK>(A, it, pt, s, lgroup, S.W, S.bo, S.red); break;
+    case 3: zb_item<T, 1, 2, NK>(A, it, pt, s, lgroup, S.W, S.bo, S.red); break;
+    default: zb_item<T, 2, 2, NK>(A, it, pt, s, lgroup, S.W, S.bo, S.red); break;
   }
 }
 
@@ -829,22 +855,33 @@ void launch_zb_response(hipStream_t st, int ncu, int nzt, int nbins, int nlayers
                      dim3(256), 0, st, ncu, nzt, nbins, nlayers, w, layer_fz, H);
 }
 
+template <bool WITH_RS>
+static void zb_sums_launch(hipStream_t st, bool f32, int nk, int grid, const ZbArgs& a, int nsum,
+                           const RpArgs& r) {
+  const dim3 block(64 * ZB_W);
+  if (f32)
+    hipLaunchKernelGGL((nk == 1 ? k_zb_sums<float, 1, WITH_RS> : nk == 2 ? k_zb_sums<float, 2, WITH_RS>
+                        : nk == 3 ? k_zb_sums<float, 3, WITH_RS> : k_zb_sums<float, 4, WITH_RS>),
+                       dim3(grid), block, 0, st, a, nsum, r);
+  else
+    hipLaunchKernelGGL((nk == 1 ? k_zb_sums<double, 1, WITH_RS> : k_zb_sums<double, 2, WITH_RS>),
+                       dim3(grid), block, 0, st, a, nsum, r);
+}
+
 void launch_zb_sums(hipStream_t st, int g, bool f32, const ZbPlan& z, const ZbTable& t,
                     const ZbItems& I, int m, int mpad64, int nparts, int nlayers,
                     const double4* cq, const int* binoff, double Lx, double Ly, double Lz,
-                    double* part) {
-  const ZbArgs a{g, m, mpad64, nparts, t.nbins, z.ncu, nlayers, z.nunits * nlayers * 32,
-                 I.d_items, z.d_cu_of, cq, binoff, Lx, Ly, Lz, t.H, part};
+                    double* part, const RpArgs* rs) {
   // planes kept per lane: up to 4 pairs (FP32) or 2 quadruples per workgroup
   const int nl = f32 ? 2 : 4, nk = std::min(f32 ? 4 : 2, (nlayers + nl - 1) / nl);
-  const dim3 grid(I.nwg * nparts * g, (nlayers + nl * nk - 1) / (nl * nk)), block(64 * ZB_W);
-  if (f32)
-    hipLaunchKernelGGL((nk == 1 ? k_zb_sums<float, 1> : nk == 2 ? k_zb_sums<float, 2>
-                        : nk == 3 ? k_zb_sums<float, 3> : k_zb_sums<float, 4>),
-                       grid, block, 0, st, a);
+  const int lgroups = (nlayers + nl * nk - 1) / (nl * nk);
+  const ZbArgs a{g, m, mpad64, nparts, t.nbins, z.ncu, nlayers, z.nunits * nlayers * 32, lgroups,
+                 I.d_items, z.d_cu_of, cq, binoff, Lx, Ly, Lz, t.H, part};
+  const int nsum = I.nwg * nparts * g * lgroups;
+  if (rs)
+    zb_sums_launch<true>(st, f32, nk, nsum + rs->nx * rs->ny * rs->nz, a, nsum, *rs);
   else
-    hipLaunchKernelGGL((nk == 1 ? k_zb_sums<double, 1> : k_zb_sums<double, 2>), grid, block, 0, st,
-                       a);
+    zb_sums_launch<false>(st, f32, nk, nsum, a, nsum, RpArgs{});
 }
 
 void launch_zb_reduce(hipStream_t st, int g, const ZbPlan& z, int nlayers, int nparts,
