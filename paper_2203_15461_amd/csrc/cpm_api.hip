@@ -298,28 +298,6 @@ bool zb_usable(const cpm_ctx* c, int b_is_f32) {
          (double)t.nbins * c->zb.ncu * c->nlayers * zb_terms(ty) * sizeof(double) <= ZB_MAXTABLE;
 }
 
-// items and parts of the binned sums for g configurations.  A workgroup fills
-// a CU, so the parts are chosen for whole rounds of 256: rounds x (charges of a
-// part + its fixed cost, about ZB_FIXED charges' time) plus the parts to add.
-// Few configurations take the narrow items (half the work per workgroup).
-const ZbItems& zb_items(const cpm_ctx* c, int g) {
-  return (double)c->zb.wide.nwg * g * ((c->m + 127) / 128) < 512.0 ? c->zb.narrow : c->zb.wide;
-}
-int zb_parts(const cpm_ctx* c, int g) {
-  const double wgs = (double)zb_items(c, g).nwg * g;
-  int best = 1;
-  double cost = 1e300;
-  for (int p = 1; p <= std::min(256, (c->m + 31) / 32); ++p) {
-    const double t = std::ceil(p * wgs / 256.0) * ((double)c->m / p + ZB_FIXED) + p;
-    if (t < cost) {
-      cost = t;
-      best = p;
-    }
-    if (p * wgs > 4096.0) break;
-  }
-  return best;
-}
-
 // The real-space sums in the launch of the binned sums: for few configurations the
 // second stream's two event waits cost more than the pair sums lose by the sums'
 // registers and LDS (a workgroup per CU instead of two).  In us, two streams ->
@@ -328,6 +306,36 @@ int zb_parts(const cpm_ctx* c, int g) {
 // 156 -> 143, 254 -> 241; 9000 atoms (25 k) 234 -> 253.
 bool zb_one_launch(const cpm_ctx* c, int g) {
   return rs_plane(c) && c->rs_conc_ok && g <= 4 && rs_units(c, g) <= 20000;
+}
+
+// items and parts of the binned sums for g configurations.  A workgroup fills
+// a CU, so the parts are chosen for whole rounds of 256: rounds x (charges of a
+// part + its fixed cost, about ZB_FIXED charges' time) plus the parts to add.
+// Few configurations take the narrow items (half the work per workgroup).  With the
+// real-space sums in the same launch no round ends at 256: a workgroup's own time,
+// and its fixed cost (0.95 charges' time) per CU.  One configuration, parts: us:
+// 288 atoms 4: 36.4, 8: 33.0, 16: 30.0, 25: 30.4; 1152 atoms 39: 66, 64: 57, 96: 61;
+// 2880 atoms 39: 56, 64: 50.6, 96: 52.8; 5000 atoms 64: 169, 128: 143.
+const ZbItems& zb_items(const cpm_ctx* c, int g) {
+  return (double)c->zb.wide.nwg * g * ((c->m + 127) / 128) < 512.0 ? c->zb.narrow : c->zb.wide;
+}
+int zb_parts(const cpm_ctx* c, int g) {
+  const double wgs = (double)zb_items(c, g).nwg * g;
+  const bool one = zb_one_launch(c, g);
+  const int most = std::min(256, one ? (c->m + 5) / 6 : (c->m + 31) / 32);
+  const int step = one && most >= 16 ? 16 : 1;
+  int best = 1;
+  double cost = 1e300;
+  for (int p = step; p <= most; p += step) {
+    const double t = one ? (double)c->m / p + 0.95 * p * wgs
+                         : std::ceil(p * wgs / 256.0) * ((double)c->m / p + ZB_FIXED) + p;
+    if (t < cost) {
+      cost = t;
+      best = p;
+    }
+    if (p * wgs > 4096.0) break;
+  }
+  return best;
 }
 
 // workgroup items: for every 16 n_y the n_x that have them, in ranges of 16
@@ -794,6 +802,8 @@ void ensure_gemm_work(cpm_ctx* c, GemmWork& w, size_t len) {
   w.len = dalloc(c, &w.p, len) == CPM_OK ? len : 0;
 }
 
+constexpr int MVQ_BATCH = 3;     // vectors of a one-launch solve (GEMM from 4 on in FP64)
+
 // work buffers of one solve: the context's own (grown on demand), or carved
 // out of the fixed scratch array of cpm_solve_charges_noalloc
 struct SolveWork {
@@ -801,11 +811,12 @@ struct SolveWork {
   uint16_t* xhi; uint16_t* xlo;
   const cpm_ctx::GemmCfg* bf16 = nullptr;      // forced split-BF16 configuration
   GemmWork gw = {};
+  int* mvcount = nullptr;                      // null: no one-launch solve
 };
 
 SolveWork ctx_work(cpm_ctx* c) {
   Buffers& b = c->b;
-  return SolveWork{b.qt, b.res, b.bpad, b.qpad, b.means, b.kpart, b.xhi, b.xlo, nullptr, b.gws};
+  return SolveWork{b.qt, b.res, b.bpad, b.qpad, b.means, b.kpart, b.xhi, b.xlo, nullptr, b.gws, b.mvcount};
 }
 
 // one split-BF16 product C (+)= X S~ over `rows` rows of this context; X is
@@ -2079,6 +2090,10 @@ cpm_status sc_prepare(cpm_ctx* c, int batch, const void* d_b, int b_is_f32, unsi
   const bool gemm = (batch >= GEMM_MIN_BATCH && prec == 0) || prec == 2 || c->factor_only;
   const int rows = gemm ? ((batch + TILE - 1) / TILE) * TILE : batch;
   TRY(ensure_solve_buffers(c, rows));
+  if (!gemm && !c->b.mvcount && batch <= MVQ_BATCH) {
+    TRY(dalloc(c, &c->b.mvcount, MVQ_BATCH));
+    HIP_TRY(c, hipMemsetAsync(c->b.mvcount, 0, MVQ_BATCH * sizeof(int), c->stream));
+  }
   if (gemm && !c->factor_only && prec == 0)
     ensure_gemm_work(c, c->b.gws, gemm_f64_work(rows, c->npad, c->npad));
   if (prec == 2) {
@@ -2154,6 +2169,12 @@ cpm_status sc_enqueue(cpm_ctx* c, int batch, const void* d_b, int b_is_f32, unsi
   // Every product with S~ acts on a centred vector: S e = 0 makes that exact,
   // and it keeps the rounding of a low-precision S~ away from the large
   // uniform part of b and of the refinement residual.
+  if (!gemm && !refine && !c->timing && w.mvcount && batch <= MVQ_BATCH && matvec_q_fits(npad)) {
+    // (timed: a name for each part)
+    launch_matvec_q(st, which, n, npad, Sm, batch, d_b, b_is_f32, b.d, b.u, b.scal, b.eid, c->n_e,
+                    w.qt, d_q, d_Qe, w.mvcount);
+    return launched(c, "solve");
+  }
   if (!gemm) {
     // q~ = S~ (b - mean(b) e) + d, one streaming pass over S~ per vector
     { Timed t(c, "row_means");
@@ -3166,7 +3187,7 @@ void cpm_destroy(cpm_ctx* c) {
   dfree(b.zcounts); dfree(b.zbinoff); dfree(b.zpart); dfree(b.dtot);
   dfree(c->zb.d_units); dfree(c->zb.d_cu_of); dfree(c->zb.d_cols); dfree(c->zb.d_w);
   dfree(c->zb.wide.d_items); dfree(c->zb.narrow.d_items); dfree(c->zt[0].H); dfree(c->zt[1].H);
-  dfree(b.kpart); dfree(b.gws.p); dfree(b.ccmU); dfree(b.ccmC); dfree(b.sg); dfree(b.zeta); dfree(b.szeta);
+  dfree(b.kpart); dfree(b.gws.p); dfree(b.mvcount); dfree(b.ccmU); dfree(b.ccmC); dfree(b.sg); dfree(b.zeta); dfree(b.szeta);
   dfree(b.Qpair); dfree(b.ell_col); dfree(b.ell_val); dfree(b.plane_off); dfree(b.dextra);
   dfree(b.bsr_col); dfree(b.bsr_val); dfree(b.cg_items); dfree(b.asmG); dfree(b.asmF);
   dfree(b.Ecat); dfree(b.cg_ident); dfree(b.cgv); dfree(b.cgred);

@@ -160,6 +160,7 @@ struct Buffers {
   uint16_t* xlo = nullptr;         //   (bpad_rows x npad each)
   double* means = nullptr;         // per-vector uniform part removed before S products
   double* kpart = nullptr;         // split-K partial slices of the batched split-BF16 GEMM
+  int* mvcount = nullptr;         // finished workgroups per vector of a one-launch solve
   GemmWork gws;                    // partial tiles of the FP64 solves
   double* ccmU = nullptr;          // constrained charges: U = A^-1 G (n x n_e)
   double* ccmC = nullptr;          // C~^-1 (n_e x n_e) followed by the targets Q (n_e)
@@ -487,6 +488,13 @@ void launch_center_rows(hipStream_t st, int n, int ld, int batch, double* x);
 void launch_make_rhs(hipStream_t st, int n, int npad, int batch, const void* bsrc, int b_is_f32,
                      const double* v, double* c);
 // q[b] = (qt[b] + add) - (e^T (qt[b] + add) / s) u ; Qe[b] = G^T q[b]   (add may be NULL)
+// S (b - mean) + d, projection and totals of each of a few vectors, in one launch
+// (npad <= 4096); y: batch x npad of work, count: batch zeros, zero again afterwards
+bool matvec_q_fits(int npad);
+void launch_matvec_q(hipStream_t st, int which, int n, int npad, const void* M, int batch,
+                     const void* b, int b_is_f32, const double* d, const double* u,
+                     const double* s_dev, const int* eid, int n_e, double* y, double* q, double* Qe,
+                     int* count);
 void launch_finalize(hipStream_t st, int n, int batch, const double* qt, int ldqt, const double* add,
                      const double* u, const double* s_dev, const int* eid, int n_e, double* q,
                      int ldq, double* Qe);

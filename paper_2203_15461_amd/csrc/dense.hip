@@ -1114,6 +1114,168 @@ void launch_finalize(hipStream_t st, int n, int batch, const double* qt, int ldq
                        n_e, q, ldq, Qe);
 }
 
+// ---------------------------------------------------------------------------
+// One vector's solve in one launch: x = b - mean(b) in LDS (every workgroup forms
+// it), rows of S x + d as k_matvec, and by the workgroup that ends last the
+// neutrality projection and electrode totals as k_finalize.  For matrices that stay
+// in the caches, whose product takes less time than the three launches' latencies
+// (centre 4 us, product 12, finalize 9 at 2880 atoms): a step of
+// 288 atoms 50 -> 45 us, of 2880 75 -> 69.5 (with a release fence per workgroup, which
+// writes back its L2, 81).
+// y is exchanged by stores and loads at device scope; *count is zero between
+// launches.  Sums in a fixed order.
+// ---------------------------------------------------------------------------
+constexpr int MQ_MAX = 4096;                         // npad: x in 32 KiB of LDS
+
+template <typename TM, typename TX, int R>
+__global__ void __launch_bounds__(256) k_matvec_q(int n, int npad, const TM* __restrict__ M,
+                                                  const TX* __restrict__ bx,
+                                                  const double* __restrict__ d,
+                                                  const double* __restrict__ u,
+                                                  const double* __restrict__ s_dev,
+                                                  const int* __restrict__ eid, int n_e, double* y,
+                                                  double* __restrict__ q, double* __restrict__ Qe,
+                                                  int* count) {
+  constexpr int PT = MQ_MAX / 256, VEC = 16 / sizeof(TM);
+  __shared__ __align__(16) double xs[MQ_MAX];
+  __shared__ double sh[8][4];
+  __shared__ int last;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, b = blockIdx.y;
+  {
+    const TX* xb = bx + (size_t)b * n;
+    double v[PT], t = 0.0;
+#pragma unroll
+    for (int k = 0; k < PT; ++k) v[k] = tid + 256 * k < n ? (double)xb[tid + 256 * k] : 0.0;
+#pragma unroll
+    for (int k = 0; k < PT; ++k) t += v[k];
+    const double mean = block_sum256(t, sh[0]) / n;
+#pragma unroll
+    for (int k = 0; k < PT; ++k)
+      if (tid + 256 * k < npad) xs[tid + 256 * k] = tid + 256 * k < n ? v[k] - mean : 0.0;
+  }
+  const int row0 = (blockIdx.x * 4 + wave) * R;
+  double* yb = y + (size_t)b * npad;
+  __syncthreads();
+  if (row0 < npad) {
+    const TM* mrow = M + (size_t)row0 * npad;
+    double acc[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) acc[r] = 0.0;
+#pragma unroll 2
+    for (int j0 = lane * VEC; j0 < npad; j0 += 64 * VEC) {
+      TM mv[R][VEC];
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const TM* src = mrow + (size_t)r * npad + j0;
+        if constexpr (VEC == 2) {
+          const d2v t = *reinterpret_cast<const d2v*>(src);
+          mv[r][0] = t.x; mv[r][1] = t.y;
+        } else {
+          const f4v t = *reinterpret_cast<const f4v*>(src);
+          mv[r][0] = t.x; mv[r][1] = t.y; mv[r][2] = t.z; mv[r][3] = t.w;
+        }
+      }
+      double xj[VEC];
+#pragma unroll
+      for (int t = 0; t < VEC; ++t) xj[t] = xs[j0 + t];
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int t = 0; t < VEC; ++t) acc[r] += (double)mv[r][t] * xj[t];
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) acc[r] = wave_sum(acc[r]);
+    if (lane < R) {
+      double t = acc[0];
+#pragma unroll
+      for (int r = 1; r < R; ++r)
+        if (lane == r) t = acc[r];
+      __hip_atomic_store(&yb[row0 + lane], t + d[row0 + lane], __ATOMIC_RELAXED,
+                         __HIP_MEMORY_SCOPE_AGENT);
+    }
+  }
+  // only y is exchanged, by device-scope accesses past the XCD's L2: the stores have
+  // to be complete before the count, no cache has to be written back
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (tid == 0)
+    last = __hip_atomic_fetch_add(&count[b], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
+           (int)gridDim.x - 1;
+  __syncthreads();
+  if (!last) return;
+  if (tid == 0) __hip_atomic_store(&count[b], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  // this thread's values of y and u
+  double v[PT], uu[PT], t = 0.0;
+#pragma unroll
+  for (int k = 0; k < PT; ++k) {
+    const int i = tid + 256 * k;
+    v[k] = i < n ? __hip_atomic_load(&yb[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0.0;
+    uu[k] = i < n ? u[i] : 0.0;
+  }
+#pragma unroll
+  for (int k = 0; k < PT; ++k) t += v[k];
+  const double mu = block_sum256(t, sh[0]) / (*s_dev);
+#pragma unroll
+  for (int k = 0; k < PT; ++k)
+    if (tid + 256 * k < n) q[(size_t)b * n + tid + 256 * k] = v[k] - mu * uu[k];
+  if (!Qe) return;
+  int e[PT];
+#pragma unroll
+  for (int k = 0; k < PT; ++k) e[k] = tid + 256 * k < n ? eid[tid + 256 * k] : -1;
+  for (int a0 = 0; a0 < n_e; a0 += 4) {
+    double tt[4] = {0.0, 0.0, 0.0, 0.0}, ww[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int k = 0; k < PT; ++k)
+#pragma unroll
+      for (int a = 0; a < 4; ++a) {
+        tt[a] += e[k] == a0 + a ? v[k] : 0.0;
+        ww[a] += e[k] == a0 + a ? uu[k] : 0.0;
+      }
+    __syncthreads();
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+      tt[a] = wave_sum(tt[a]);
+      ww[a] = wave_sum(ww[a]);
+      if (lane == 0) {
+        sh[a][wave] = tt[a];
+        sh[4 + a][wave] = ww[a];
+      }
+    }
+    __syncthreads();
+    if (tid < 4 && a0 + tid < n_e)
+      Qe[(size_t)b * n_e + a0 + tid] =
+          ((sh[tid][0] + sh[tid][1]) + (sh[tid][2] + sh[tid][3])) -
+          mu * ((sh[4 + tid][0] + sh[4 + tid][1]) + (sh[4 + tid][2] + sh[4 + tid][3]));
+  }
+}
+
+bool matvec_q_fits(int npad) { return npad <= MQ_MAX; }
+
+template <typename TM, typename TX>
+static void matvec_q_launch(hipStream_t st, int n, int npad, const TM* M, int batch, const TX* b,
+                            const double* d, const double* u, const double* s_dev, const int* eid,
+                            int n_e, double* y, double* q, double* Qe, int* count) {
+  const int R = npad >= 2048 ? 4 : npad >= 1024 ? 2 : 1;
+  hipLaunchKernelGGL((R == 4 ? k_matvec_q<TM, TX, 4> : R == 2 ? k_matvec_q<TM, TX, 2>
+                                                               : k_matvec_q<TM, TX, 1>),
+                     dim3((npad / R + 3) / 4, batch), dim3(256), 0, st, n, npad, M, b, d, u, s_dev,
+                     eid, n_e, y, q, Qe, count);
+}
+
+void launch_matvec_q(hipStream_t st, int which, int n, int npad, const void* M, int batch,
+                     const void* b, int b_is_f32, const double* d, const double* u,
+                     const double* s_dev, const int* eid, int n_e, double* y, double* q, double* Qe,
+                     int* count) {
+  auto go = [&](auto m, auto x) {
+    matvec_q_launch(st, n, npad, m, batch, x, d, u, s_dev, eid, n_e, y, q, Qe, count);
+  };
+  if (which == 0) {
+    if (b_is_f32) go((const double*)M, (const float*)b); else go((const double*)M, (const double*)b);
+  } else {
+    if (b_is_f32) go((const float*)M, (const float*)b); else go((const float*)M, (const double*)b);
+  }
+}
+
 
 // ---------------------------------------------------------------------------
 // Inverse kept as the Cholesky factor (the solves are GEMMs with the factor's
