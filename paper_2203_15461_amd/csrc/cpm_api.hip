@@ -1155,22 +1155,32 @@ cpm_status assemble_A(cpm_ctx* c, hipStream_t st) {
     const int ldG = (2 * c->ncolsort + 15) / 16 * 16;
     TRY(dalloc(c, &b.Qpair, (size_t)c->ncolsort * c->nlayers * c->nlayers));
     TRY(dalloc(c, &b.asmG, (size_t)c->nmap * ldG));
-    TRY(dalloc(c, &b.asmF, (size_t)ldG * npad));
+    // F of as many planes at a time as 256 MiB hold: one launch for all of them
+    const int per = (int)std::max<size_t>(
+        1, std::min({(size_t)ASM_PLANES, (size_t)c->nlayers, ((size_t)256 << 20) / ((size_t)ldG * npad * sizeof(double))}));
+    TRY(dalloc_cap(c, &b.asmF, (size_t)per * ldG * npad));
     launch_plane_pair_weights(st, c->ncolsort, c->nlayers, b.sc_lo, b.sc_len, b.sc_koff,
                               b.w2, b.layer_fz, b.Qpair);
     launch_build_G(st, c->nmap, c->ncolsort, ldG, b.amap, b.sc_nx, b.sc_ny, b, b.asmG);
     int row0 = 0;
-    for (int L = 0; L < c->nlayers; ++L) {
-      const int rows = c->h_plane_rows[L];              // this plane's rows of the map (x 64)
-      // only the lower triangle of A is kept (mirrored at the end): the
-      // plane's rows need the columns up to their largest atom index
-      int amax = 0;
-      for (int r = row0; r < row0 + rows; ++r) amax = std::max(amax, c->h_amap[r]);
-      const int ncols = std::min(npad, (amax + 64) / 64 * 64);
-      launch_build_F(st, L, n, npad, c->nlayers, c->ncolsort, ldG, b.sc_nx, b.sc_ny, b,
+    for (int L0 = 0; L0 < c->nlayers; L0 += per) {
+      const int planes = std::min(per, c->nlayers - L0);
+      AsmPlanes pl{};
+      int rows = 0;
+      for (int p = 0; p < planes; ++p) {
+        // only the lower triangle of A is kept (mirrored at the end): the
+        // plane's rows need the columns up to their largest atom index
+        const int r0 = row0 + rows;
+        rows += c->h_plane_rows[L0 + p];                // this plane's rows of the map (x 64)
+        int amax = 0;
+        for (int r = r0; r < row0 + rows; ++r) amax = std::max(amax, c->h_amap[r]);
+        pl.ncols[p] = std::min(npad, (amax + 64) / 64 * 64);
+        pl.tile_end[p] = rows / 64;
+      }
+      launch_build_F(st, L0, planes, n, npad, c->nlayers, c->ncolsort, ldG, b.sc_nx, b.sc_ny, b,
                      b.Qpair, b.asmF);
-      launch_gemm_f64(st, false, false, rows, ncols, ldG, c->ke, b.asmG + (size_t)row0 * ldG,
-                      ldG, b.asmF, npad, 1.0, b.A, npad, 0, 0, b.amap + row0);
+      launch_gemm_planes(st, pl, planes, c->ke, b.asmG + (size_t)row0 * ldG, ldG, b.asmF, b.A, npad,
+                         b.amap + row0);
       TRY(launched(c, "kspace planes"));
       row0 += rows;
     }
@@ -2146,7 +2156,7 @@ cpm_status sc_enqueue(cpm_ctx* c, int batch, const void* d_b, int b_is_f32, unsi
         launch_pad_rows(st, n, npad, batch, rows, d_b, b_is_f32, nullptr, w.bpad); }
       Timed t(c, "gemm_f64");
       launch_gemm_f64(st, false, false, rows, npad, npad, 1.0, w.bpad, npad, b.Ainv, npad, 0.0, w.qt,
-                      npad, 0, 0, nullptr, w.gw);
+                      npad, 0, 0, w.gw);
     }
     { Timed t(c, "finalize");
       launch_ccm_finalize(st, n, batch, w.qt, npad, b.ccmU, b.ccmC, b.ccmC + c->n_e * c->n_e, b.eid,
@@ -2159,7 +2169,7 @@ cpm_status sc_enqueue(cpm_ctx* c, int batch, const void* d_b, int b_is_f32, unsi
     if (prec == 0) {
       Timed t(c, "gemm_f64");
       launch_gemm_f64(st, false, false, rows, npad, npad, 1.0, x, npad, b.S, npad,
-                      accumulate ? 1.0 : 0.0, y, npad, 0, 0, nullptr, w.gw);
+                      accumulate ? 1.0 : 0.0, y, npad, 0, 0, w.gw);
     } else {
       Timed t(c, "gemm_bf16x3");
       enqueue_bf16(c, x, y, rows, accumulate, w.bf16 ? *w.bf16 : bf16_cfg(c, rows), w);

@@ -442,7 +442,7 @@ void launch_plane_pair_weights(hipStream_t st, int ncolsort, int nlayers, const 
                                 const double* layer_fz, double2* Q);
 void launch_build_G(hipStream_t st, int nmap, int ncolsort, int ldG, const int* amap,
                     const int* sc_nx, const int* sc_ny, const Buffers& b, double* G);
-void launch_build_F(hipStream_t st, int L, int n, int npad, int nlayers, int ncolsort, int ldG,
+void launch_build_F(hipStream_t st, int L, int planes, int n, int npad, int nlayers, int ncolsort, int ldG,
                     const int* sc_nx, const int* sc_ny, const Buffers& b, const double2* Q,
                     double* F);
 void launch_mirror_lower(hipStream_t st, int npad, double* A);
@@ -452,8 +452,15 @@ void launch_mirror_lower(hipStream_t st, int npad, double* A);
 // tri: 0 all tiles, 1 lower tiles only.  kmode: 0 K range [0,K), 1 [max(m0,n0), K).
 void launch_gemm_f64(hipStream_t st, bool transA, bool transB, int M, int N, int K,
                      double alpha, const double* A, int lda, const double* B, int ldb,
-                     double beta, double* C, int ldc, int tri, int kmode, const int* rowmap = nullptr,
-                     GemmWork work = {});
+                     double beta, double* C, int ldc, int tri, int kmode, GemmWork work = {});
+// A[amap[r]][..] += alpha G_r F^p for planes p of consecutive 64-row tiles of G and amap:
+// ends (in tiles) and columns of each; F: ldG x npad per plane
+constexpr int ASM_PLANES = 16;
+struct AsmPlanes {
+  int tile_end[ASM_PLANES], ncols[ASM_PLANES];
+};
+void launch_gemm_planes(hipStream_t st, const AsmPlanes& pl, int n, double alpha, const double* G,
+                        int ldG, const double* F, double* A, int npad, const int* amap);
 // doubles of work that splits an M x N x K product (0: it is better unsplit); with
 // less it runs unsplit.  Only untransposed, full products are split.
 size_t gemm_f64_work(int M, int N, int K);

@@ -207,15 +207,14 @@ template <bool TA, bool TB>
 __global__ void __launch_bounds__(256, 4) k_gemm_f64(GtGeom g, double alpha,
                                                      const double* __restrict__ A, int lda,
                                                      const double* __restrict__ B, int ldb,
-                                                     double beta, double* C, int ldc,
-                                                     const int* __restrict__ rowmap) {
+                                                     double beta, double* C, int ldc) {
   __shared__ __align__(16) double lds[GT_LDS64];
   int bm, bn;
   g.tile(blockIdx.x, bm, bn);
   const size_t m0 = 64 * bm, n0 = 64 * bn, k0 = g.kbeg(bm);
   gemm_tile64<TA, TB>(lds, TA ? A + k0 * lda + m0 : A + m0 * lda + k0, lda,
                       TB ? B + n0 * ldb + k0 : B + k0 * ldb + n0, ldb, g.K - (int)k0, alpha, beta,
-                      C + (rowmap ? 0 : m0 * ldc) + n0, ldc, rowmap ? rowmap + m0 : nullptr);
+                      C + m0 * ldc + n0, ldc, nullptr);
 }
 
 __global__ void __launch_bounds__(512, 4) k_gemm_f64_split(GtGeom g, double alpha,
@@ -330,6 +329,33 @@ __global__ void __launch_bounds__(512) k_gemm_f64_join(GtGeom g, double alpha, d
   }
 }
 
+// The planes' products of the assembly of A in one launch (their rows follow one
+// another in the atom map): a plane alone fills the chip only in large cells.  2880
+// atoms, six planes of 480 to 512 rows, K = 672: six launches 308 us,
+// one 154.
+__global__ void __launch_bounds__(256, 4) k_gemm_planes(AsmPlanes pl, int tn, double alpha, double beta,
+                                                        const double* __restrict__ G, int ldG,
+                                                        const double* __restrict__ F, double* A,
+                                                        int npad, const int* __restrict__ amap) {
+  __shared__ __align__(16) double lds[GT_LDS64];
+  const int bm = blockIdx.x / tn, bn = blockIdx.x % tn;
+  int p = 0;
+  while (bm >= pl.tile_end[p]) ++p;
+  if (64 * bn >= pl.ncols[p]) return;
+  // (beta an argument: a constant 1 would contract alpha acc + A into one rounding)
+  gemm_tile64<false, false>(lds, G + (size_t)64 * bm * ldG, ldG, F + (size_t)p * ldG * npad + 64 * bn,
+                            npad, ldG, alpha, beta, A + 64 * bn, npad, amap + 64 * bm);
+}
+
+void launch_gemm_planes(hipStream_t st, const AsmPlanes& pl, int n, double alpha, const double* G,
+                        int ldG, const double* F, double* A, int npad, const int* amap) {
+  int tn = 0;
+  for (int p = 0; p < n; ++p) tn = std::max(tn, pl.ncols[p] / 64);
+  if (n > 0 && pl.tile_end[n - 1] > 0 && tn > 0)
+    hipLaunchKernelGGL(k_gemm_planes, dim3(pl.tile_end[n - 1] * tn), dim3(256), 0, st, pl, tn, alpha,
+                       1.0, G, ldG, F, A, npad, amap);
+}
+
 // Split up to two 64-tiles per CU, where unsplit workgroups have a CU to themselves
 // or share it unevenly: N = K = 2944 with M = 512 (368 tiles) 220 -> 177 us, M = 1024
 // (736 tiles) 316 -> 305, not worth twice the work array.  Short products do not
@@ -343,10 +369,10 @@ size_t gemm_f64_work(int M, int N, int K) {
 
 void launch_gemm_f64(hipStream_t st, bool transA, bool transB, int M, int N, int K, double alpha,
                      const double* A, int lda, const double* B, int ldb, double beta, double* C,
-                     int ldc, int tri, int kmode, const int* rowmap, GemmWork work) {
+                     int ldc, int tri, int kmode, GemmWork work) {
   if (M <= 0 || N <= 0) return;
   const size_t need = gemm_f64_work(M, N, K);
-  if (need > 0 && work.len >= need && !transA && !transB && !tri && !kmode && !rowmap) {
+  if (need > 0 && work.len >= need && !transA && !transB && !tri && !kmode) {
     const GtGeom g{M, N, K, 0, 0, (M + 127) / 128, (N + 127) / 128,
                    ((M + 127) / 128) * ((N + 127) / 128) * (K / 16)};
     hipLaunchKernelGGL(k_gemm_f64_split, dim3(GT_RUNS), dim3(512), 0, st, g, alpha, A, lda, B, ldb,
@@ -358,7 +384,7 @@ void launch_gemm_f64(hipStream_t st, bool transA, bool transB, int M, int N, int
   const GtGeom g{M, N, K, tri, kmode, M / 64, N / 64, 0};
 #define CPM_GT(TA, TB)                                                                              \
   hipLaunchKernelGGL((k_gemm_f64<TA, TB>), dim3(g.tiles()), dim3(256), 0, st, g, alpha, A, lda, B,  \
-                     ldb, beta, C, ldc, rowmap)
+                     ldb, beta, C, ldc)
   if (transA) {
     if (transB) CPM_GT(true, true); else CPM_GT(true, false);
   } else {
@@ -1077,10 +1103,11 @@ __global__ void __launch_bounds__(1024) k_finalize(int n, const double* __restri
     }
     // wave sums, then thread k < 4 adds electrode a0 + k's 16 wave sums in order
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      t[k] = wave_sum(t[k]);
-      w[k] = wave_sum(w[k]);
-    }
+    for (int k = 0; k < 4; ++k)
+      if (a0 + k < n_e) {
+        t[k] = wave_sum(t[k]);
+        w[k] = wave_sum(w[k]);
+      }
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     if (lane == 0)
 #pragma unroll
