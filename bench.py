@@ -23,6 +23,7 @@ from __future__ import annotations
 
 import argparse
 import json
+import math
 import os
 import sys
 import time
@@ -32,8 +33,8 @@ sys.path.insert(0, ROOT)
 
 MODES = {
     # name: (store flags, b in fp32, solve mode, dtype label).  The reduced-
-    # precision modes keep b in FP32 (structure factors on FP16 matrix cores
-    # with split operands) and refine q once against A in FP64.
+    # precision modes keep b in FP32 (k space on FP32 matrix
+    # cores) and refine q once against A in FP64.
     "f64": (1, False, 0x000, "f64"),
     "f32r": (1 | 2, True, 0x101, "b f32, S f32, f64 refine"),
     "bf16r": (1 | 4, True, 0x102, "b f32, S bf16x3 (f32 accumulation), f64 refine"),
@@ -129,7 +130,7 @@ def run_factor_step(w, B, steps, warmup, b_f32):
     assembled and Cholesky-factored on the second stream while b runs, and
     q = P A^-1 b + d comes from forward and back substitution with the
     factor for all B configurations (FP64 solve; no L^-1, A^-1 or S); b in
-    FP64, or in FP32 from the FP32 structure factors (b_f32)."""
+    FP64, or in FP32, k space on FP32 matrix cores (b_f32)."""
     import torch
     from paper_2203_15461_amd import cpm
     from paper_2203_15461_amd import inputs as I
@@ -259,7 +260,7 @@ def run_workload(args, w, B, name, steps, warmup, calibrate_copy):
     step()
     fams = ["sf_tables", "structure_factor", "sf_reduce", "kspace_project", "projection", "real_space_b", "combine",
             "gemm_f64", "gemm_bf16x3", "matvec_f64", "matvec_f32", "finalize", "potrf_diag",
-            "chol_update", "trtri", "lauum", "assemble_real", "assemble_kspace",
+            "chol_solve", "chol_update", "lauum", "assemble_real", "assemble_kspace",
             "row_means", "pad_rows", "make_rhs", "center_rows"]
     timing = {f: ctx.timing(f) for f in fams}
     ctx.enable_timing(False)
@@ -302,7 +303,7 @@ def run_workload(args, w, B, name, steps, warmup, calibrate_copy):
     # host time to enqueue the loop: close to the wall time when the host,
     # not the GPU, bounds one configuration per step
     plain_host_us = (t_host - ts) / n_plain * 1e6
-    # the same loop with b in FP32 (the split-FP16 structure factors), still
+    # the same loop with b in FP32 (k space on FP32 matrix cores), still
     # solved by the FP64 matvec: the reduced-precision single-configuration
     # step; its charges are compared with the FP64 loop's last ones
     b1f = torch.empty((1, w.n), dtype=torch.float32, device=dev)
@@ -321,28 +322,33 @@ def run_workload(args, w, B, name, steps, warmup, calibrate_copy):
     matvec = matvec_roofline(ctx, w, xyz, dev)
     cg = cg_measure(w, xyz, dev, ctx)
 
-    # dominant kernel: the structure factors
+    # dominant kernel: the k-space sums over the charges
     nk = int(ctx.info("nk"))
     sf_avg = sf_ms / max(sf_cnt, 1) * 1e-3
     # algorithmic work of one launch (it covers one launch group of
-    # configurations): on matrix cores, 4 flop per (k, charge) pair (one
-    # real 2 x 2 product of (Re C, Im C) with (Re Z, Im Z) serves k and its
-    # mirror in k_z: 8 flop per 2 k); on the VALU kernel, 8 flop per pair (a
-    # complex rotation and a complex accumulate)
+    # configurations).  Planar electrodes, charges sorted by z (k_zb_sums): per
+    # charge and column (n_x, n_y >= 0) the four products of cosines and sines
+    # with 16 (FP64) or 8 (FP32) functions of z, 2 flop each.  Explicit
+    # structure factors (CPM_SF_ZBIN=0): on matrix cores 4 flop per (k, charge)
+    # pair (one real 2 x 2 product of (Re C, Im C) with (Re Z, Im Z) serves k
+    # and its mirror in k_z: 8 flop per 2 k); on the VALU kernel 8 flop per
+    # pair (a complex rotation and a complex accumulate)
     snaps_per_launch = B * steps / max(sf_cnt, 1)
     matrix = ctx.info("sf_matrix") == 1.0
     sf_prec = ctx.info("sf_fp32") if (b_f32 and matrix) else 0.0
     sf_fp32, sf_f16 = sf_prec == 1.0, sf_prec == 2.0
-    flop_per_pair = 4.0 if matrix else 8.0
-    flop_per_launch = flop_per_pair * nk * w.m * snaps_per_launch
+    zbin = matrix and os.environ.get("CPM_SF_ZBIN") != "0" and os.environ.get("CPM_SF_F16") != "0"
+    columns = k_columns(w)
+    flop_per_pair = (64.0 if sf_fp32 else 128.0) if zbin else 4.0 if matrix else 8.0
+    flop_per_launch = flop_per_pair * (columns if zbin else nk) * w.m * snaps_per_launch
     achieved = flop_per_launch / sf_avg if sf_avg > 0 else 0.0
     # FP64 MFMA and FP64 vector peaks are both 78.6 TFLOP/s; with b stored in
-    # FP32 the structure factors run on FP16 matrix cores with split operands
-    # (2.5 PFLOP/s dense; three products per algorithmic one) or, switched
-    # to, on FP32 matrix cores (157.3 TFLOP/s)
+    # FP32 the sums run on FP32 matrix cores (157.3 TFLOP/s), explicit structure
+    # factors on FP16 ones with split operands (2.5 PFLOP/s dense; three
+    # products per algorithmic one)
     peak = PEAK_FP16_MFMA if sf_f16 else PEAK_FP32_VALU if sf_fp32 else PEAK_FP64_VALU
-    sf_kernel = ("cpm::k_sf_mfma16<2>" if sf_f16 else "cpm::k_sf_mfma32" if sf_fp32
-                 else "cpm::k_sf_mfma")
+    sf_kernel = ("cpm::k_zb_sums" if zbin else "cpm::k_sf_mfma16<2>" if sf_f16
+                 else "cpm::k_sf_mfma32" if sf_fp32 else "cpm::k_sf_mfma")
     traffic = stored_traffic(name, sf_kernel, snaps_per_launch)
     sf_bound = "mfma" if matrix else "alu"
 
@@ -367,7 +373,9 @@ def run_workload(args, w, B, name, steps, warmup, calibrate_copy):
         "roofline": {"kernel": "structure_factor", "bound": sf_bound,
                      "achieved": achieved / 1e12, "peak": peak / 1e12, "unit": "TFLOP/s",
                      "frac": achieved / peak, "traffic": traffic,
-                     "flop_per_launch": flop_per_launch, "flop_per_k_charge_pair": flop_per_pair,
+                     "flop_per_launch": flop_per_launch,
+                     ("flop_per_column_charge_pair" if zbin else "flop_per_k_charge_pair"):
+                         flop_per_pair,
                      "avg_launch_us": sf_avg * 1e6,
                      "configurations_per_launch": snaps_per_launch,
                      "launch_group": int(ctx.info("group")),
@@ -401,7 +409,7 @@ def run_mixed(args):
     graphene cells; electrolyte 10 N water charges + 1 M ions), 128
     configurations each: per step every A is assembled and inverted (on the
     context's second stream, beside the b of the instances), b is computed
-    per instance (FP32, from the FP32 structure factors), and all instances
+    per instance (FP32, k space on FP32 matrix cores), and all instances
     are solved by cpm_solve_grouped (split-BF16, refined) in one persistent
     launch per S~ product."""
     import numpy as np
@@ -520,6 +528,14 @@ def matvec_roofline(ctx, w, xyz, dev, reps=20):
     return out
 
 
+def k_columns(w):
+    """Columns (n_x, n_y >= 0) of the k set, mirrors in n_x and n_y not counted."""
+    kc = 2.0 * w.alpha * math.sqrt(math.log(1e8))
+    ax, ay = 2.0 * math.pi / w.Lx, 2.0 * math.pi / w.Ly
+    return sum(1 for nx in range(int(kc / ax) + 1) for ny in range(int(kc / ay) + 1)
+               if (nx * ax) ** 2 + (ny * ay) ** 2 <= kc * kc)
+
+
 def count_pairs(w, xyz_one):
     """Electrode-electrolyte pairs closer than r_c in one configuration (all
     periodic images in x and y; the slab clearance keeps z images beyond r_c)."""
@@ -541,7 +557,7 @@ def count_pairs(w, xyz_one):
 
 def real_space_roofline(w, xyz, R, eid, bvec, group, name, reps=3):
     """FP64 rate of the real-space b kernel on its own: in the timed step it
-    shares the chip with the structure factors (a stream of its own), so its
+    shares the chip with the k-space sums (a stream of its own), so its
     event time there is not its speed.  A second context with the real-space
     pass on the context stream (CPM_RS_CONCURRENT=0, read when a context is
     created) forms b for `reps` launch groups of the step's size; rate =
@@ -588,7 +604,7 @@ def real_space_roofline(w, xyz, R, eid, bvec, group, name, reps=3):
             "flop_per_pair": REAL_SPACE_FLOP_PER_PAIR, "configurations_per_launch": per_launch_cfg,
             "avg_launch_us": avg * 1e6, "us_per_configuration": avg * 1e6 / per_launch_cfg,
             "measured": f"{reps} launch groups of {g} configurations, the real-space pass alone "
-                        "on the context stream (in the timed step it overlaps the structure factors)"}
+                        "on the context stream (in the timed step it overlaps the k-space sums)"}
 
 
 def batched_comparator(w, B=256, reps=5):
@@ -799,19 +815,21 @@ def stored_traffic(workload, kernel, configs_per_launch):
     FETCH_SIZE / WRITE_SIZE summary (each counter scaled by what it reads for
     a 1 GiB device copy), per configuration times the timed run's average
     configurations per launch (a step's last launch group can be partial);
-    None when the kernel source changed since the counters were taken, when
+    None when a kernel source changed since the counters were taken, when
     no record covers this kernel and workload, or when the average launch
     holds fewer than 3/4 (or more) of the profiled configurations."""
     import hashlib
     path = os.path.join(ROOT, "profiles", "structure_factor_traffic.json")
-    src = os.path.join(ROOT, "paper_2203_15461_amd", "csrc", "bvector.hip")
     try:
         rec = json.load(open(path))
-        digest = hashlib.sha256(open(src, "rb").read()).hexdigest()
+        sources = hashlib.sha256()
+        for f in rec.get("sources", []):
+            with open(os.path.join(ROOT, "paper_2203_15461_amd", "csrc", f), "rb") as src:
+                sources.update(src.read())
     except (OSError, ValueError):
         return None
     entry = rec.get("kernels", {}).get(kernel, {}).get(workload)
-    if not entry or rec.get("bvector_sha256") != digest:
+    if not entry or rec.get("sources_sha256") != sources.hexdigest():
         return None
     per = entry.get("configurations_per_launch", 1)
     if configs_per_launch > per * 1.001 or configs_per_launch < 0.75 * per:
@@ -873,7 +891,7 @@ def accuracy_vs_oracle(w, q_ref, Q_ref):
     """Error of each solve path in q and in the electrode totals against the
     oracle's FP64 result for snapshot 0: the plain FP64 path (one vector,
     streaming matvec), and the batched FP32 and split-BF16 paths (a batch of 8
-    snapshots, snapshot 0 first; b in FP32 from the FP32 structure factors,
+    snapshots, snapshot 0 first; b in FP32, k space on FP32 matrix cores,
     and for split-BF16 also b in FP64), each with one FP64 refinement step."""
     import numpy as np
     import torch

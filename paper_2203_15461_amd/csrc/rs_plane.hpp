@@ -24,12 +24,15 @@ namespace cpm {
 // the marked ones in FP64 (s < rc^2 exactly; the others take the zero polynomial
 // after the table's last).  The summation order of an atom is fixed by the data
 // (deterministic).
-// Issue slots bound it (VALU 64 % busy, LDS gathers 60 % with their conflicts): about
-// 41 instructions per pair step of a wave, of whose lanes 64 to 78 % have a pair
-// left; the rest is shared by the screen and the blocks' near tests.  So the screen
-// shifts sign bits into the mask (4 instructions per entry; compare and set took 7.5)
-// and the other images of a block are looked at only where one of them can reach the
-// tile.  MEASURED
+// What bounds it: LDS broadcasts and the vector issue slots together (the FP64 step
+// of a wave is about 41 instructions, of whose lanes 64 to 78 % have a pair left),
+// at 2.6 of 4 possible waves per SIMD.  So the screen, a 64 x 64 product of depth 3,
+// is taken on the matrix cores (32x32x2 FP32 twice per quarter: the entries arrive
+// as operands instead of as one broadcast per entry and lane; sign bits become each
+// lane's mask), and the other images of a block are looked at only where one of them
+// can reach the tile.  The kernel alone: 20064 atoms, one configuration, 288 to
+// 250 us (283 with the instructions cut but the broadcasts left); 2880 atoms, 64
+// configurations, 78 to 70 us.
 constexpr int RP_RING = 128, RP_WAVES = 8;
 typedef float f16v __attribute__((ext_vector_type(16)));
 struct RpWave {
