@@ -81,34 +81,72 @@ __device__ void store_partials(const double (&v)[NF], const int (&f)[NF],
 #pragma unroll
   for (int k = 0; k < NF; ++k) sh[k][w][s] = v[k];
   __syncthreads();
-  if (threadIdx.x < VL) {
 #pragma unroll
-    for (int k = 0; k < NF; ++k) red[((size_t)blockIdx.x * CG_RED + f[k]) * VL + s] = sum16(sh[k], s);
-  }
+  for (int k = 0; k < NF; ++k)                       // (a wave per field)
+    if (w == k) red[((size_t)blockIdx.x * CG_RED + f[k]) * VL + s] = sum16(sh[k], s);
 }
 
-// Totals over the nprod blocks of the producing kernel of fields f[0..NF),
-// computed by every block of the consuming kernel in the same fixed order
+// Totals over the nprod[k] >= 1 blocks of the producing kernel of fields f[k],
+// k < NF, computed by every block of the consuming kernel in the same fixed order
 // (wave w adds blocks w, w + 16, ..., then a fixed tree over the waves), so
 // all blocks see identical values without any inter-block communication.
-// out[k][s] is valid for all threads after the call.
+// load() asks for the first four partials of every field, sum() forms the totals:
+// out[k][s] is valid for all threads after it.
 template <int NF>
-__device__ void block_totals(const double* __restrict__ red, int nprod, const int (&f)[NF],
-                             double (*out)[VL]) {
-  __shared__ double sh[NF][CG_WAVES][VL];
-  const int s = threadIdx.x & 63, w = threadIdx.x >> 6;
+struct Totals {
+  double v[NF][4];
+  __device__ __forceinline__ void load(const double* __restrict__ red, const int (&nprod)[NF],
+                                       const int (&f)[NF], int b0) {
+    const int s = threadIdx.x & 63;
 #pragma unroll
-  for (int k = 0; k < NF; ++k) {
-    double a = 0.0;
-    for (int b = w; b < nprod; b += CG_WAVES) a += red[((size_t)b * CG_RED + f[k]) * VL + s];
-    sh[k][w][s] = a;
-  }
-  __syncthreads();
-  if (threadIdx.x < VL) {
+    for (int k = 0; k < NF; ++k)
 #pragma unroll
-    for (int k = 0; k < NF; ++k) out[k][s] = sum16(sh[k], s);
+      for (int u = 0; u < 4; ++u)
+        v[k][u] = red[((size_t)min(b0 + u * CG_WAVES, nprod[k] - 1) * CG_RED + f[k]) * VL + s];
   }
-  __syncthreads();
+  __device__ static __forceinline__ int wave() {
+    return __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  }
+  __device__ __forceinline__ void load(const double* __restrict__ red, const int (&nprod)[NF],
+                                       const int (&f)[NF]) {
+    load(red, nprod, f, wave());
+  }
+  __device__ __forceinline__ void sum(const double* __restrict__ red, const int (&nprod)[NF],
+                                      const int (&f)[NF], double (*out)[VL]) {
+    __shared__ double sh[NF][CG_WAVES][VL];
+    const int s = threadIdx.x & 63, w = wave();
+    double a[NF];
+    int most = 0;
+#pragma unroll
+    for (int k = 0; k < NF; ++k) {
+      a[k] = 0.0;
+      most = max(most, nprod[k]);
+    }
+    for (int b0 = w;;) {
+#pragma unroll
+      for (int k = 0; k < NF; ++k)
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          a[k] = b0 + u * CG_WAVES < nprod[k] ? a[k] + v[k][u] : a[k];
+      b0 += 4 * CG_WAVES;
+      if (b0 >= most) break;
+      load(red, nprod, f, b0);
+    }
+#pragma unroll
+    for (int k = 0; k < NF; ++k) sh[k][w][s] = a[k];
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < NF; ++k)
+      if (w == k) out[k][s] = sum16(sh[k], s);
+    __syncthreads();
+  }
+};
+template <int NF>
+__device__ __forceinline__ void block_totals(const double* __restrict__ red, const int (&nprod)[NF],
+                                             const int (&f)[NF], double (*out)[VL]) {
+  Totals<NF> t;
+  t.load(red, nprod, f);
+  t.sum(red, nprod, f, out);
 }
 
 // ---- real-space + self part of A in ELL form (slot space) -----------------
@@ -443,6 +481,48 @@ __global__ void __launch_bounds__(256) k_proj_one(int nslot, int M2, const int* 
 // ---- A p and the conjugate-gradient steps ---------------------------------
 // Every kernel below runs on the same grid (nblk blocks of CG_WAVES waves),
 // so the partials of one are summed by the next over the same block count.
+// Latency bounds those of an iteration (1.5 MB vectors at 2880 atoms): a chain of
+// totals, then the wave's rows, three or four of them, one after another.  The rows
+// depend on the totals only in their arithmetic, so CG_U of them are loaded ahead
+// of the totals and each further batch at once: apply, update and direction take
+// 11.2, 7.6 and 7.2 us at 2880 atoms (16.6, 11.4, 9.8 row by row after the totals;
+// 64 right-hand sides 4.75 -> 4.12 ms).
+constexpr int CG_U = 4;
+
+// the atoms of this wave's next CG_U rows (-1: pad, or no row) and the rows'
+// offsets in the vectors (a row that is there)
+__device__ __forceinline__ void batch_rows(const Rows& w, int nslot, int s,
+                                           const int* __restrict__ slot_atom, int (&at)[CG_U],
+                                           size_t (&o)[CG_U]) {
+#pragma unroll
+  for (int u = 0; u < CG_U; ++u) {
+    const int r = w.r + u * w.step, rc = min(r, nslot - 1);
+    at[u] = r < nslot ? slot_atom[rc] : -1;
+    o[u] = (size_t)rc * VL + s;
+  }
+}
+__device__ __forceinline__ void batch_load(const double* __restrict__ v, const size_t (&o)[CG_U],
+                                           double (&x)[CG_U]) {
+#pragma unroll
+  for (int u = 0; u < CG_U; ++u) x[u] = v[o[u]];
+}
+// sum of the parts of each row, in order
+__device__ __forceinline__ void batch_sum(const double* __restrict__ v, int nparts, size_t stride,
+                                          const size_t (&o)[CG_U], double (&x)[CG_U]) {
+#pragma unroll
+  for (int u = 0; u < CG_U; ++u) x[u] = 0.0;
+  for (int q0 = 0; q0 < nparts; q0 += 4) {
+    double t[4][CG_U];
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int u = 0; u < CG_U; ++u) t[q][u] = v[(size_t)min(q0 + q, nparts - 1) * stride + o[u]];
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int u = 0; u < CG_U; ++u) x[u] = q0 + q < nparts ? x[u] + t[q][u] : x[u];
+  }
+}
 
 // moments (sum p, sum p x, sum p y, sum p z) of one row into v[0..4)
 __device__ inline void add_moments(double* v, double p, int i, const double* __restrict__ ex,
@@ -471,29 +551,56 @@ __global__ void __launch_bounds__(CG_BLK) k_cg_apply(
     double* __restrict__ AP, double* __restrict__ red) {
   __shared__ double M[4][VL];
   const int s = threadIdx.x & 63;
-  if (!DENSE) {
-    const int f[4] = {F_M0, F_M0 + 1, F_M0 + 2, F_M0 + 3};
-    block_totals<4>(red, gridDim.x, f, M);
-  }
-  double v[2] = {0.0, 0.0};
-  for (Rows w; w.r < nslot; w.r += w.step) {
-    const int r = w.r, i = slot_atom[r];
-    const double pv = P[(size_t)r * VL + s];
-    double ap = 0.0;
-    if (i >= 0) {
-      if (DENSE) {
-        ap = AP[(size_t)r * VL + s];
-      } else {
-        double phi = 0.0;
-        for (int q = 0; q < nparts; ++q) phi += Phi[((size_t)q * nslot + r) * VL + s];
-        ap = ke * (phi + (background * M[0][s] +
-                          (cx * ex[i] * M[1][s] + cy * ey[i] * M[2][s] + cz * ez[i] * M[3][s]))) +
-             dextra[i] * pv;
+  Rows w;
+  int at[CG_U];
+  size_t o[CG_U];
+  double pv[CG_U], x[CG_U];                          // x: sum of the Phi parts, or Ap
+  double rx[CG_U], ry[CG_U], rz[CG_U], de[CG_U];
+  auto load = [&]() __attribute__((always_inline)) {
+    batch_rows(w, nslot, s, slot_atom, at, o);
+    batch_load(P, o, pv);
+    if (DENSE)
+      batch_load(AP, o, x);
+    else
+      batch_sum(Phi, nparts, (size_t)nslot * VL, o, x);
+    if (!DENSE)
+#pragma unroll
+      for (int u = 0; u < CG_U; ++u) {
+        const int i = max(at[u], 0);
+        rx[u] = ex[i];
+        ry[u] = ey[i];
+        rz[u] = ez[i];
+        de[u] = dextra[i];
       }
+  };
+  const int nb = gridDim.x;
+  const int np[4] = {nb, nb, nb, nb};
+  const int fm[4] = {F_M0, F_M0 + 1, F_M0 + 2, F_M0 + 3};
+  Totals<4> tot;
+  if (!DENSE) tot.load(red, np, fm);
+  load();
+  if (!DENSE) tot.sum(red, np, fm, M);
+  double v[2] = {0.0, 0.0};
+  while (true) {
+#pragma unroll
+    for (int u = 0; u < CG_U; ++u) {
+      if (w.r + u * w.step >= nslot) continue;
+      double ap = 0.0;
+      if (at[u] >= 0) {
+        if (DENSE)
+          ap = x[u];
+        else
+          ap = ke * (x[u] + (background * M[0][s] +
+                             (cx * rx[u] * M[1][s] + cy * ry[u] * M[2][s] + cz * rz[u] * M[3][s]))) +
+               de[u] * pv[u];
+      }
+      if (!DENSE) AP[o[u]] = ap;
+      v[0] += pv[u] * ap;
+      v[1] += ap;
     }
-    if (!DENSE) AP[(size_t)r * VL + s] = ap;
-    v[0] += pv * ap;
-    v[1] += ap;
+    w.r += CG_U * w.step;
+    if (w.r >= nslot) break;
+    load();
   }
   const int f[2] = {F_PAP, F_SAP};
   store_partials<2>(v, f, red);
@@ -513,31 +620,44 @@ __global__ void __launch_bounds__(CG_BLK) k_cg_update(int nslot, int n, int cur,
                                                       const double* __restrict__ AP,
                                                       double* __restrict__ red,
                                                       double* __restrict__ scal) {
-  __shared__ double t[4][VL];
-  __shared__ double z[1][VL];
+  __shared__ double t[5][VL];
   const int s = threadIdx.x & 63;
+  Rows w;
+  int at[CG_U];
+  size_t o[CG_U];
+  double x[CG_U], r[CG_U], p[CG_U], ap[CG_U];
+  auto load = [&]() __attribute__((always_inline)) {
+    batch_rows(w, nslot, s, slot_atom, at, o);
+    batch_load(X, o, x);
+    batch_load(R, o, r);
+    batch_load(P, o, p);
+    batch_load(AP, o, ap);
+  };
   {
-    const int f[4] = {F_PAP, F_SAP, F_RR + cur, F_RRI};
-    block_totals<4>(red, gridDim.x, f, t);
-  }
-  if (npc > 0) {
-    const int f[1] = {F_RZ + cur};
-    block_totals<1>(red, npc, f, z);
+    const int nb = gridDim.x;
+    const int np[5] = {nb, nb, nb, nb, max(npc, 1)};
+    const int f[5] = {F_PAP, F_SAP, F_RR + cur, F_RRI, F_RZ + cur};
+    load();
+    block_totals<5>(red, np, f, t);
   }
   const double pap = t[0][s], mean = t[1][s] / n, rr = t[2][s], rr0 = t[3][s];
-  const double rz = npc > 0 ? z[0][s] : rr;
+  const double rz = npc > 0 ? t[4][s] : rr;
   const bool active = rr > tol2 * rr0 && pap > 0.0;
   const double a = active ? rz / pap : 0.0;
   if (blockIdx.x == 0 && threadIdx.x < VL && active) scal[S_ITERS * VL + s] += 1.0;
   double v[1] = {0.0};
-  for (Rows w; w.r < nslot; w.r += w.step) {
-    const int r = w.r;
-    if (slot_atom[r] < 0) continue;
-    const size_t o = (size_t)r * VL + s;
-    X[o] += a * P[o];
-    const double rn = R[o] - a * (AP[o] - mean);
-    R[o] = rn;
-    v[0] += rn * rn;
+  while (true) {
+#pragma unroll
+    for (int u = 0; u < CG_U; ++u) {
+      if (at[u] < 0) continue;
+      X[o[u]] = x[u] + a * p[u];
+      const double rn = r[u] - a * (ap[u] - mean);
+      R[o[u]] = rn;
+      v[0] += rn * rn;
+    }
+    w.r += CG_U * w.step;
+    if (w.r >= nslot) break;
+    load();
   }
   const int f[1] = {F_RR + (1 - cur)};
   store_partials<1>(v, f, red);
@@ -558,34 +678,55 @@ __global__ void __launch_bounds__(CG_BLK) k_cg_dir(int nslot, int n, int cur, do
                                                    const double* __restrict__ Z,
                                                    double* __restrict__ P, double* __restrict__ red,
                                                    double* __restrict__ scal) {
-  __shared__ double t[3][VL];
-  __shared__ double u[3][VL];
+  __shared__ double t[6][VL];
   const int s = threadIdx.x & 63;
+  const double* src = npc > 0 ? Z : R;
+  Rows w;
+  int at[CG_U];
+  size_t o[CG_U];
+  double x[CG_U], po[CG_U], rx[CG_U], ry[CG_U], rz[CG_U];
+  auto load = [&]() __attribute__((always_inline)) {
+    batch_rows(w, nslot, s, slot_atom, at, o);
+    batch_load(src, o, x);
+    batch_load(P, o, po);
+#pragma unroll
+    for (int u = 0; u < CG_U; ++u) {
+      const int i = max(at[u], 0);
+      rx[u] = ex[i];
+      ry[u] = ey[i];
+      rz[u] = ez[i];
+    }
+  };
   {
-    const int f[3] = {F_RR + cur, F_RR + (1 - cur), F_RRI};
-    block_totals<3>(red, gridDim.x, f, t);
-  }
-  if (npc > 0) {
-    const int f[3] = {F_RZ + cur, F_RZ + (1 - cur), F_ZSUM};
-    block_totals<3>(red, npc, f, u);
+    const int nb = gridDim.x, nz = max(npc, 1);
+    const int np[6] = {nb, nb, nb, nz, nz, nz};
+    const int f[6] = {F_RR + cur, F_RR + (1 - cur), F_RRI, F_RZ + cur, F_RZ + (1 - cur), F_ZSUM};
+    load();
+    block_totals<6>(red, np, f, t);
   }
   const double rr = t[0][s], rn = t[1][s], rr0 = t[2][s];
   const bool go = !first && rr > tol2 * rr0;
-  const double beta = !go ? 0.0 : npc > 0 ? u[1][s] / u[0][s] : rn / rr;
-  const double zmean = npc > 0 ? u[2][s] / n : 0.0;
+  const double beta = !go ? 0.0 : npc > 0 ? t[4][s] / t[3][s] : rn / rr;
+  const double zmean = npc > 0 ? t[5][s] / n : 0.0;
   if (blockIdx.x == 0 && threadIdx.x < VL) {
     scal[S_RR * VL + s] = rn;
     scal[S_RR0 * VL + s] = rr0;
   }
-  const double* src = npc > 0 ? Z : R;
   double m[4] = {0.0, 0.0, 0.0, 0.0};
-  for (Rows w; w.r < nslot; w.r += w.step) {
-    const int r = w.r, i = slot_atom[r];
-    if (i < 0) continue;
-    const size_t o = (size_t)r * VL + s;
-    const double p = (src[o] - zmean) + beta * P[o];
-    P[o] = p;
-    add_moments(m, p, i, ex, ey, ez);
+  while (true) {
+#pragma unroll
+    for (int u = 0; u < CG_U; ++u) {
+      if (at[u] < 0) continue;
+      const double p = (x[u] - zmean) + beta * po[u];
+      P[o[u]] = p;
+      m[0] += p;
+      m[1] += p * rx[u];
+      m[2] += p * ry[u];
+      m[3] += p * rz[u];
+    }
+    w.r += CG_U * w.step;
+    if (w.r >= nslot) break;
+    load();
   }
   store_moments(m, red);
 }
@@ -630,7 +771,7 @@ __global__ void __launch_bounds__(CG_BLK) k_cg_init(int nslot, int n, int g,
   const int s = threadIdx.x & 63;
   {
     const int f[1] = {F_SUM};
-    block_totals<1>(red, gridDim.x, f, t);
+    block_totals<1>(red, {(int)gridDim.x}, f, t);
   }
   const double cm = t[0][s] / n;
   double rr[2] = {0.0, 0.0};
@@ -698,7 +839,7 @@ __global__ void __launch_bounds__(CG_BLK) k_cg_scatter(int nslot, int n, int g, 
   double sh = 0.0;
   if (center) {
     const int f[1] = {F_SUM};
-    block_totals<1>(red, gridDim.x, f, t);
+    block_totals<1>(red, {(int)gridDim.x}, f, t);
     sh = t[0][s] / n;
   }
   for (Rows w; w.r < nslot; w.r += w.step) {
@@ -853,8 +994,11 @@ __device__ inline double tile_sum(const double* __restrict__ V, double (*sh)[VL]
   const int s = threadIdx.x & 63, w = threadIdx.x >> 6;
   const size_t base = (size_t)(tile >= 0 ? tile : blockIdx.x) * 64;
   double a = 0.0;
-  for (int r = w; r < 64; r += 4)
-    a += (phi ? phi[(base + r) * 3 + c] : 1.0) * V[(base + r) * VL + s];
+#pragma unroll
+  for (int k = 0; k < 16; ++k) {
+    const size_t r = base + w + 4 * k;
+    a += (phi ? phi[r * 3 + c] : 1.0) * V[r * VL + s];
+  }
   __syncthreads();
   sh[w][s] = a;
   __syncthreads();
@@ -985,7 +1129,13 @@ __global__ void __launch_bounds__(256) k_bnn_sum(int ntile, int K, int ld, int n
   __shared__ double sy[4][VL];
   const int u = blockIdx.x, s = threadIdx.x & 63, w = threadIdx.x >> 6;
   double a = 0.0;
-  for (int p = w; p < nparts; p += 4) a += Ypart[((size_t)p * ld + u) * VL + s];
+  for (int p0 = w; p0 < nparts; p0 += 32) {
+    double v[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) v[k] = Ypart[((size_t)min(p0 + 4 * k, nparts - 1) * ld + u) * VL + s];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) a = p0 + 4 * k < nparts ? a + v[k] : a;
+  }
   sy[w][s] = a;
   // uniform branch: tile_sum synchronises inside
   const double tt = u < ntile * K ? tile_sum(R, sh, K > 1 ? phi : nullptr, u % K, u / K) : 0.0;
@@ -1043,6 +1193,7 @@ __global__ void __launch_bounds__(CG_BLK) k_bnn_coarse_rows(int ld, const double
   __shared__ double s2[CG_WAVES][VL];
   const int u = blockIdx.x, s = threadIdx.x & 63, w = threadIdx.x >> 6;
   double a = 0.0, b = 0.0;
+#pragma unroll 4
   for (int v = w; v < ld; v += CG_WAVES) {
     const double c = Cinv[(size_t)u * ld + v], h = H[(size_t)u * ld + v];
     const double tv = Tt[(size_t)v * VL + s];
