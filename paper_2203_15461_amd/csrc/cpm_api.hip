@@ -1623,11 +1623,15 @@ cpm_status build_impl(cpm_ctx* c, int n, const double* d_xyz, const int* d_eid, 
       HIP_TRY(c, hipMemcpy(b.bsr_val, bval.data(), bval.size() * sizeof(double), hipMemcpyHostToDevice));
       dfree(c, b.ell_col);
       dfree(c, b.ell_val);
-      // work items of the fused projection / real-space kernel: about 512
-      // items of similar size (a unit: K = 64 of one 64 x 64 output tile)
+      // work items of the fused projection / real-space kernel: about 1024
+      // items of similar size (a unit: K = 64 of one 64 x 64 output tile), of 4
+      // units or more.  64 right-hand sides in ms with 512, 1024, 2048 and 4096
+      // items: 4992 atoms 6.79, 6.30, 6.26, -; 20064 33.6, 28.9, 28.3, 28.8; 40 at
+      // 8400: 9.74, 8.82, 8.94, - (each item adds a part for k_cg_apply to read).
+      // Items of 2 units at 2880 atoms: 3.98 -> 4.04.
       const int kunits = 2 * c->ncp / 64;
       const long U = (long)T * kunits + (long)bcol.size();
-      const int u = (int)std::max<long>(4, (U + 511) / 512);
+      const int u = (int)std::max<long>(4, (U + 1023) / 1024);
       std::vector<int> items;
       int nparts = 1;
       for (int I = 0; I < T; ++I) {
