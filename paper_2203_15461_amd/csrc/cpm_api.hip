@@ -676,8 +676,9 @@ cpm_status ensure_step_buffers(cpm_ctx* c) {
   c->rchunks = std::max(1, std::min(512 / atom_blocks, std::max(1, c->m / 32)));
   TRY(dalloc_cap(c, &b.sf_part, (size_t)2 * c->nk * c->mchunks));
   const bool fast = c->sf_mfma && c->nlayers > 0;
-  // explicit structure factors: unless both kinds of b take the binned sums
-  const bool explicit_sf = !(zb_usable(c, 0) && zb_usable(c, 1));
+  // explicit structure factors: unless both kinds of b take the binned sums, in
+  // batches of any size (smaller ones than pv_fast_min take the general path)
+  const bool explicit_sf = !(zb_usable(c, 0) && zb_usable(c, 1)) || c->pv_fast_min > 1;
   const size_t mpad64 = (size_t)std::max(64, (c->m + 63) / 64 * 64);
   if (fast && !explicit_sf) {
     // configurations per launch group, within ~1 GB: sorted charges,
