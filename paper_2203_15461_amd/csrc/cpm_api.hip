@@ -795,15 +795,30 @@ cpm_status ensure_kpart(cpm_ctx* c, size_t len) {
   return CPM_OK;
 }
 
-// work for the partial tiles of split FP64 products: without it (no memory) they
-// run unsplit
-void ensure_gemm_work(cpm_ctx* c, GemmWork& w, size_t len) {
-  if (len <= w.len) return;
-  dfree(c, w.p);
-  w.len = dalloc(c, &w.p, len) == CPM_OK ? len : 0;
-}
-
 constexpr int MVQ_BATCH = 3;     // vectors of a one-launch solve (GEMM from 4 on in FP64)
+
+// the counters of one-launch solves, and work for the partial tiles of split FP64
+// products (without it, for want of memory, they run unsplit).  They come with the
+// inverse: a solve that needed them first would allocate, which makes a captured
+// step's replay refuse and fails under a capture of the caller's.
+cpm_status ensure_solve_scratch(cpm_ctx* c) {
+  Buffers& b = c->b;
+  if (matvec_q_fits(c->npad) && !b.mvcount) {
+    const int zero[MVQ_BATCH] = {};
+    TRY(dalloc(c, &b.mvcount, MVQ_BATCH));
+    const hipError_t e = hipMemcpy(b.mvcount, zero, sizeof zero, hipMemcpyHostToDevice);
+    if (e != hipSuccess) {
+      dfree(c, b.mvcount);
+      return fail(c, CPM_EHIP, "counters of the solves: %s", hipGetErrorString(e));
+    }
+  }
+  const size_t len = gemm_f64_most_work(c->npad, c->npad);
+  if (len > b.gws.len) {
+    dfree(c, b.gws.p);
+    b.gws.len = dalloc(c, &b.gws.p, len) == CPM_OK ? len : 0;
+  }
+  return CPM_OK;
+}
 
 // work buffers of one solve: the context's own (grown on demand), or carved
 // out of the fixed scratch array of cpm_solve_charges_noalloc
@@ -1254,7 +1269,7 @@ cpm_status ensure_inverse_buffers(cpm_ctx* c, unsigned store_flags, bool factor 
     TRY(dalloc(c, &b.Shi, (size_t)npad * npad));
     TRY(dalloc(c, &b.Slo, (size_t)npad * npad));
   }
-  return CPM_OK;
+  return ensure_solve_scratch(c);
 }
 
 // X <- X A^-1 for `rows` right-hand sides stored as rows (stride npad,
@@ -2105,12 +2120,6 @@ cpm_status sc_prepare(cpm_ctx* c, int batch, const void* d_b, int b_is_f32, unsi
   const bool gemm = (batch >= GEMM_MIN_BATCH && prec == 0) || prec == 2 || c->factor_only;
   const int rows = gemm ? ((batch + TILE - 1) / TILE) * TILE : batch;
   TRY(ensure_solve_buffers(c, rows));
-  if (!gemm && !c->b.mvcount && batch <= MVQ_BATCH) {
-    TRY(dalloc(c, &c->b.mvcount, MVQ_BATCH));
-    HIP_TRY(c, hipMemsetAsync(c->b.mvcount, 0, MVQ_BATCH * sizeof(int), c->stream));
-  }
-  if (gemm && !c->factor_only && prec == 0)
-    ensure_gemm_work(c, c->b.gws, gemm_f64_work(rows, c->npad, c->npad));
   if (prec == 2) {
     const cpm_ctx::GemmCfg cfg = bf16_cfg(c, rows);
     if (cfg.ks > 1) TRY(ensure_kpart(c, (size_t)cfg.ks * rows * c->npad));

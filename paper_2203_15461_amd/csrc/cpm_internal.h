@@ -464,6 +464,7 @@ void launch_gemm_planes(hipStream_t st, const AsmPlanes& pl, int n, double alpha
 // doubles of work that splits an M x N x K product (0: it is better unsplit); with
 // less it runs unsplit.  Only untransposed, full products are split.
 size_t gemm_f64_work(int M, int N, int K);
+size_t gemm_f64_most_work(int N, int K);             // of any M
 void launch_potrf_diag(hipStream_t st, double* Lblk, int ld, double* Dinv, int* flag, int k0);
 // steps of A = L L^T and X = L^-1 (X null: the factor alone); Dinv: L_kk^-1 of the
 // panel at k0, and of the block after the update, which that launch factors.  update:

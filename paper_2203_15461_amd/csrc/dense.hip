@@ -367,6 +367,12 @@ size_t gemm_f64_work(int M, int N, int K) {
   return split ? (size_t)GT_PART * GT_RUNS : 0;
 }
 
+size_t gemm_f64_most_work(int N, int K) {
+  size_t most = 0;
+  for (int M = 64; (long)(M / 64) * (N / 64) <= 512; M += 64) most = std::max(most, gemm_f64_work(M, N, K));
+  return most;
+}
+
 void launch_gemm_f64(hipStream_t st, bool transA, bool transB, int M, int N, int K, double alpha,
                      const double* A, int lda, const double* B, int ldb, double beta, double* C,
                      int ldc, int tri, int kmode, GemmWork work) {
