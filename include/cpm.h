@@ -318,10 +318,12 @@ cpm_status cpm_solve_charges(cpm_ctx* ctx, int batch, const void* d_b, int b_is_
  * capture, tight serving loops, harnesses that forbid hipMalloc: the same
  * solve as cpm_solve_charges (same arguments, modes, kernels and results),
  * with its work buffers in one fixed device array of
- * CPM_NOALLOC_SCRATCH_BYTES per GPU instead of context memory.  Nothing is
- * allocated or freed (the split-BF16 product runs without its split-K
- * option).  The array is held by every GPU the library runs on until the
- * process ends; each call clears the part it uses (a fill kernel).  Sizes:
+ * CPM_NOALLOC_SCRATCH_BYTES per GPU (the partial tiles of split FP64 products
+ * stay in the context, which has them from cpm_invert on).  Nothing is
+ * allocated or freed (a split-BF16 product that cpm_autotune gave a split-K
+ * form runs without it).  The array is held by every GPU the library runs on
+ * until the process ends; each call clears the part it uses (a fill kernel).
+ * Sizes:
  * the batch (rounded up to 64 for the matrix-core modes) times the padded
  * n, 5 doubles per element for the matrix-core modes, 4 otherwise, must fit
  * the array (e.g. 128 configurations at n = 2880), else CPM_EINVAL with the

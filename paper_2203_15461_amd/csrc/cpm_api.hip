@@ -2327,7 +2327,10 @@ cpm_status cpm_solve_charges_noalloc(cpm_ctx* c, int batch, const void* d_b, int
   // qt, res, qpad, bpad (FP64), the BF16 pairs of the left operand (half a
   // matrix of doubles each), the row means (rounded to 256 bytes)
   const size_t means = (rows + 31) / 32 * 32;
-  const size_t need = 4 * sz + (gemm ? sz : 0) + means;
+  // counters of a one-launch solve (cleared with the array); split FP64 products use
+  // the context's partial tiles, as cpm_solve_charges does
+  const bool counters = !gemm && batch <= MVQ_BATCH && matvec_q_fits(c->npad);
+  const size_t need = 4 * sz + (gemm ? sz : 0) + means + (counters ? 2 : 0);
   if (need * sizeof(double) > NOALLOC_BYTES)
     return fail(c, CPM_EINVAL,
                 "batch %d at n = %d needs %zu bytes of work space, more than the %zu of the fixed "
@@ -2344,6 +2347,9 @@ cpm_status cpm_solve_charges_noalloc(cpm_ctx* c, int batch, const void* d_b, int
   w.xhi = gemm ? reinterpret_cast<uint16_t*>(base + 4 * sz + means) : nullptr;
   w.xlo = gemm ? w.xhi + sz : nullptr;
   w.kpart = nullptr;
+  w.gw = c->b.gws;
+  static_assert(MVQ_BATCH * sizeof(int) <= 2 * sizeof(double), "room for the counters");
+  w.mvcount = counters ? reinterpret_cast<int*>(base + 4 * sz + means) : nullptr;
   cpm_ctx::GemmCfg cfg = bf16_cfg(c, (int)rows);
   if (cfg.ks != 1) { cfg.ks = 1; cfg.grid = 0; }   // no split-K partials
   w.bf16 = &cfg;
