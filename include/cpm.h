@@ -460,7 +460,9 @@ cpm_status cpm_get_info(const cpm_ctx* ctx, int key, double* out);
  * comma-separated list of kernel families (for example "structure_factor",
  * "kspace_project", "real_space_b", "matvec_f64", "gemm_f64") restricts it to
  * those.  Each timed launch is bracketed by two HIP event records and its
- * elapsed time is accumulated per family.  Every call clears the totals. */
+ * elapsed time is accumulated per family; a launch that does the work of
+ * several families counts in full under each of them.  Timing changes neither
+ * the launches nor the results.  Every call clears the totals. */
 cpm_status cpm_enable_timing(cpm_ctx* ctx, const char* families);
 
 /* Total milliseconds and launch count of kernel family `name` recorded since

@@ -160,7 +160,9 @@ void resolve_timing(cpm_ctx* c, bool wait) {
   (void)hipGetLastError();
 }
 
-// brackets the launches of one kernel family with events while timing is on
+// brackets the launches of one kernel family with events while timing is on (a launch
+// that does the work of several families has a bracket of each; what is launched does
+// not depend on timing)
 struct Timed {
   cpm_ctx* c;
   const char* name;
@@ -168,7 +170,7 @@ struct Timed {
   hipEvent_t a = nullptr;
   Timed(cpm_ctx* c_, const char* n, hipStream_t s_ = nullptr)
       : c(c_), name(n), st(s_ ? s_ : c_->stream) {
-    if (!c->timing) return;
+    if (!c->timing || !name) return;
     if (!c->timing_only.empty() &&
         std::find(c->timing_only.begin(), c->timing_only.end(), n) == c->timing_only.end())
       return;
@@ -1987,7 +1989,7 @@ cpm_status pv_enqueue(cpm_ctx* c, int batch, const double* d_xyz, void* d_b, int
     // structure factors (VALU/LDS-bound beside MFMA-bound work); it starts
     // after everything enqueued so far (the previous group's final sum,
     // which read its partials) and the final sum of this group waits for it
-    const bool one = zb && !c->timing && zb_one_launch(c, g);   // (timed: a name for each)
+    const bool one = zb && zb_one_launch(c, g);
     const bool conc = fast && !one && c->rs_stream && !c->capturing;
     hipStream_t rst = st;
     if (zb) {
@@ -2017,7 +2019,7 @@ cpm_status pv_enqueue(cpm_ctx* c, int batch, const double* d_xyz, void* d_b, int
       const int np = zb_parts(c, g);
       const RpArgs rs = rp_args(g, n, m, mpad64, rch, rs_sub(c, g), b, c->nmap, b.cq, b.zr, p.Lx,
                                 p.Ly, c->Lz, p.rcut, b.phir_part, rs_target(c, g), b.ptab);
-      { Timed t(c, "structure_factor");
+      { Timed t(c, "structure_factor"), r(c, one ? "real_space_b" : nullptr);
         launch_zb_sums(st, g, zty != 0, c->zb, c->zt[zty], zb_items(c, g), m, mpad64, np,
                        c->nlayers, b.cq, b.zbinoff, p.Lx, p.Ly, c->Lz, b.zpart, one ? &rs : nullptr); }
       { Timed t(c, "sf_reduce");
@@ -2193,8 +2195,8 @@ cpm_status sc_enqueue(cpm_ctx* c, int batch, const void* d_b, int b_is_f32, unsi
   // Every product with S~ acts on a centred vector: S e = 0 makes that exact,
   // and it keeps the rounding of a low-precision S~ away from the large
   // uniform part of b and of the refinement residual.
-  if (!gemm && !refine && !c->timing && w.mvcount && batch <= MVQ_BATCH && matvec_q_fits(npad)) {
-    // (timed: a name for each part)
+  if (!gemm && !refine && w.mvcount && batch <= MVQ_BATCH && matvec_q_fits(npad)) {
+    Timed t(c, mv_name), m(c, "row_means"), f(c, "finalize");
     launch_matvec_q(st, which, n, npad, Sm, batch, d_b, b_is_f32, b.d, b.u, b.scal, b.eid, c->n_e,
                     w.qt, d_q, d_Qe, w.mvcount);
     return launched(c, "solve");
