@@ -376,15 +376,19 @@ void zb_make_items(const ZbPlan& z, bool narrow, ZbItems& out) {
 
 // Form the response table of precision ty if the planes have moved since (its
 // memory is allocated with the step buffers, so a call in the other precision
-// leaves a captured step's buffers alone).
-cpm_status ensure_zb_table(cpm_ctx* c, int ty) {
+// leaves a captured step's buffers alone).  captured: the caller is capturing the
+// stream, so nothing runs yet and the launch belongs to that graph only; from then
+// on a rebuild forms the table itself, as that graph's replays do not come here.
+cpm_status ensure_zb_table(cpm_ctx* c, int ty, bool captured = false) {
   ZbTable& t = c->zt[ty];
+  t.captured = t.captured || captured;
   if (t.ready || !t.H || !c->b.layer_fz) return CPM_OK;
   const ZbPlan& z = c->zb;
   launch_zb_response(c->stream, z.ncu, z.nzt, t.nbins, c->nlayers, zb_terms(ty), z.d_w,
                      c->b.layer_fz, t.H);
   TRY(launched(c, "z-bin response"));
-  t.ready = t.used = true;
+  t.used = true;
+  t.ready = !captured;
   return CPM_OK;
 }
 
@@ -1514,6 +1518,8 @@ cpm_status build_impl(cpm_ctx* c, int n, const double* d_xyz, const int* d_eid, 
     const int nzt = c->sfm_npadc / 2, nslot = c->nmap, T = nslot / 64;
     TRY(dalloc(c, &b.pz, (size_t)c->nlayers * nzt));
     launch_plane_phases(c->stream, c->nlayers, nzt, b.layer_fz, b.pz);
+    for (int ty = 0; ty < 2; ++ty)
+      if (c->zt[ty].captured) TRY(ensure_zb_table(c, ty));
     c->ncp = (c->ncolsort + 31) / 32 * 32;
     c->h_tile_plane.clear();
     for (int L = 0; L < c->nlayers; ++L)
@@ -1939,7 +1945,11 @@ cpm_status pv_prepare(cpm_ctx* c, int batch, const double* d_xyz, void* d_b, int
   if (b_is_f32 != 0 && b_is_f32 != 1) return fail(c, CPM_EINVAL, "b_is_f32 must be 0 or 1");
   TRY(ensure_uploaded(c));
   TRY(ensure_step_buffers(c));
-  if (zb_usable(c, b_is_f32)) TRY(ensure_zb_table(c, zb_type(c, b_is_f32)));
+  if (zb_usable(c, b_is_f32)) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (c->stream) HIP_TRY(c, hipStreamIsCapturing(c->stream, &cap));
+    TRY(ensure_zb_table(c, zb_type(c, b_is_f32), cap != hipStreamCaptureStatusNone));
+  }
   if (c->rs_conc_ok) TRY(ensure_rs_stream(c));
   return CPM_OK;
 }

@@ -83,6 +83,7 @@ struct ZbTable {
   double* H = nullptr;             // nbins x ncu x nlayers x terms
   bool ready = false;              // formed for the current planes
   bool used = false;               // formed at least once
+  bool captured = false;           // read by a graph of the caller's
 };
 
 // partial tiles of split FP64 products (see launch_gemm_f64)

@@ -1,0 +1,87 @@
+"""cpm_potential_vector captured by the caller (not by cpm_capture_step): the first call
+of a precision may be the captured one, eager calls before the graph's first replay are
+right, and replays follow a rebuild that moves the planes.  Every replay, with eager
+work between them, equals the eager result bit for bit; b against the oracle, FP64
+within 1e-11 and FP32 within 2e-6 of the largest entry.
+"""
+import sys
+
+import numpy as np
+import pytest
+
+from oracle import cpm_oracle as O
+from paper_2203_15461_amd import inputs as I
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+TOL = {torch.float64: 1e-11, torch.float32: 2e-6}
+
+
+def say(msg):
+    print(f"[gpu] {msg}", flush=True)
+    sys.stdout.flush()
+
+
+@pytest.fixture(scope="module")
+def cpm():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2203_15461_amd import cpm as C
+    C.lib()
+    return C
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64], ids=["f32", "f64"])
+def test_capture_of_the_callers(cpm, dtype):
+    w = I.small_capacitor("a")
+    p = O.params_for(w)
+    s = torch.cuda.Stream()
+    other = torch.float64 if dtype == torch.float32 else torch.float32
+    eid = torch.as_tensor(w.electrode_id, device="cuda")
+    ctx = cpm.Context(cpm.Params.of(w), s)
+    ctx.set_electrolyte(w.electrolyte_q)
+    # memory that a missing table would be read from: not zeros
+    junk = torch.full((1 << 24,), float("nan"), dtype=torch.float64, device="cuda")
+    torch.cuda.synchronize()
+    del junk
+    torch.cuda.empty_cache()
+    x = torch.as_tensor(I.snapshot(w, 0)[None].copy(), device="cuda")
+    b, ref = (torch.empty((1, w.n), dtype=dtype, device="cuda") for _ in range(2))
+    warm = torch.empty((1, w.n), dtype=other, device="cuda")
+    R0 = np.ascontiguousarray(w.electrode_xyz)
+    torch.cuda.synchronize()
+    ctx.build_elastance(torch.as_tensor(R0, device="cuda"), eid, 2)
+    ctx.potential_vector(x, warm)                  # buffers, in the other precision
+    ctx.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=s):
+        ctx.potential_vector(x, b)
+    torch.cuda.synchronize()
+
+    def check(out, R, snap, what):
+        torch.cuda.synchronize()
+        err = np.abs(out.double().cpu().numpy()[0] -
+                     O.potential_vector(R, I.snapshot(w, snap), w.electrolyte_q, p))
+        err = float(err.max() / np.abs(O.potential_vector(R, I.snapshot(w, snap), w.electrolyte_q, p)).max())
+        say(f"{dtype} {what}: {err:.2e}")
+        assert err < TOL[dtype]
+
+    ctx.potential_vector(x, ref)
+    check(ref, R0, 0, "eager call before the first replay")
+    R = R0
+    for snap, shift in ((0, 0.0), (1, 0.0), (2, 1.25), (0, 1.25), (1, 0.5)):
+        moved = R0 + np.array([0.0, 0.0, shift]) * (w.electrode_id[:, None] == 0)
+        if not np.array_equal(moved, R):
+            R = moved
+            ctx.build_elastance(torch.as_tensor(R, device="cuda"), eid, 2)
+        x.copy_(torch.as_tensor(I.snapshot(w, snap)[None].copy()))
+        b.fill_(float("nan"))
+        torch.cuda.synchronize()
+        with torch.cuda.stream(s):
+            g.replay()
+        check(b, R, snap, f"replay, snapshot {snap}, planes shifted by {shift}")
+        ctx.potential_vector(x, ref)
+        torch.cuda.synchronize()
+        assert torch.equal(ref, b)
+    ctx.close()
