@@ -1768,11 +1768,11 @@ cpm_status cpm_invert(cpm_ctx* c, unsigned store_flags) {
   // 64-wide panels inside blocks of OB columns (a multiple of 64), so that
   // the large trailing updates are rank-OB products (OB / 64 times fewer
   // passes over the trailing matrix than rank-64 ones).  X = L^-1 by forward
-  // substitution (in Ainv's buffer first), grouped alike, in the same launches.
+  // substitution (in S's buffer first), grouped alike, in the same launches.
   const int OB = c->chol_block;
   const unsigned store_before = c->store;
   const bool have_q_before = c->have_q;
-  double* X = factor ? nullptr : b.Ainv;
+  double* X = factor ? nullptr : b.S;
   auto dinv = [&](int k0) { return b.Dinv + (size_t)(k0 / TILE) * TILE * TILE; };
   if (X) launch_set_identity(st, npad, X);
   { Timed t(c, "potrf_diag", st);
@@ -1796,13 +1796,13 @@ cpm_status cpm_invert(cpm_ctx* c, unsigned store_flags) {
     TRY(factor_response(c, st));
     c->store = CPM_STORE_F64;
   } else {
-    // A^-1 = X^T X (lower tiles, k from max(row, col)), result into L's buffer,
-    // then swap names so Ainv holds A^-1
+    // A^-1 = X^T X (lower tiles, k from max(row, col)), always into the same buffer:
+    // a captured step of constrained charges reads it
     { Timed t(c, "lauum", st);
-      launch_gemm_f64(st, true, false, npad, npad, npad, 1.0, X, npad, X, npad, 0.0, b.L, npad, 1, 1);
-      launch_mirror_lower(st, npad, b.L); }
+      launch_gemm_f64(st, true, false, npad, npad, npad, 1.0, X, npad, X, npad, 0.0, b.Ainv, npad, 1,
+                      1);
+      launch_mirror_lower(st, npad, b.Ainv); }
     TRY(launched(c, "lauum"));
-    std::swap(b.L, b.Ainv);
     TRY(form_S(c, st, store_flags));
   }
   c->factor_only = factor;
