@@ -118,9 +118,13 @@ enum {
   CPM_INFO_PC_COARSE = 25,    /*   ... its coarse-space dimension                 */
   CPM_INFO_SF_FP32 = 26,      /* cpm_potential_vector with b_is_f32 forms the     */
                               /* k-space sums on FP16 matrix cores with split     */
-                              /* operands (2) or FP32 matrix cores (1)            */
-  CPM_INFO_RS_PLANE = 27      /* 1: the real-space part of b runs the planar      */
+                              /* operands (2) or FP32 matrix cores (1: the binned */
+                              /* sums or explicit structure factors, see SF_ZBIN) */
+  CPM_INFO_RS_PLANE = 27,     /* 1: the real-space part of b runs the planar      */
                               /* kernel (atoms on z planes, Lz >= 2 r_c)          */
+  CPM_INFO_SF_ZBIN = 28       /* k space of b from charges binned in z, after     */
+                              /* cpm_build_*: 1 for FP64 output, plus 2 for FP32  */
+                              /* output (0: explicit structure factors)           */
 };
 
 /* Method knobs; they map onto the paper's `fix electrode` keywords and the
@@ -288,8 +292,9 @@ cpm_status cpm_set_field(cpm_ctx* ctx, double dv0, int bottom);
  * (CPM_INFO_NLAYERS > 0) every configuration's charges are sorted by z and the
  * k-space sums taken bin by bin in Chebyshev polynomials of z; with FP32 output
  * their operands (formed in FP64) and sums over at most 128 charges are FP32.
- * Other electrodes, and cells of more than 512 bins, take explicit structure
- * factors, with FP32 output on FP16 matrix cores with split operands: every
+ * Other electrodes, and cells of more than 512 bins or response tables above
+ * 2 GiB (bins x in-plane waves x planes), take explicit structure factors
+ * (CPM_INFO_SF_ZBIN tells which), with FP32 output on FP16 matrix cores with split operands: every
  * operand value is carried as two FP16 numbers, hi and 2^11 (value - hi), a
  * product as three FP16 products summed in FP32 over a charge chunk.  The rest
  * of b stays FP64 until the final rounding; FP32 b is within about 1e-6

@@ -3184,6 +3184,7 @@ cpm_status cpm_get_info(const cpm_ctx* c, int key, double* out) {
                  ? (c->sf16_ok && !zb_usable(c, 1) ? 2.0 : 1.0) : 0.0;
       return CPM_OK;
     case CPM_INFO_RS_PLANE: *out = rs_plane(c) ? 1.0 : 0.0; return CPM_OK;
+    case CPM_INFO_SF_ZBIN: *out = (zb_usable(c, 0) ? 1 : 0) + (zb_usable(c, 1) ? 2 : 0); return CPM_OK;
     default: return CPM_EINVAL;
   }
 }
