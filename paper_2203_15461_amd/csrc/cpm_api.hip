@@ -318,13 +318,20 @@ bool zb_one_launch(const cpm_ctx* c, int g) {
 // and its fixed cost (0.95 charges' time) per CU.  One configuration, parts: us:
 // 288 atoms 4: 36.4, 8: 33.0, 16: 30.0, 25: 30.4; 1152 atoms 39: 66, 64: 57, 96: 61;
 // 2880 atoms 39: 56, 64: 50.6, 96: 52.8; 5000 atoms 64: 169, 128: 143.
+int zb_passes(const cpm_ctx* c) { return (c->nlayers + 7) / 8; }
 const ZbItems& zb_items(const cpm_ctx* c, int g) {
   return (double)c->zb.wide.nwg * g * ((c->m + 127) / 128) < 512.0 ? c->zb.narrow : c->zb.wide;
 }
+// Every pass over 8 planes has workgroups of its own; without them in the count many
+// planes had too many parts (2880 atoms on 9, 32 and 64 planes, 16 configurations in
+// FP32: 195, 338 and 574 us, now 170, 267 and 405).  The parts of all configurations
+// stay within 256 MiB.
 int zb_parts(const cpm_ctx* c, int g) {
-  const double wgs = (double)zb_items(c, g).nwg * g;
+  const double wgs = (double)zb_items(c, g).nwg * g * zb_passes(c);
   const bool one = zb_one_launch(c, g);
-  const int most = std::min(256, one ? (c->m + 5) / 6 : (c->m + 31) / 32);
+  const double part = 256.0 * c->zb.nunits * c->nlayers;     // bytes
+  const int fit = (int)std::max(1.0, std::min(256.0, ZB_MAXPARTS / (part * g)));
+  const int most = std::min(fit, one ? (c->m + 5) / 6 : (c->m + 31) / 32);
   const int step = one && most >= 16 ? 16 : 1;
   int best = 1;
   double cost = 1e300;
@@ -688,7 +695,9 @@ cpm_status ensure_step_buffers(cpm_ctx* c) {
   const size_t mpad64 = (size_t)std::max(64, (c->m + 63) / 64 * 64);
   if (fast && !explicit_sf) {
     // configurations per launch group, within ~1 GB: sorted charges,
-    // real-space partials, parts of T
+    // real-space partials, two parts of T each.  Beside that come at most 256 MiB
+    // of parts for few configurations (zb_parts) and the response tables, up to
+    // 2 GiB for each output type.
     const double per = 40.0 * mpad64 + 16.0 * c->n + 16.0 * 32.0 * c->zb.nunits * c->nlayers;
     c->pv_group = std::max(1, std::min(std::min(CG_MAXG, c->pv_group_cap),
                                        (int)(1024.0 * 1024 * 1024 / per)));

@@ -58,6 +58,7 @@ inline int zb_terms(int f32) { return f32 ? 8 : 16; }      // Chebyshev terms pe
 constexpr int ZB_MAXSORT = 512;    // most sort bins (and z bins) of a configuration
 constexpr double ZB_FIXED = 200.0;  // fixed cost of a workgroup's part, in charges
 constexpr double ZB_MAXTABLE = 2.0 * 1024 * 1024 * 1024;   // largest response table (bytes)
+constexpr double ZB_MAXPARTS = 256.0 * 1024 * 1024;        // parts of T beyond one per configuration
 
 // a workgroup item of the binned k-space sums: n_x = nxa .. nxa + nxn - 1 (NU
 // per wave) and the 8 NC values of n_y from ny0 on; shape = NU + 2 (NC - 1)
