@@ -44,7 +44,7 @@ cpm_status dalloc(cpm_ctx* c, T** p, size_t count) {
   if (*p) return CPM_OK;
   void* q = nullptr;
   const size_t bytes = count * sizeof(T) > 0 ? count * sizeof(T) : 16;
-  if (hipMalloc(&q, bytes) != hipSuccess) {
+  if ((c->max_bytes && c->bytes + bytes > c->max_bytes) || hipMalloc(&q, bytes) != hipSuccess) {
     (void)hipGetLastError();
     return fail(c, CPM_ENOMEM, "device allocation of %zu bytes failed", count * sizeof(T));
   }
@@ -671,9 +671,8 @@ void precond_apply(cpm_ctx* c, int parity, const double* R, double* Z) {
                     b.pc_ztr, b.cgred);
 }
 
-cpm_status ensure_step_buffers(cpm_ctx* c) {
+cpm_status size_step_buffers(cpm_ctx* c) {
   Buffers& b = c->b;
-  if (c->step_ready) return CPM_OK;
   c->zperm_ok = false;
   // chunking of the per-snapshot sums (fixed per context, so results are
   // reproducible): ~512 workgroups per kernel, >= 64 charges per SF chunk,
@@ -767,6 +766,24 @@ cpm_status ensure_step_buffers(cpm_ctx* c) {
   }
   c->step_ready = true;
   return CPM_OK;
+}
+
+// b-path work arrays for the current geometry; the explicit structure factors serve
+// where there is no memory for the binned sums' tables and parts
+cpm_status ensure_step_buffers(cpm_ctx* c) {
+  if (c->step_ready) return CPM_OK;
+  cpm_status st = size_step_buffers(c);
+  if (st != CPM_ENOMEM || !(zb_usable(c, 0) || zb_usable(c, 1))) return st;
+  Buffers& b = c->b;
+  dfree(c, b.zpart); dfree(c, b.zcounts); dfree(c, b.zbinoff); dfree(c, b.dtot);
+  for (ZbTable& t : c->zt) {
+    dfree(c, t.H);
+    t.ready = t.used = false;
+  }
+  c->zb_ok = false;
+  st = size_step_buffers(c);
+  if (st != CPM_OK) c->zb_ok = true;
+  return st;
 }
 
 cpm_status ensure_solve_buffers(cpm_ctx* c, int batch) {
@@ -988,6 +1005,7 @@ cpm_status cpm_create(const cpm_params* params, void* hip_stream, cpm_ctx** out)
     const int v = std::atoi(ev);
     c->sf16_nt = v >= 4 ? 4 : v >= 2 ? 2 : 1;
   }
+  if (const char* ev = std::getenv("CPM_MAX_WORKSPACE_MB")) c->max_bytes = (size_t)std::max(0, std::atoi(ev)) << 20;
   if (const char* ev = std::getenv("CPM_SF_ZBIN")) c->zb_ok = std::atoi(ev) != 0;
   if (const char* ev = std::getenv("CPM_RS_PLANE")) c->rs_plane_ok = std::atoi(ev) != 0;
   c->kc = (p.kcut > 0.0) ? p.kcut : 2.0 * p.alpha * std::sqrt(std::log(1.0 / p.kspace_eps));

@@ -355,6 +355,7 @@ struct cpm_ctx {
   double s_sum = 0;                // e^T A^-1 e
   int pivot = -1;
   size_t bytes = 0;
+  size_t max_bytes = 0;            // most device memory of the context (CPM_MAX_WORKSPACE_MB; 0: no bound)
   std::map<const void*, size_t> alloc_sizes;   // device allocations and their sizes
   unsigned long long alloc_gen = 0;    // bumped by every device allocation / free
   std::vector<double> h_v;         // per-electrode potential
@@ -373,7 +374,8 @@ struct cpm_ctx {
   int sf16_nt = 2;                 // ... M tiles per work item (1, 2 or 4)
   bool rs_plane_ok = true;         // planar real-space kernel (pair polynomials in r^2)
   bool factor_only = false;        // cpm_invert kept the Cholesky factor, not S
-  bool zb_ok = true;               // planar k space from z-sorted charges (CPM_SF_ZBIN=0: structure factors)
+  bool zb_ok = true;               // planar k space from z-sorted charges (CPM_SF_ZBIN=0, or no
+                                   // memory for them: structure factors)
   cpm::ZbPlan zb;
   cpm::ZbTable zt[2];              // z bins for FP64 and FP32 sums
   int ncolsort = 0, sfm_tiles = 0, sfm_npadc = 0, sfm_ntot = 0;
