@@ -337,7 +337,9 @@ def run_workload(args, w, B, name, steps, warmup, calibrate_copy):
     matrix = ctx.info("sf_matrix") == 1.0
     sf_prec = ctx.info("sf_fp32") if (b_f32 and matrix) else 0.0
     sf_fp32, sf_f16 = sf_prec == 1.0, sf_prec == 2.0
-    zbin = bool(int(ctx.info("sf_zbin")) & (2 if b_f32 else 1))
+    # the route of one configuration or of full launch groups (alike between them for
+    # the workloads here)
+    zbin = bool(int(ctx.info("sf_zbin")) & (1 if B < 64 else 4) * (2 if b_f32 else 1))
     columns = k_columns(w)
     flop_per_pair = (64.0 if sf_fp32 else 128.0) if zbin else 4.0 if matrix else 8.0
     flop_per_launch = flop_per_pair * (columns if zbin else nk) * w.m * snaps_per_launch

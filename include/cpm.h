@@ -105,7 +105,8 @@ enum {
   CPM_INFO_TUNE_GRID = 15,    /*   ... workgroups of the persistent launch        */
   CPM_INFO_TUNE_US = 16,      /*   ... measured microseconds per product          */
   CPM_INFO_GROUP = 17,        /* configurations per launch group of              */
-                              /* cpm_potential_vector (planar electrodes)         */
+                              /* cpm_potential_vector (planar electrodes; large   */
+                              /* batches with FP64 output)                        */
   CPM_INFO_CG_ITERS = 18,     /* last cpm_solve_cg: most iterations of a vector   */
   CPM_INFO_CG_RESID = 19,     /*   ... largest final |r| / |r0|                   */
   CPM_INFO_ELL_WIDTH = 20,    /* entries per row of the operator's real-space     */
@@ -123,8 +124,10 @@ enum {
   CPM_INFO_RS_PLANE = 27,     /* 1: the real-space part of b runs the planar      */
                               /* kernel (atoms on z planes, Lz >= 2 r_c)          */
   CPM_INFO_SF_ZBIN = 28       /* k space of b from charges binned in z, after     */
-                              /* cpm_build_*: 1 for FP64 output, plus 2 for FP32  */
-                              /* output (0: explicit structure factors)           */
+                              /* cpm_build_*: 1 for one configuration with FP64   */
+                              /* output, 2 with FP32 output, 4 and 8 for batches  */
+                              /* of 64 and more, added (0: explicit structure     */
+                              /* factors for all)                                 */
 };
 
 /* Method knobs; they map onto the paper's `fix electrode` keywords and the
@@ -289,19 +292,23 @@ cpm_status cpm_set_field(cpm_ctx* ctx, double dv0, int bottom);
  * d_xyz: batch x m x 3 FP64 positions (row-major, snapshot-major).
  * d_b: batch x n output, FP64 (b_is_f32 = 0) or FP32 (b_is_f32 = 1, for
  * the reduced-precision solve modes).  For electrodes on z planes
- * (CPM_INFO_NLAYERS > 0) every configuration's charges are sorted by z and the
- * k-space sums taken bin by bin in Chebyshev polynomials of z; with FP32 output
- * their operands (formed in FP64) and sums over at most 128 charges are FP32.
- * Other electrodes, and cells of more than 512 bins or response tables above
- * 2 GiB (bins x in-plane waves x planes), take explicit structure factors
- * (CPM_INFO_SF_ZBIN tells which), with FP32 output on FP16 matrix cores with split operands: every
- * operand value is carried as two FP16 numbers, hi and 2^11 (value - hi), a
- * product as three FP16 products summed in FP32 over a charge chunk.  The rest
- * of b stays FP64 until the final rounding; FP32 b is within about 1e-6
- * (relative to its largest entry) of the FP64 result.  Switches read when a
- * context is created: CPM_SF_ZBIN=0 takes the explicit structure factors for
- * every electrode; CPM_SF_F16=0 their FP32 matrix-core kernel (FP32 phase
- * tables and products, FP32 sums over 128 charges) for FP32 output;
+ * (CPM_INFO_NLAYERS > 0) the k-space sums are taken in one of two ways, by
+ * their cost for the batch (planes, charges, bins, k vectors;
+ * CPM_INFO_SF_ZBIN tells which).  Binned: every configuration's charges are
+ * sorted by z and the sums taken bin by bin in Chebyshev polynomials of z;
+ * with FP32 output their operands (formed in FP64) and sums over at most 128
+ * charges are FP32.  Explicit structure factors, for FP32 output on FP16
+ * matrix cores with split operands: every operand value is carried as two FP16
+ * numbers, hi and 2^11 (value - hi), a product as three FP16 products summed
+ * in FP32 over a charge chunk.  These also serve other electrodes, cells of
+ * more than 512 bins, response tables above 2 GiB (bins x in-plane waves x
+ * planes) and contexts without memory for the tables.  The rest of b stays
+ * FP64 until the final rounding; FP32 b is within about 1e-6 (relative to its
+ * largest entry) of the FP64 result.  Switches read when a context is created:
+ * CPM_SF_ZBIN=0 takes the explicit structure factors for every electrode,
+ * CPM_SF_ZBIN=2 the binned sums wherever the bounds allow; CPM_SF_F16=0 the
+ * FP32 matrix-core structure factors (FP32 phase tables and products, FP32
+ * sums over 128 charges) for FP32 output;
  * CPM_SF_FP32=0 keeps FP64 k-space sums for it.  b
  * includes the real-space erfc sum, the k-space structure-factor term and
  * the electrolyte cross term of the slab correction (Eq. 12). */

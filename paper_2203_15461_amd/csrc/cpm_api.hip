@@ -300,6 +300,49 @@ bool zb_usable(const cpm_ctx* c, int b_is_f32) {
          (double)t.nbins * c->zb.ncu * c->nlayers * zb_terms(ty) * sizeof(double) <= ZB_MAXTABLE;
 }
 
+bool zb_one_launch(const cpm_ctx* c, int g);
+int zb_passes(const cpm_ctx* c) { return (c->nlayers + 7) / 8; }
+
+// Binned or explicit sums for a batch.  Binned, every charge meets 16 or 8 functions of z
+// per column instead of the column's k_z, but once for every 8 planes (a workgroup keeps
+// 8), and every bin that holds charges costs a contraction with the response however few
+// they are.  So explicit structure factors are the faster ones on many planes and for
+// dilute charges in tall cells, and more so with FP32 output, whose bins are narrower.
+// Us per configuration, by terms fitted to b of both routes on 3400 systems per output
+// type (40 to 80000 charges, 1 to 64 planes and configurations, cells of 12 to 110 A
+// times 24 to 200, alpha 0.19 to 0.6), the explicit ones at nine tenths:
+//   binned: passes (charge columns m + bin bins) + edge columns bins planes + a chain of
+//     tiles, chain bins / parts, per launch
+//   explicit: pair |K+| max(m, 64) + column columns planes, + spill |K+| where the
+//     group's partial sums pass the last-level cache, + the launches that one launch of
+//     sums and pairs saves
+// Checked on 5400 others (100 charges and more, as many atoms on a plane as in graphite
+// or a sixth of it): the binned sums always taken cost 6 % (FP64) and 16 % (FP32) more
+// than the better route of each system, at most 3.9 and 4.6 times; the explicit ones 62
+// and 30 %, at most 16 and 9 times; this rule 1.1 and 1.2 %.
+// 64 configurations at 2880 atoms on 8, 25 and 64 planes, FP32, binned and explicit: 297
+// and 681, 649 and 774, 1393 and 1120 us; 1440 atoms, 1000 charges, 48 planes: 340 and 281.
+struct SumCost { double charge, bin, edge, chain_one, chain, pair, column, spill, saved; };
+constexpr SumCost SUM_COST[2] = {{1.5e-6, 4.5e-3, 1.2e-5, 1.2, 0.45, 7.4e-8, 2.2e-4, 1.2e-5, 7.5},
+                                 {4.4e-7, 4.0e-3, 1.2e-5, 0.45, 0.4, 1.8e-8, 2.4e-4, 1.1e-5, 4.0}};
+
+bool zb_takes(const cpm_ctx* c, int b_is_f32, int batch) {
+  if (!zb_usable(c, b_is_f32) || batch < c->pv_fast_min) return false;
+  if (c->zb_always) return true;
+  const int ty = zb_type(c, b_is_f32), g = std::min(batch, std::min(CG_MAXG, c->pv_group_cap));
+  const SumCost& k = SUM_COST[ty];
+  const bool one = zb_one_launch(c, g);
+  const double m = c->m, cols = c->ncolsort, nk = c->nk, planes = c->nlayers;
+  // the charges of a slab cell lie between its electrodes, 1 / slab_factor of the bins
+  const double bins = std::min(m, c->zt[ty].nbins / std::max(1.0, c->p.slab_factor));
+  const double binned = zb_passes(c) * (k.charge * cols * m + k.bin * bins) + k.edge * cols * bins * planes;
+  const double sf = k.pair * nk * std::max(m, 64.0) + k.column * cols * planes +
+                    (16.0 * g * nk > 2.5e8 ? k.spill * nk : 0.0);
+  const double parts = std::max(1.0, std::min(64.0, m / (one ? 6.0 : 32.0)));
+  return g * binned + (one ? k.chain_one : k.chain) * bins / parts <
+         1.1 * (g * sf + (one ? k.saved : 0.0));
+}
+
 // The real-space sums in the launch of the binned sums: for few configurations the
 // second stream's two event waits cost more than the pair sums lose by the sums'
 // registers and LDS (a workgroup per CU instead of two).  In us, two streams ->
@@ -318,7 +361,6 @@ bool zb_one_launch(const cpm_ctx* c, int g) {
 // and its fixed cost (0.95 charges' time) per CU.  One configuration, parts: us:
 // 288 atoms 4: 36.4, 8: 33.0, 16: 30.0, 25: 30.4; 1152 atoms 39: 66, 64: 57, 96: 61;
 // 2880 atoms 39: 56, 64: 50.6, 96: 52.8; 5000 atoms 64: 169, 128: 143.
-int zb_passes(const cpm_ctx* c) { return (c->nlayers + 7) / 8; }
 const ZbItems& zb_items(const cpm_ctx* c, int g) {
   return (double)c->zb.wide.nwg * g * ((c->m + 127) / 128) < 512.0 ? c->zb.narrow : c->zb.wide;
 }
@@ -688,18 +730,23 @@ cpm_status size_step_buffers(cpm_ctx* c) {
   c->rchunks = std::max(1, std::min(512 / atom_blocks, std::max(1, c->m / 32)));
   TRY(dalloc_cap(c, &b.sf_part, (size_t)2 * c->nk * c->mchunks));
   const bool fast = c->sf_mfma && c->nlayers > 0;
-  // explicit structure factors: unless both kinds of b take the binned sums, in
-  // batches of any size (smaller ones than pv_fast_min take the general path)
-  const bool explicit_sf = !(zb_usable(c, 0) && zb_usable(c, 1)) || c->pv_fast_min > 1;
+  // the routes that batches of any size and either output type take
+  const int most = std::min(CG_MAXG, c->pv_group_cap);
+  bool binned[2] = {false, false}, explicit_sf = !fast;
+  for (int f = 0; f < 2; ++f)
+    for (int g = 1; g <= most; ++g) {
+      if (zb_takes(c, f, g)) binned[f] = true;
+      else explicit_sf = true;
+    }
   const size_t mpad64 = (size_t)std::max(64, (c->m + 63) / 64 * 64);
-  if (fast && !explicit_sf) {
+  c->zb_group = c->sf_group = 1;
+  if (binned[0] || binned[1]) {
     // configurations per launch group, within ~1 GB: sorted charges,
     // real-space partials, two parts of T each.  Beside that come at most 256 MiB
     // of parts for few configurations (zb_parts) and the response tables, up to
     // 2 GiB for each output type.
     const double per = 40.0 * mpad64 + 16.0 * c->n + 16.0 * 32.0 * c->zb.nunits * c->nlayers;
-    c->pv_group = std::max(1, std::min(std::min(CG_MAXG, c->pv_group_cap),
-                                       (int)(1024.0 * 1024 * 1024 / per)));
+    c->zb_group = std::max(1, std::min(most, (int)(1024.0 * 1024 * 1024 / per)));
   }
   if (c->sf_mfma && explicit_sf) {
     c->mpad = std::max(64, (c->m + 63) / 64 * 64);
@@ -715,10 +762,9 @@ cpm_status size_step_buffers(cpm_ctx* c) {
     if (fast) {
       const double per = 16.0 * c->sft_rows * c->mpad + 16.0 * c->sfm_pchunk +
                          16.0 * c->n + 32.0 * c->m + 24.0 * ((c->m + 255) / 256);
-      c->pv_group = std::max(1, std::min(std::min(CG_MAXG, c->pv_group_cap),
-                                         (int)(1024.0 * 1024 * 1024 / per)));
+      c->sf_group = std::max(1, std::min(most, (int)(1024.0 * 1024 * 1024 / per)));
     }
-    const int G = c->pv_group;
+    const int G = c->sf_group;
     size_t part_rows = 0;                 // (configuration, chunk) blocks of sfm_part
     for (int g = 1; g <= G; ++g)
       part_rows = std::max(part_rows, (size_t)g * std::max(sf_chunks_for(c, g, false),
@@ -726,34 +772,35 @@ cpm_status size_step_buffers(cpm_ctx* c) {
     TRY(dalloc_cap(c, &b.sfm_part, part_rows * c->sfm_pchunk));
     TRY(dalloc_cap(c, &b.sft, (size_t)G * c->sft_rows * c->mpad));
   }
+  const int groups = std::max(c->zb_group, c->sf_group);
   // (configuration, chunk) rows of the real-space partials
   size_t rrows = (size_t)c->rchunks;
   if (fast)
-    for (int g = 1; g <= c->pv_group; ++g) rrows = std::max(rrows, (size_t)g * rchunks_for(c, g));
+    for (int g = 1; g <= groups; ++g) rrows = std::max(rrows, (size_t)g * rchunks_for(c, g));
   TRY(dalloc_cap(c, &b.sfw, (size_t)2 * c->nk));
   const int pk_rows = c->nlayers > 0 ? layer_project_chunks((int)c->h_cols.size()) : c->kchunks;
   TRY(dalloc_cap(c, &b.phik_part, (size_t)c->n * std::max(pk_rows, c->kchunks)));
   TRY(dalloc_cap(c, &b.phir_part, rrows * c->n));
   c->dip_blocks = std::max(1, (c->m + 255) / 256);
-  TRY(dalloc_cap(c, &b.dip, (size_t)c->pv_group * c->dip_blocks * 3));
+  TRY(dalloc_cap(c, &b.dip, (size_t)groups * c->dip_blocks * 3));
   TRY(dalloc_cap(c, &b.rtab, (size_t)3 * (RS_NT + 1)));
-  if (zb_usable(c, 0) || zb_usable(c, 1)) {
+  if (binned[0] || binned[1]) {
     size_t parts = 0;
-    for (int g = 1; g <= c->pv_group; ++g) parts = std::max(parts, (size_t)g * zb_parts(c, g));
+    for (int g = 1; g <= c->zb_group; ++g) parts = std::max(parts, (size_t)g * zb_parts(c, g));
     TRY(dalloc_cap(c, &b.zpart, parts * c->zb.nunits * c->nlayers * 32));
-    TRY(dalloc_cap(c, &b.zcounts, (size_t)c->pv_group * zb_sort_blocks(c->m) * ZB_MAXSORT));
-    TRY(dalloc_cap(c, &b.zbinoff, (size_t)c->pv_group * (ZB_MAXSORT + 1)));
-    TRY(dalloc_cap(c, &b.dtot, (size_t)c->pv_group * 3));
+    TRY(dalloc_cap(c, &b.zcounts, (size_t)c->zb_group * zb_sort_blocks(c->m) * ZB_MAXSORT));
+    TRY(dalloc_cap(c, &b.zbinoff, (size_t)c->zb_group * (ZB_MAXSORT + 1)));
+    TRY(dalloc_cap(c, &b.dtot, (size_t)c->zb_group * 3));
     for (int f = 0; f < 2; ++f)
-      if (zb_usable(c, f)) {
+      if (binned[f]) {
         ZbTable& t = c->zt[zb_type(c, f)];
         if (!t.H) t.ready = false;
         TRY(dalloc(c, &t.H, (size_t)t.nbins * c->zb.ncu * c->nlayers * zb_terms(zb_type(c, f))));
       }
   }
   TRY(dalloc_cap(c, &b.zperm, mpad64));
-  TRY(dalloc_cap(c, &b.cq, (size_t)c->pv_group * mpad64));
-  TRY(dalloc_cap(c, &b.zr, (size_t)c->pv_group * (mpad64 / 64)));
+  TRY(dalloc_cap(c, &b.cq, (size_t)groups * mpad64));
+  TRY(dalloc_cap(c, &b.zr, (size_t)groups * (mpad64 / 64)));
   launch_pair_table(c->stream, c->p.alpha, c->p.eta, c->p.rcut, b.rtab);
   TRY(launched(c, "pair table"));
   if (!b.ptab) {
@@ -1006,7 +1053,10 @@ cpm_status cpm_create(const cpm_params* params, void* hip_stream, cpm_ctx** out)
     c->sf16_nt = v >= 4 ? 4 : v >= 2 ? 2 : 1;
   }
   if (const char* ev = std::getenv("CPM_MAX_WORKSPACE_MB")) c->max_bytes = (size_t)std::max(0, std::atoi(ev)) << 20;
-  if (const char* ev = std::getenv("CPM_SF_ZBIN")) c->zb_ok = std::atoi(ev) != 0;
+  if (const char* ev = std::getenv("CPM_SF_ZBIN")) {
+    c->zb_ok = std::atoi(ev) != 0;
+    c->zb_always = std::atoi(ev) >= 2;
+  }
   if (const char* ev = std::getenv("CPM_RS_PLANE")) c->rs_plane_ok = std::atoi(ev) != 0;
   c->kc = (p.kcut > 0.0) ? p.kcut : 2.0 * p.alpha * std::sqrt(std::log(1.0 / p.kspace_eps));
   c->ke = (p.coulomb_k > 0.0) ? p.coulomb_k : KE_DEFAULT;
@@ -1972,7 +2022,7 @@ cpm_status pv_prepare(cpm_ctx* c, int batch, const double* d_xyz, void* d_b, int
   if (b_is_f32 != 0 && b_is_f32 != 1) return fail(c, CPM_EINVAL, "b_is_f32 must be 0 or 1");
   TRY(ensure_uploaded(c));
   TRY(ensure_step_buffers(c));
-  if (zb_usable(c, b_is_f32)) {
+  if (zb_takes(c, b_is_f32, batch)) {
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     if (c->stream) HIP_TRY(c, hipStreamIsCapturing(c->stream, &cap));
     TRY(ensure_zb_table(c, zb_type(c, b_is_f32), cap != hipStreamCaptureStatusNone));
@@ -1989,16 +2039,16 @@ cpm_status pv_enqueue(cpm_ctx* c, int batch, const double* d_xyz, void* d_b, int
   Buffers& b = c->b;
   hipStream_t st = c->stream;
   // FP64 structure factors on matrix cores unless switched off; planar
-  // electrodes then take the grouped path (pv_group configurations per
+  // electrodes then take the grouped path (zb_group or sf_group configurations per
   // launch, k_z folded into the planes, projection fused into the combine)
   const bool mfma = c->sf_mfma && c->use_sf_mfma;
   const bool fast = mfma && c->nlayers > 0 && batch >= c->pv_fast_min;
   // b stored in FP32 (the reduced-precision solve path): structure factors on
   // FP32 matrix cores, FP32 phase tables (switch: CPM_SF_FP32=0)
   const int sf32 = (b_is_f32 && c->sf32_ok) ? (c->sf16_ok ? 2 : 1) : 0;
-  const bool zb = fast && zb_usable(c, b_is_f32);
+  const bool zb = fast && zb_takes(c, b_is_f32, batch);
   const int zty = zb_type(c, b_is_f32);
-  const int G = fast ? c->pv_group : 1;
+  const int G = !fast ? 1 : zb ? c->zb_group : c->sf_group;
   const int mpad64 = std::max(64, (m + 63) / 64 * 64);
   // the charges ordered by z (from the first configuration of a large
   // batch) for the real-space pass, so that whole blocks fall outside the
@@ -3197,7 +3247,7 @@ cpm_status cpm_get_info(const cpm_ctx* c, int key, double* out) {
     case CPM_INFO_TUNE_KS: *out = c->last_tune.ks; return CPM_OK;
     case CPM_INFO_TUNE_GRID: *out = c->last_tune.grid; return CPM_OK;
     case CPM_INFO_TUNE_US: *out = c->last_tune.us; return CPM_OK;
-    case CPM_INFO_GROUP: *out = c->pv_group; return CPM_OK;
+    case CPM_INFO_GROUP: *out = zb_takes(c, 0, CG_MAXG) ? c->zb_group : c->sf_group; return CPM_OK;
     case CPM_INFO_CG_ITERS: *out = c->cg_iters; return CPM_OK;
     case CPM_INFO_CG_RESID: *out = c->cg_resid; return CPM_OK;
     case CPM_INFO_ELL_WIDTH: *out = c->ell_width; return CPM_OK;
@@ -3208,10 +3258,13 @@ cpm_status cpm_get_info(const cpm_ctx* c, int key, double* out) {
     case CPM_INFO_PC_COARSE: *out = (double)c->pc_tiles * c->pc_kuse; return CPM_OK;
     case CPM_INFO_SF_FP32:
       *out = (c->sf_mfma && c->use_sf_mfma && c->sf32_ok)
-                 ? (c->sf16_ok && !zb_usable(c, 1) ? 2.0 : 1.0) : 0.0;
+                 ? (c->sf16_ok && !zb_takes(c, 1, CG_MAXG) ? 2.0 : 1.0) : 0.0;
       return CPM_OK;
     case CPM_INFO_RS_PLANE: *out = rs_plane(c) ? 1.0 : 0.0; return CPM_OK;
-    case CPM_INFO_SF_ZBIN: *out = (zb_usable(c, 0) ? 1 : 0) + (zb_usable(c, 1) ? 2 : 0); return CPM_OK;
+    case CPM_INFO_SF_ZBIN:
+      *out = (zb_takes(c, 0, 1) ? 1 : 0) + (zb_takes(c, 1, 1) ? 2 : 0) +
+             (zb_takes(c, 0, CG_MAXG) ? 4 : 0) + (zb_takes(c, 1, CG_MAXG) ? 8 : 0);
+      return CPM_OK;
     default: return CPM_EINVAL;
   }
 }

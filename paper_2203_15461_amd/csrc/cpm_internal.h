@@ -152,8 +152,8 @@ struct Buffers {
   int* zbinoff = nullptr;          // first sorted charge of each z bin, per configuration
   double* zpart = nullptr;         // parts of T(c, L) (zbasis.hip)
   double* dtot = nullptr;          // electrolyte dipole per configuration
-  double4* cq = nullptr;           // gathered charges (x, y wrapped, z, q), pv_group x mpad64
-  double2* zr = nullptr;           // z range of each 64-charge block, pv_group x mpad64 / 64
+  double4* cq = nullptr;           // gathered charges (x, y wrapped, z, q), group x mpad64
+  double2* zr = nullptr;           // z range of each 64-charge block, group x mpad64 / 64
   double* qt = nullptr;            // q-tilde (batch x npad)
   double* res = nullptr;           // refinement residual / corrections (batch x npad)
   double* bpad = nullptr;          // padded b for batched solves (bpad_rows x npad)
@@ -376,13 +376,15 @@ struct cpm_ctx {
   bool factor_only = false;        // cpm_invert kept the Cholesky factor, not S
   bool zb_ok = true;               // planar k space from z-sorted charges (CPM_SF_ZBIN=0, or no
                                    // memory for them: structure factors)
+  bool zb_always = false;          // CPM_SF_ZBIN=2: wherever the bounds allow, not by cost
   cpm::ZbPlan zb;
   cpm::ZbTable zt[2];              // z bins for FP64 and FP32 sums
   int ncolsort = 0, sfm_tiles = 0, sfm_npadc = 0, sfm_ntot = 0;
   int sfm_nbz = 2, sfm_nitems = 0, sf16_nitems = 0, mpad = 0, sft_rows = 0, sft_blocks = 1;
   int sfm_pchunk = 0;              // doubles per (configuration, chunk) of sfm_part
   int sfm_maxcnt = 0;              // largest number of n >= 0 of a sorted column
-  int pv_group = 1;                // configurations per launch group (planar fast path)
+  int zb_group = 1, sf_group = 1;  // configurations per launch group (planar): binned sums,
+                                   // explicit structure factors
   int pv_group_cap = 64;           // most configurations per launch group (CPM_PV_GROUP)
   int b_nitems = 0, b_nparts = 1;  // work split of the b-path projection product
   int nmap = 0;                    // length of the real-space atom map

@@ -33,7 +33,8 @@ def cpm():
 
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.float64], ids=["f32", "f64"])
-def test_capture_of_the_callers(cpm, dtype):
+def test_capture_of_the_callers(cpm, dtype, monkeypatch):
+    monkeypatch.setenv("CPM_SF_ZBIN", "2")         # response tables for this small system too
     w = I.small_capacitor("a")
     p = O.params_for(w)
     s = torch.cuda.Stream()

@@ -1,7 +1,7 @@
-"""Which k-space sums cpm_potential_vector takes (info key sf_zbin: 1 FP64 output, plus
-2 FP32 output from charges binned in z; 0 explicit structure factors), by the switches
-and by the sizes alone, and b of each route against the oracle: FP64 within 1e-10, FP32
-within 5e-6 of the largest entry.
+"""Which k-space sums cpm_potential_vector takes (info key sf_zbin: charges binned in z
+for one configuration with FP64 output 1, FP32 output 2, for batches of 64 4 and 8; 0
+explicit structure factors), by the switches, by the bounds and by the sizes, and b of
+each route against the oracle: FP64 within 1e-10, FP32 within 5e-6 of the largest entry.
 """
 import sys
 
@@ -47,10 +47,11 @@ def check(C, params, oparams, R, eid, q, xyz, route, fp32):
 
 
 @pytest.mark.parametrize("env,route,fp32", [
-    ({}, 3, 1), ({"CPM_SF_ZBIN": "0"}, 0, 2), ({"CPM_SF_F16": "0"}, 1, 1), ({"CPM_SF_FP32": "0"}, 3, 0),
+    ({"CPM_SF_ZBIN": "2"}, 15, 1), ({"CPM_SF_ZBIN": "0"}, 0, 2),
+    ({"CPM_SF_ZBIN": "2", "CPM_SF_F16": "0"}, 5, 1), ({"CPM_SF_ZBIN": "2", "CPM_SF_FP32": "0"}, 15, 0),
     ({"CPM_SF_ZBIN": "0", "CPM_SF_F16": "0"}, 0, 1), ({"CPM_SF_ZBIN": "0", "CPM_SF16_NT": "1"}, 0, 2),
     ({"CPM_SF_ZBIN": "0", "CPM_SF16_NT": "4"}, 0, 2), ({"CPM_SF_ZBIN": "0", "CPM_SF_FP32": "0"}, 0, 0),
-    ({"CPM_SF_MFMA": "0"}, 0, 0),
+    ({"CPM_SF_MFMA": "0"}, 0, 0), ({"CPM_SF_ZBIN": "2", "CPM_PV_FAST_MIN": "2"}, 12, 1),
 ], ids=lambda e: "-".join(f"{k[4:]}={v}" for k, v in e.items()) if isinstance(e, dict) else str(e))
 @pytest.mark.parametrize("batch", [1, 5])
 def test_routes_by_switch(cpm, env, route, fp32, batch, monkeypatch):
@@ -64,9 +65,10 @@ def test_routes_by_switch(cpm, env, route, fp32, batch, monkeypatch):
 
 
 # cell heights 3 h whose z bins exceed 512 in neither, in FP32 only, and in both
-@pytest.mark.parametrize("h,route", [(300.0, 3), (350.0, 1), (450.0, 0)])
+@pytest.mark.parametrize("h,route", [(300.0, 15), (350.0, 5), (450.0, 0)])
 @pytest.mark.parametrize("batch", [1, 9])
-def test_routes_by_bins(cpm, h, route, batch):
+def test_routes_by_bins(cpm, h, route, batch, monkeypatch):
+    monkeypatch.setenv("CPM_SF_ZBIN", "2")
     L, m = (9.0, 10.0), 70
     rng = np.random.default_rng(int(h))
     z = np.repeat([0.0, 0.4 * h, h], 12)
@@ -79,7 +81,42 @@ def test_routes_by_bins(cpm, h, route, batch):
     q -= q.mean()
     say(f"cell height {3 * h}, batch {batch}")
     check(cpm, cpm.Params(L[0], L[1], h), O.Params(L[0], L[1], 3 * h, 1.979, 0.3, 12.0, 1e-8),
-          R, (z > 0.5 * h).astype(np.int32), q, xyz, route, 1 if route & 2 else 2)
+          R, (z > 0.5 * h).astype(np.int32), q, xyz, route, 1 if route & 8 else 2)
+
+
+# by cost: the standard capacitor; 1000 charges in a small cell on few and on many planes,
+# dilute charges in a tall one.  Batches below and above a launch group's 64, and one in
+# between, in one context, whose buffers serve both routes
+@pytest.mark.parametrize("planes,L,h,m,route", [(6, 34.0, 75.0, 6128, 15), (16, 25.0, 45.0, 1000, 7),
+                                                (48, 25.0, 45.0, 1000, 3), (8, 25.0, 150.0, 100, 3),
+                                                (64, 30.0, 150.0, 300, 0)])
+def test_routes_by_cost(cpm, planes, L, h, m, route):
+    rng = np.random.default_rng(planes)
+    half = planes // 2
+    z = np.repeat(np.concatenate([np.linspace(0, 6, half), np.linspace(h - 6, h, half)]), 5)
+    R = np.column_stack([rng.uniform(0, L, len(z)), rng.uniform(0, L, len(z)), z])
+    eid = (z > 0.5 * h).astype(np.int32)
+    q = np.where(np.arange(m) < m // 2, 1.0, -1.0)
+    p = O.Params(L, L, 3 * h, 1.979, 0.3, 12.0, 1e-8)
+    base = [np.column_stack([rng.uniform(0, L, m), rng.uniform(0, L, m), rng.uniform(9, h - 9, m)])
+            for _ in range(3)]
+    ref = np.stack([O.potential_vector(R, x, q, p) for x in base])
+    ctx = cpm.Context(cpm.Params(L, L, h))
+    ctx.set_electrolyte(q)
+    ctx.build_elastance(torch.as_tensor(R, device="cuda"), torch.as_tensor(eid, device="cuda"), 2)
+    say(f"{planes} planes, cell {L} x {h}, m {m}: route {int(ctx.info('sf_zbin'))}")
+    assert int(ctx.info("sf_zbin")) == route
+    for batch in (70, 1, 11, 64):
+        idx = np.arange(batch) % 3
+        x = torch.as_tensor(np.stack([base[i] for i in idx]), device="cuda")
+        for dtype, tol in ((torch.float64, 1e-10), (torch.float32, 5e-6)):
+            b = torch.full((batch, len(R)), float("nan"), dtype=dtype, device="cuda")
+            ctx.potential_vector(x, b)
+            ctx.synchronize()
+            err = np.abs(b.double().cpu().numpy() - ref[idx]).max() / np.abs(ref).max()
+            say(f"  batch {batch} {dtype} {err:.2e}")
+            assert err < tol
+    ctx.close()
 
 
 def test_other_electrodes_take_structure_factors(cpm):

@@ -40,6 +40,7 @@ def test_no_room_for_the_binned_sums(cpm, monkeypatch):
     p = O.Params(L[0], L[1], 3 * h, 1.979, 0.3, 12.0, 1e-8)
     ref = np.stack([O.potential_vector(R, x, q, p) for x in xyz])
     monkeypatch.setenv("CPM_PV_GROUP", "4")
+    monkeypatch.setenv("CPM_SF_ZBIN", "2")             # binned wherever there is room
     x = torch.as_tensor(xyz, device="cuda")
     routes, before, after = [], None, None
     for room in (None, 64, 1):                 # MiB beside what the build takes
