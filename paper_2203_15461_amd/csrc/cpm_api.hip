@@ -728,7 +728,10 @@ cpm_status size_step_buffers(cpm_ctx* c) {
   // remain (rchunks is set below, once the group size is known)
   const int atom_blocks = (c->nmap + real_space_block_atoms() - 1) / real_space_block_atoms();
   c->rchunks = std::max(1, std::min(512 / atom_blocks, std::max(1, c->m / 32)));
-  TRY(dalloc_cap(c, &b.sf_part, (size_t)2 * c->nk * c->mchunks));
+  // the vector-unit structure factors, and the path of single configurations
+  const bool valu = !(c->sf_mfma && c->use_sf_mfma);
+  const bool general = valu || c->nlayers == 0 || c->pv_fast_min > 1;
+  if (valu) TRY(dalloc_cap(c, &b.sf_part, (size_t)2 * c->nk * c->mchunks));
   const bool fast = c->sf_mfma && c->nlayers > 0;
   // the routes that batches of any size and either output type take
   const int most = std::min(CG_MAXG, c->pv_group_cap);
@@ -769,17 +772,21 @@ cpm_status size_step_buffers(cpm_ctx* c) {
     for (int g = 1; g <= G; ++g)
       part_rows = std::max(part_rows, (size_t)g * std::max(sf_chunks_for(c, g, false),
                                                            sf_chunks_for(c, g, true)));
-    TRY(dalloc_cap(c, &b.sfm_part, part_rows * c->sfm_pchunk));
-    TRY(dalloc_cap(c, &b.sft, (size_t)G * c->sft_rows * c->mpad));
+    // (one allocation: a large one takes about 35 us)
+    const size_t tables = (size_t)G * c->sft_rows * c->mpad;
+    TRY(dalloc_cap(c, &b.sft, tables + (part_rows * c->sfm_pchunk + 1) / 2));
+    b.sfm_part = reinterpret_cast<double*>(b.sft + tables);
   }
   const int groups = std::max(c->zb_group, c->sf_group);
   // (configuration, chunk) rows of the real-space partials
   size_t rrows = (size_t)c->rchunks;
   if (fast)
     for (int g = 1; g <= groups; ++g) rrows = std::max(rrows, (size_t)g * rchunks_for(c, g));
-  TRY(dalloc_cap(c, &b.sfw, (size_t)2 * c->nk));
-  const int pk_rows = c->nlayers > 0 ? layer_project_chunks((int)c->h_cols.size()) : c->kchunks;
-  TRY(dalloc_cap(c, &b.phik_part, (size_t)c->n * std::max(pk_rows, c->kchunks)));
+  if (general) {
+    const int pk_rows = c->nlayers > 0 ? layer_project_chunks((int)c->h_cols.size()) : c->kchunks;
+    TRY(dalloc_cap(c, &b.sfw, (size_t)2 * c->nk));
+    TRY(dalloc_cap(c, &b.phik_part, (size_t)c->n * std::max(pk_rows, c->kchunks)));
+  }
   TRY(dalloc_cap(c, &b.phir_part, rrows * c->n));
   c->dip_blocks = std::max(1, (c->m + 255) / 256);
   TRY(dalloc_cap(c, &b.dip, (size_t)groups * c->dip_blocks * 3));
@@ -3298,7 +3305,7 @@ void cpm_destroy(cpm_ctx* c) {
   dfree(b.ex); dfree(b.ey); dfree(b.ez); dfree(b.efx); dfree(b.efy); dfree(b.efz); dfree(b.eid);
   dfree(b.layer_of); dfree(b.layer_fz); dfree(b.layerT); dfree(b.amap);
   dfree(b.sc_nx); dfree(b.sc_ny); dfree(b.sc_lo); dfree(b.sc_len); dfree(b.sc_koff); dfree(b.sc_n0);
-  dfree(b.sc_nidx); dfree(b.tile_nb); dfree(b.sfm_part); dfree(b.sfm_items); dfree(b.sf16_items); dfree(b.sft);
+  dfree(b.sc_nidx); dfree(b.tile_nb); dfree(b.sfm_items); dfree(b.sf16_items); dfree(b.sft);
   dfree(b.tile_off); dfree(b.pz); dfree(b.slot_of); dfree(b.b_items); dfree(b.bT); dfree(b.bPhi);
   dfree(b.runs); dfree(b.cols); dfree(b.chunk_col); dfree(b.w2); dfree(b.knx); dfree(b.kny); dfree(b.knz);
   dfree(b.A); dfree(b.L); dfree(b.Dinv); dfree(b.Ainv); dfree(b.S); dfree(b.S32); dfree(b.Shi);

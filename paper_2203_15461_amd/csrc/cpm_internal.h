@@ -109,7 +109,7 @@ struct Buffers {
   // matrix-core structure factors: full (k_x, k_y) columns sorted by k_z extent
   int* sc_nx = nullptr; int* sc_ny = nullptr; int* sc_lo = nullptr; int* sc_len = nullptr;
   int* sc_koff = nullptr; int* sc_n0 = nullptr; int* sc_nidx = nullptr; int* tile_nb = nullptr;
-  double* sfm_part = nullptr;      // chunk partials [chunk][tile][32][npadc]
+  double* sfm_part = nullptr;      // chunk partials [chunk][tile][32][npadc] (behind sft)
   int4* sfm_items = nullptr;       // work items {M tile, first n block, n blocks, 0}
   int4* sf16_items = nullptr;      // the same with <= SF16_NB blocks (split-FP16 kernel)
   int* tile_off = nullptr;         // offset of each M tile's block in a chunk of sfm_part
