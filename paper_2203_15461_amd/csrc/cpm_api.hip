@@ -431,10 +431,10 @@ void zb_make_items(const ZbPlan& z, bool narrow, ZbItems& out) {
 cpm_status ensure_zb_table(cpm_ctx* c, int ty, bool captured = false) {
   ZbTable& t = c->zt[ty];
   t.captured = t.captured || captured;
-  if (t.ready || !t.H || !c->b.layer_fz) return CPM_OK;
+  if (t.ready || !t.H || !c->b.layer_z) return CPM_OK;
   const ZbPlan& z = c->zb;
   launch_zb_response(c->stream, z.ncu, z.nzt, t.nbins, c->nlayers, zb_terms(ty), z.d_w,
-                     c->b.layer_fz, t.H);
+                     t.d_J, c->b.layer_z, c->Lz, t.H);
   TRY(launched(c, "z-bin response"));
   t.used = true;
   t.ready = !captured;
@@ -970,6 +970,8 @@ cpm_status ensure_uploaded(cpm_ctx* c) {
         return CPM_OK;
       };
       TRY(up2(&z.d_units, z.units)); TRY(up2(&z.d_cu_of, z.cu_of)); TRY(up2(&z.d_cols, z.cols));
+      for (ZbTable& t : c->zt)
+        if (!t.J.empty()) TRY(up2(&t.d_J, t.J));
       TRY(up2(&z.d_w, z.w)); TRY(up2(&z.wide.d_items, z.wide.h)); TRY(up2(&z.narrow.d_items, z.narrow.h));
     }
     TRY(dalloc(c, &b.chunk_col, c->h_chunk_col.size()));
@@ -1196,7 +1198,7 @@ cpm_status cpm_create(const cpm_params* params, void* hip_stream, cpm_ctx** out)
       // n and -n together; the column (0, 0) holds only n > 0
       const int lo = c->h_sc_lo[k], hi = lo + c->h_sc_len[k] - 1;
       for (int n = std::max(0, lo); n <= hi; ++n)
-        z.w[(size_t)n * z.ncu + cu] = (n > 0 && lo < 0 ? 2.0 : 1.0) * c->h_w2[c->h_sc_koff[k] + n - lo];
+        z.w[(size_t)(z.nzt - 1 - n) * z.ncu + cu] = (n > 0 && lo < 0 ? 2.0 : 1.0) * c->h_w2[c->h_sc_koff[k] + n - lo];
     }
     zb_make_items(z, false, z.wide);
     zb_make_items(z, true, z.narrow);
@@ -1210,6 +1212,7 @@ cpm_status cpm_create(const cpm_params* params, void* hip_stream, cpm_ctx** out)
       // that a plane's real-space window can skip
       t.sub = std::max(1, std::min(ZB_MAXSORT / t.nbins, (int)std::lround(2.0 * c->Lz / t.nbins)));
       t.nsort = t.nbins * t.sub;
+      if (c->sf_mfma && t.nbins <= ZB_MAXSORT) zb_bessel_factors(z.nzt, t.nbins, zb_terms(ty), t.J);
     }
   }
   *out = c;
@@ -1548,9 +1551,11 @@ cpm_status build_impl(cpm_ctx* c, int n, const double* d_xyz, const int* d_eid, 
       lay[i] = (int)(std::lower_bound(zs.begin(), zs.end(), c->h_xyz[3 * i + 2]) - zs.begin());
     TRY(dalloc(c, &b.layer_of, n));
     TRY(dalloc(c, &b.layer_fz, c->nlayers));
+    TRY(dalloc(c, &b.layer_z, c->nlayers));
     TRY(dalloc(c, &b.layerT, c->h_cols.size() * (size_t)c->nlayers));
     HIP_TRY(c, hipMemcpy(b.layer_of, lay.data(), n * sizeof(int), hipMemcpyHostToDevice));
     HIP_TRY(c, hipMemcpy(b.layer_fz, lfz.data(), c->nlayers * sizeof(double), hipMemcpyHostToDevice));
+    HIP_TRY(c, hipMemcpy(b.layer_z, zs.data(), c->nlayers * sizeof(double), hipMemcpyHostToDevice));
   }
   {
     // real-space thread map: the atoms of each z plane fill whole waves
@@ -3303,7 +3308,7 @@ void cpm_destroy(cpm_ctx* c) {
   if (c->h_async) (void)hipHostFree(c->h_async);
   Buffers& b = c->b;
   dfree(b.ex); dfree(b.ey); dfree(b.ez); dfree(b.efx); dfree(b.efy); dfree(b.efz); dfree(b.eid);
-  dfree(b.layer_of); dfree(b.layer_fz); dfree(b.layerT); dfree(b.amap);
+  dfree(b.layer_of); dfree(b.layer_fz); dfree(b.layer_z); dfree(b.layerT); dfree(b.amap);
   dfree(b.sc_nx); dfree(b.sc_ny); dfree(b.sc_lo); dfree(b.sc_len); dfree(b.sc_koff); dfree(b.sc_n0);
   dfree(b.sc_nidx); dfree(b.tile_nb); dfree(b.sfm_items); dfree(b.sf16_items); dfree(b.sft);
   dfree(b.tile_off); dfree(b.pz); dfree(b.slot_of); dfree(b.b_items); dfree(b.bT); dfree(b.bPhi);
@@ -3317,6 +3322,7 @@ void cpm_destroy(cpm_ctx* c) {
   dfree(b.zcounts); dfree(b.zbinoff); dfree(b.zpart); dfree(b.dtot);
   dfree(c->zb.d_units); dfree(c->zb.d_cu_of); dfree(c->zb.d_cols); dfree(c->zb.d_w);
   dfree(c->zb.wide.d_items); dfree(c->zb.narrow.d_items); dfree(c->zt[0].H); dfree(c->zt[1].H);
+  dfree(c->zt[0].d_J); dfree(c->zt[1].d_J);
   dfree(b.kpart); dfree(b.gws.p); dfree(b.mvcount); dfree(b.ccmU); dfree(b.ccmC); dfree(b.sg); dfree(b.zeta); dfree(b.szeta);
   dfree(b.Qpair); dfree(b.ell_col); dfree(b.ell_val); dfree(b.plane_off); dfree(b.dextra);
   dfree(b.bsr_col); dfree(b.bsr_val); dfree(b.cg_items); dfree(b.asmG); dfree(b.asmF);

@@ -73,7 +73,7 @@ struct ZbPlan {
   int ncu = 0, nunits = 0, nzt = 0;
   std::vector<int2> units, cols;         // {n_x, n_y / 8}; {column of +n_y, -n_y}
   std::vector<int4> cu_of;               // per n_x: {first c, n_y count, first unit, 0}
-  std::vector<double> w;                 // w(c, n), nzt x ncu
+  std::vector<double> w;                 // w(c, n), nzt x ncu, the largest n first
   ZbItems wide, narrow;                  // many / few configurations
   int2* d_units = nullptr; int4* d_cu_of = nullptr; int2* d_cols = nullptr;
   double* d_w = nullptr;
@@ -81,6 +81,8 @@ struct ZbPlan {
 // z bins and response of one precision
 struct ZbTable {
   int nbins = 0, nsort = 0, sub = 1;
+  std::vector<double> J;           // Bessel factors of the response, terms x nzt
+  double* d_J = nullptr;
   double* H = nullptr;             // nbins x ncu x nlayers x terms
   bool ready = false;              // formed for the current planes
   bool used = false;               // formed at least once
@@ -101,6 +103,7 @@ struct Buffers {
   int* layer_of = nullptr;         // plane index per atom (planar electrodes)
   int* amap = nullptr;             // real-space thread -> atom map: whole waves per plane, -1 pads
   double* layer_fz = nullptr;      // fractional z of each plane
+  double* layer_z = nullptr;       // its z as given
   double2* layerT = nullptr;       // T(column, plane)
   // k-set
   KRun* runs = nullptr;            // nruns
@@ -592,7 +595,8 @@ void launch_zb_sort(hipStream_t st, int g, int m, int mpad64, const ZbTable& t, 
                     double Ly, double Lz, const double* xyz, const double* q, int* counts,
                     double4* cq, double2* zr, int* binoff, double* dip);
 void launch_zb_response(hipStream_t st, int ncu, int nzt, int nbins, int nlayers, int P,
-                        const double* w, const double* layer_fz, double* H);
+                        const double* w, const double* J, const double* layer_z, double Lz, double* H);
+void zb_bessel_factors(int nzt, int nbins, int P, std::vector<double>& out);
 // the planar real-space kernel's arguments (its code: rs_plane.hpp)
 struct RpArgs {
   int g, n, m, mpad64, sub, nmap, nx, ny, nz;        // grid nx x ny x nz

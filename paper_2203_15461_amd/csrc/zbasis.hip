@@ -24,6 +24,7 @@
 // 1.3 ms.
 #include <algorithm>
 #include <cmath>
+#include <vector>
 
 #include "cpm_internal.h"
 #include "rs_plane.hpp"
@@ -223,48 +224,72 @@ __global__ void __launch_bounds__(64 * ZS_W) k_zb_scatter(
 
 // ---------------------------------------------------------------------------
 // H: Chebyshev coefficients of G_c(z - z_L) on every bin.  One block per
-// (bin, plane): K(p, n) = (2 - delta_p0) / P sum_q cos(2 pi n (z_q - z_L) / Lz)
-// T_p(t_q) over the P Chebyshev nodes t_q of the bin, n in pieces of ZB_NC,
-// then H(c, p) = sum_n w(c, n) K(p, n) for every column pair c = (n_x, n_y >= 0)
-// (weights stored n by n).
+// (bin, plane).  With z = z_b + hw t, A = n kz1 (z_b - z_L) and B = n kz1 hw,
+//   cos(A + B t) = sum_p K(p, n) T_p(t),
+//   K(p, n) = (2 - delta_p0) (-1)^floor((p + 1) / 2) J_p(B) (cos A, or sin A for odd p)
+// (Jacobi and Anger), n in pieces of ZB_NC, and H(c, p) = sum_n w(c, n) K(p, n) for
+// every column pair c = (n_x, n_y >= 0), the largest n and smallest weights first (J and
+// w are stored in that order).  J: the factors of K without A, from zb_bessel_factors.  The
+// coefficients fall with p like J_p, and so does their rounding: taken from values at
+// the Chebyshev nodes, all p had the rounding of G_c itself, which the charges' uneven
+// T_p sums carried into b (largest error of FP64 b against long double, relative to its
+// largest entry, at 2880 and 4000 atoms: 2.3e-15 to 3.7e-15, now 1.0e-15 to 2.1e-15,
+// explicit structure factors 1.1e-15 to 2.0e-15).  Once per rebuild and output type:
+// 35 us (FP64) and 31 us (FP32) at 2880 atoms, 67 and 58 at 7176, 53 and 46 at 20064.
 // Layout H[((bin ncu + c) nlayers + L) P + i], i the position of p in the
 // matrix-core result layout of the consuming kernel (4 consecutive i per lane
 // group).
 // ---------------------------------------------------------------------------
 constexpr int ZB_NC = 64;
 
+// centre of a z bin, and a charge's distance from it: rounded the same way wherever
+// they are formed (no contraction with what follows)
+__device__ inline double bin_centre(int bin, double width) {
+#pragma clang fp contract(off)
+  return (bin + 0.5) * width;
+}
+__device__ inline double from_centre(double z, double Lz, double invLz, double zc) {
+#pragma clang fp contract(off)
+  return fma(-Lz, floor(z * invLz), z) - zc;
+}
+
 template <int P>
 __global__ void __launch_bounds__(256) k_zb_response(int ncu, int nzt, int nbins, int nlayers,
                                                      const double* __restrict__ w,
-                                                     const double* __restrict__ layer_fz,
-                                                     double* __restrict__ H) {
-  __shared__ double E[P][ZB_NC];                     // cos at node q, index n
+                                                     const double* __restrict__ J,
+                                                     const double* __restrict__ layer_z,
+                                                     double Lz, double* __restrict__ H) {
+  __shared__ double E[2][ZB_NC];                     // cos A, sin A
   __shared__ double K[P][ZB_NC];
-  __shared__ double ct[P][P];                        // (2 - delta) / P T_p(t_q)
   const int bin = blockIdx.x, L = blockIdx.y, tid = threadIdx.x;
-  if (tid < P * P) {
-    const int p = tid / P, q = tid % P;
-    ct[p][q] = (p == 0 ? 1.0 : 2.0) / P * cospi(p * (2 * q + 1) / (2.0 * P));
+  // the bin's centre minus the plane in cells, f + flo: a rounding of f alone would shift
+  // all charges of the bin
+  double f, flo;
+  {
+#pragma clang fp contract(off)
+    const double zc = bin_centre(bin, Lz / nbins), zl = layer_z[L];
+    const double d = zc - zl, back = d + zl;
+    const double dlo = (zc - back) + ((back - d) - zl);
+    f = d / Lz;
+    flo = (fma(-f, Lz, d) + dlo) / Lz;
+    f -= rint(f);
   }
-  const double fz = layer_fz[L];
-  for (int n0 = 0; n0 < nzt; n0 += ZB_NC) {
-    const int nn = min(ZB_NC, nzt - n0);
+  for (int i0 = 0; i0 < nzt; i0 += ZB_NC) {          // n = nzt - 1 - i
+    const int ni = min(ZB_NC, nzt - i0);
     __syncthreads();
-    for (int e = tid; e < P * nn; e += 256) {
-      const int q = e / nn, n = e % nn;
-      // node of the bin minus the plane, in cells
-      const double f = (bin + 0.5) / nbins + 0.5 / nbins * cospi((2 * q + 1) / (2.0 * P)) - fz;
-      double th = (n0 + n) * (f - rint(f));
-      th -= rint(th);
-      E[q][n] = cospi(2.0 * th);
+    if (tid < ni) {
+#pragma clang fp contract(off)
+      const double n = nzt - 1 - i0 - tid, th = n * f;
+      const double lo = fma(n, f, -th) + n * flo;
+      double sn, cs;
+      sincospi(2.0 * ((th - rint(th)) + lo), &sn, &cs);
+      E[0][tid] = cs;
+      E[1][tid] = sn;
     }
     __syncthreads();
-    for (int e = tid; e < P * nn; e += 256) {
-      const int p = e / nn, n = e % nn;
-      double a = 0.0;
-#pragma unroll
-      for (int q = 0; q < P; ++q) a += ct[p][q] * E[q][n];
-      K[p][n] = a;
+    for (int e = tid; e < P * ZB_NC; e += 256) {
+      const int p = e / ZB_NC, i = e % ZB_NC;
+      if (i < ni) K[p][i] = J[p * nzt + i0 + i] * E[p & 1][i];
     }
     __syncthreads();
     // a thread per column pair; FP64 results (P = 16) hold row g + 4 r in
@@ -273,12 +298,12 @@ __global__ void __launch_bounds__(256) k_zb_response(int ncu, int nzt, int nbins
       double a[P];
       double* o = H + (((size_t)bin * ncu + c) * nlayers + L) * P;
 #pragma unroll
-      for (int p = 0; p < P; ++p) a[p] = n0 ? o[P == 16 ? (p & 3) * 4 + (p >> 2) : p] : 0.0;
-#pragma unroll 4
-      for (int n = 0; n < nn; ++n) {
-        const double wn = w[(size_t)(n0 + n) * ncu + c];
+      for (int p = 0; p < P; ++p) a[p] = i0 ? o[P == 16 ? (p & 3) * 4 + (p >> 2) : p] : 0.0;
+#pragma unroll 2
+      for (int i = 0; i < ni; ++i) {
+        const double wn = w[(size_t)(i0 + i) * ncu + c];
 #pragma unroll
-        for (int p = 0; p < P; ++p) a[p] += wn * K[p][n];
+        for (int p = 0; p < P; ++p) a[p] += wn * K[p][i];
       }
 #pragma unroll
       for (int p = 0; p < P; ++p) o[P == 16 ? (p & 3) * 4 + (p >> 2) : p] = a[p];
@@ -473,8 +498,7 @@ __device__ inline void zb_item(const ZbArgs& A, const ZbItem it, int pt, int s, 
       }
     }
     {
-      const double zc = (t.bin + 0.5) * bw;
-      const double tz = in ? (v.z - A.Lz * floor(v.z * invLz) - zc) * ihw : 0.0;
+      const double tz = in ? from_centre(v.z, A.Lz, invLz, bin_centre(t.bin, bw)) * ihw : 0.0;
       double a = 1.0, b = tz;                                // T_0, T_1
       for (int k = 0; k < grp * QB; ++k) {
         const double c = 2.0 * tz * b - a;
@@ -830,6 +854,33 @@ double zb_half_width(double alpha, double kc, int P, double tol) {
   return 2.0 / k * std::exp((std::log(0.5 * tol) + lf + k * k / (4.0 * alpha * alpha)) / P);
 }
 
+// factors (2 - delta_p0) (-1)^floor((p + 1) / 2) J_p(pi n / nbins) at [p nzt + i], p < P,
+// n = nzt - 1 - i (pi n / nbins = n kz1 hw); J_p by Miller's downward recurrence, normalised by
+// J_0 + 2 (J_2 + J_4 + ..) = 1
+void zb_bessel_factors(int nzt, int nbins, int P, std::vector<double>& out) {
+  out.assign((size_t)nzt * P, 0.0);
+  out[nzt - 1] = 1.0;                                // n = 0: J_0 alone
+  std::vector<double> j;
+  for (int n = 1; n < nzt; ++n) {
+    const double x = M_PI * n / nbins;
+    const int top = 2 * (((int)x + P + 40) / 2);     // J_top / J_P below 1e-30 for P <= 16
+    j.assign(top + 2, 0.0);
+    j[top] = 1e-300;
+    double norm = 0.0;
+    for (int k = top; k > 0; --k) {
+      j[k - 1] = 2.0 * k / x * j[k] - j[k + 1];
+      if (std::fabs(j[k - 1]) > 1e200) {             // keep within range
+        for (int i = k - 1; i <= top; ++i) j[i] *= 1e-300;
+        norm *= 1e-300;
+      }
+      if (k - 1 > 0 && (k - 1) % 2 == 0) norm += 2.0 * j[k - 1];
+    }
+    norm += j[0];
+    for (int p = 0; p < P; ++p)
+      out[(size_t)p * nzt + nzt - 1 - n] = (p ? 2.0 : 1.0) * ((p + 1) / 2 % 2 ? -1.0 : 1.0) * j[p] / norm;
+  }
+}
+
 int zb_sort_blocks(int m) { return std::max(1, (m + ZS_BLK - 1) / ZS_BLK); }
 
 void launch_zb_sort(hipStream_t st, int g, int m, int mpad64, const ZbTable& t, double Lx,
@@ -850,9 +901,9 @@ void launch_zb_sort(hipStream_t st, int g, int m, int mpad64, const ZbTable& t, 
 }
 
 void launch_zb_response(hipStream_t st, int ncu, int nzt, int nbins, int nlayers, int P,
-                        const double* w, const double* layer_fz, double* H) {
+                        const double* w, const double* J, const double* layer_z, double Lz, double* H) {
   hipLaunchKernelGGL((P == 16 ? k_zb_response<16> : k_zb_response<8>), dim3(nbins, nlayers),
-                     dim3(256), 0, st, ncu, nzt, nbins, nlayers, w, layer_fz, H);
+                     dim3(256), 0, st, ncu, nzt, nbins, nlayers, w, J, layer_z, Lz, H);
 }
 
 template <bool WITH_RS>
