@@ -1545,17 +1545,19 @@ cpm_status build_impl(cpm_ctx* c, int n, const double* d_xyz, const int* d_eid, 
   if (dense) TRY(dalloc(c, &b.A, (size_t)npad * npad));
   if (c->nlayers > 0) {
     std::vector<int> lay(n);
-    std::vector<double> lfz(c->nlayers);
-    for (int L = 0; L < c->nlayers; ++L) lfz[L] = zs[L] / c->Lz;
+    std::vector<double> lz(2 * c->nlayers);           // fractional z, then z
+    for (int L = 0; L < c->nlayers; ++L) {
+      lz[L] = zs[L] / c->Lz;
+      lz[c->nlayers + L] = zs[L];
+    }
     for (int i = 0; i < n; ++i)
       lay[i] = (int)(std::lower_bound(zs.begin(), zs.end(), c->h_xyz[3 * i + 2]) - zs.begin());
     TRY(dalloc(c, &b.layer_of, n));
-    TRY(dalloc(c, &b.layer_fz, c->nlayers));
-    TRY(dalloc(c, &b.layer_z, c->nlayers));
+    TRY(dalloc(c, &b.layer_fz, lz.size()));
+    b.layer_z = b.layer_fz + c->nlayers;
     TRY(dalloc(c, &b.layerT, c->h_cols.size() * (size_t)c->nlayers));
     HIP_TRY(c, hipMemcpy(b.layer_of, lay.data(), n * sizeof(int), hipMemcpyHostToDevice));
-    HIP_TRY(c, hipMemcpy(b.layer_fz, lfz.data(), c->nlayers * sizeof(double), hipMemcpyHostToDevice));
-    HIP_TRY(c, hipMemcpy(b.layer_z, zs.data(), c->nlayers * sizeof(double), hipMemcpyHostToDevice));
+    HIP_TRY(c, hipMemcpy(b.layer_fz, lz.data(), lz.size() * sizeof(double), hipMemcpyHostToDevice));
   }
   {
     // real-space thread map: the atoms of each z plane fill whole waves
@@ -3308,7 +3310,7 @@ void cpm_destroy(cpm_ctx* c) {
   if (c->h_async) (void)hipHostFree(c->h_async);
   Buffers& b = c->b;
   dfree(b.ex); dfree(b.ey); dfree(b.ez); dfree(b.efx); dfree(b.efy); dfree(b.efz); dfree(b.eid);
-  dfree(b.layer_of); dfree(b.layer_fz); dfree(b.layer_z); dfree(b.layerT); dfree(b.amap);
+  dfree(b.layer_of); dfree(b.layer_fz); dfree(b.layerT); dfree(b.amap);
   dfree(b.sc_nx); dfree(b.sc_ny); dfree(b.sc_lo); dfree(b.sc_len); dfree(b.sc_koff); dfree(b.sc_n0);
   dfree(b.sc_nidx); dfree(b.tile_nb); dfree(b.sfm_items); dfree(b.sf16_items); dfree(b.sft);
   dfree(b.tile_off); dfree(b.pz); dfree(b.slot_of); dfree(b.b_items); dfree(b.bT); dfree(b.bPhi);

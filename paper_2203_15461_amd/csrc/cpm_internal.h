@@ -103,7 +103,7 @@ struct Buffers {
   int* layer_of = nullptr;         // plane index per atom (planar electrodes)
   int* amap = nullptr;             // real-space thread -> atom map: whole waves per plane, -1 pads
   double* layer_fz = nullptr;      // fractional z of each plane
-  double* layer_z = nullptr;       // its z as given
+  double* layer_z = nullptr;       // its z as given (behind layer_fz)
   double2* layerT = nullptr;       // T(column, plane)
   // k-set
   KRun* runs = nullptr;            // nruns

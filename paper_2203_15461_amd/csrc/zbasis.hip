@@ -242,15 +242,10 @@ __global__ void __launch_bounds__(64 * ZS_W) k_zb_scatter(
 // ---------------------------------------------------------------------------
 constexpr int ZB_NC = 64;
 
-// centre of a z bin, and a charge's distance from it: rounded the same way wherever
-// they are formed (no contraction with what follows)
-__device__ inline double bin_centre(int bin, double width) {
-#pragma clang fp contract(off)
-  return (bin + 0.5) * width;
-}
-__device__ inline double from_centre(double z, double Lz, double invLz, double zc) {
-#pragma clang fp contract(off)
-  return fma(-Lz, floor(z * invLz), z) - zc;
+// a charge's distance from the centre (bin + 0.5) width of its z bin, the centre not
+// rounded (k_zb_response forms the bins' phases from the same centres)
+__device__ inline double from_centre(double z, double Lz, double invLz, int bin, double width) {
+  return fma(-(bin + 0.5), width, fma(-Lz, floor(z * invLz), z));
 }
 
 template <int P>
@@ -267,9 +262,9 @@ __global__ void __launch_bounds__(256) k_zb_response(int ncu, int nzt, int nbins
   double f, flo;
   {
 #pragma clang fp contract(off)
-    const double zc = bin_centre(bin, Lz / nbins), zl = layer_z[L];
+    const double width = Lz / nbins, zc = (bin + 0.5) * width, zl = layer_z[L];
     const double d = zc - zl, back = d + zl;
-    const double dlo = (zc - back) + ((back - d) - zl);
+    const double dlo = (zc - back) + ((back - d) - zl) + fma(bin + 0.5, width, -zc);
     f = d / Lz;
     flo = (fma(-f, Lz, d) + dlo) / Lz;
     f -= rint(f);
@@ -498,7 +493,7 @@ __device__ inline void zb_item(const ZbArgs& A, const ZbItem it, int pt, int s, 
       }
     }
     {
-      const double tz = in ? from_centre(v.z, A.Lz, invLz, bin_centre(t.bin, bw)) * ihw : 0.0;
+      const double tz = in ? from_centre(v.z, A.Lz, invLz, t.bin, bw) * ihw : 0.0;
       double a = 1.0, b = tz;                                // T_0, T_1
       for (int k = 0; k < grp * QB; ++k) {
         const double c = 2.0 * tz * b - a;
