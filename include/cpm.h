@@ -118,9 +118,10 @@ enum {
   CPM_INFO_PC_MODE = 24,      /*   ... its form: 0 none, 1 additive, 2 balancing  */
   CPM_INFO_PC_COARSE = 25,    /*   ... its coarse-space dimension                 */
   CPM_INFO_SF_FP32 = 26,      /* cpm_potential_vector with b_is_f32 forms the     */
-                              /* k-space sums on FP16 matrix cores with split     */
-                              /* operands (2) or FP32 matrix cores (1: the binned */
-                              /* sums or explicit structure factors, see SF_ZBIN) */
+                              /* k-space sums of large batches on FP16 matrix     */
+                              /* cores with split operands (2) or FP32 matrix     */
+                              /* cores (1: the binned sums or explicit structure  */
+                              /* factors, see SF_ZBIN)                            */
   CPM_INFO_RS_PLANE = 27,     /* 1: the real-space part of b runs the planar      */
                               /* kernel (atoms on z planes, Lz >= 2 r_c)          */
   CPM_INFO_SF_ZBIN = 28       /* k space of b from charges binned in z, after     */

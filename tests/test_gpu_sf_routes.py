@@ -119,6 +119,54 @@ def test_routes_by_cost(cpm, planes, L, h, m, route):
     ctx.close()
 
 
+@pytest.mark.parametrize("captured,between", [(64, 1), (1, 64)])
+def test_captured_step_beside_the_other_route(cpm, captured, between):
+    """A captured step on one route, eager calls on the other between its replays."""
+    L, h, m, planes = 25.0, 45.0, 1000, 16
+    rng = np.random.default_rng(4)
+    z = np.repeat(np.concatenate([np.linspace(0, 6, 8), np.linspace(h - 6, h, 8)]), 5)
+    R = np.column_stack([rng.uniform(0, L, len(z)), rng.uniform(0, L, len(z)), z])
+    eid = (z > 0.5 * h).astype(np.int32)
+    n = len(z)
+    ctx = cpm.Context(cpm.Params(L, L, h), torch.cuda.Stream())
+    ctx.set_electrolyte(np.where(np.arange(m) < m // 2, 1.0, -1.0))
+    extra = torch.full((n,), 40.0, dtype=torch.float64, device="cuda")   # atoms may come close
+    Rd, ed = torch.as_tensor(R, device="cuda"), torch.as_tensor(eid, device="cuda")
+    torch.cuda.synchronize()
+    ctx.build_elastance(Rd, ed, 2, extra)
+    ctx.invert()
+    ctx.set_potential([-0.5, 0.5])
+    assert int(ctx.info("sf_zbin")) == 7            # FP32: one configuration binned, 64 explicit
+    lo, hi = torch.tensor([0.0, 0.0, 9.0], device="cuda"), torch.tensor([L, L, h - 9.0], device="cuda")
+    gen = torch.Generator(device="cuda").manual_seed(1)
+
+    def positions(batch):
+        return lo + (hi - lo) * torch.rand((batch, m, 3), dtype=torch.float64, device="cuda", generator=gen)
+
+    def buffers(batch):
+        return (torch.empty((batch, n), dtype=torch.float32, device="cuda"),
+                torch.empty((batch, n), dtype=torch.float64, device="cuda"))
+
+    x = positions(captured)
+    (b, q), (be, qe), (bo, _) = buffers(captured), buffers(captured), buffers(between)
+    # what an eager call could allocate, before the capture
+    ctx.solve_charges(torch.zeros((64, n), dtype=torch.float32, device="cuda"), cpm.SOLVE_F64, buffers(64)[1])
+    ctx.synchronize()
+    ctx.capture_step(x, b, cpm.SOLVE_F64, q)
+    for rep in range(3):
+        x.copy_(positions(captured))
+        other = positions(between)
+        torch.cuda.synchronize()
+        ctx.potential_vector(other, bo)
+        ctx.replay_step()
+        ctx.potential_vector(x, be)
+        ctx.solve_charges(be, cpm.SOLVE_F64, qe)
+        ctx.synchronize()
+        say(f"captured {captured}, {between} between, replay {rep}")
+        assert torch.equal(b, be) and torch.equal(q, qe)
+    ctx.close()
+
+
 def test_other_electrodes_take_structure_factors(cpm):
     w = I.small_capacitor("a")
     rng = np.random.default_rng(7)
